@@ -381,14 +381,17 @@ def rooflines(timing, wls, tile, workload):
     if prop:
         dom = max(prop, key=lambda k: prop[k]["total_ms"])
         avg_s = prop[dom]["avg_us"] * 1e-6
-        # a paired launch takes forward step j and (for j < N) a backward step: 2N - 1 steps
-        # in N launches per evaluation
-        steps_per_launch = (2 * N - 1) / N if dom == "pair" else max(1, tile[3])
+        # paired sweeps take 2N - 1 of an evaluation's 2N steps, in N launches of one step
+        # each way, or (row tilings, k = -K) in m launches of up to K, one more when m is odd
+        K = max(1, -tile[3])
+        m = -(-(N - 1) // K)
+        pair_launches = N if K == 1 else m + m % 2
+        steps_per_launch = (2 * N - 1) / pair_launches if dom == "pair" else max(1, tile[3])
         units = V_total * steps_per_launch
         b_unit = bytes_per_update(wl)
         achieved = b_unit * units / avg_s / 1e9
         traffic = MEASURED_TRAFFIC.get((workload, wl.precision, tuple(tile), dom))
-        prop_roof = {"bound": "hbm", "kernel": f"k_{dom}", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        prop_roof = {"bound": "hbm", "kernel": "k_rows" if dom == "pair" and tile[3] < -1 else f"k_{dom}", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "traffic_unit": "bytes per launch (counters)",
                      "traffic_frac": traffic / avg_s / 1e9 / HBM_PEAK_GBS if traffic else None,

@@ -400,12 +400,16 @@ int hsf_get_work(hsf_ctx *ctx, long long *evals, double *site_evals, int reset);
  * core tile of cx*cy*cz sites per workgroup advanced k contour steps per launch;
  * k = 0: one step per launch, read through the caches; k = -1: as k = 0, but each
  * launch takes a forward and a backward step together (N + 1 launches per
- * evaluation instead of 2 N, densities bit for bit those of k = 0).
+ * evaluation instead of 2 N, densities bit for bit those of k = 0); k = -K with K >= 2:
+ * each launch takes up to K steps of both sweeps (row tilings: cx = 64 or, for boxes of
+ * 128 sites in x only, cx = 128 sites of a row per wavefront, cy x cz rows per workgroup;
+ * densities those of k = 0 up to the summation order of Q; not for boxes above 2^28 sites
+ * per replica, and the largest ones in FP32 contexts only).
  * hsf_set_tile accepts only the configurations compiled into the library
  * (HSF_EINVAL otherwise); results do not depend on the choice beyond rounding.
  * hsf_autotune times one density-functional evaluation `reps` times with every
- * configuration that fits the device's LDS and keeps the fastest (best_ms, may be
- * NULL, receives its time).  It leaves densities, fields and LB state unchanged. */
+ * configuration with k <= 0 that suits the replicas' boxes (those with k > 0 were never
+ * the fastest) and keeps the fastest (best_ms, may be NULL, receives its time).  It leaves densities, fields and LB state unchanged. */
 int hsf_set_tile(hsf_ctx *ctx, const int cfg[4]);
 int hsf_get_tile(const hsf_ctx *ctx, int cfg[4]);
 int hsf_autotune(hsf_ctx *ctx, int reps, double *best_ms);

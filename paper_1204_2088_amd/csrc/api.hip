@@ -17,6 +17,7 @@
 
 #include "hsf_internal.h"
 #include "prop_block.h"
+#include "prop_rows.h"
 
 using namespace hsf;
 
@@ -50,8 +51,11 @@ struct hsf_ctx {
     int *bad_hd = nullptr;           // its device-side address
     Plan plan;                       // site plan: kBlock consecutive sites per block
     TileCfg tile{8, 8, 8, 2};        // propagator tile configuration in use
-    Plan tplan;                      // tile plan of `tile`
-    std::vector<int> tile_blk_first; // host copy of the tile plan's first block per replica
+    Plan tplan;                      // tile plan of `dtile`
+    TileCfg dtile{8, 8, 8, 2};       // tiling of the density launch: `tile`, or with row tilings a one-step one
+    Plan rplan;                      // plan of the row sweeps (row tilings only)
+    Plan rplan64;                    // and of their FP64 evaluations in an FP32 context (refinement)
+    int sweep_most = 0;              // most sweep blocks of one replica
     int max_tile_blocks = 0;         // over every configuration (sizes the partials)
     size_t lds_limit = 65536;
     int tuned = 0;
@@ -343,9 +347,10 @@ void tile_blocks(const hsf_ctx *c, const TileCfg &t, std::vector<int> &blk_rep, 
     blk_first.clear();
     for (int r = 0; r < c->n_rep; ++r) {
         const Rep &R = c->reps[r];
-        const long long nb = tile_is_stream(t) ? stream_blocks(t, R.Lx, R.Ly, R.Lz)
-                                               : (long long)((R.Lx + t.cx - 1) / t.cx) * ((R.Ly + t.cy - 1) / t.cy) *
-                                                     ((R.Lz + t.cz - 1) / t.cz);
+        const long long nb = tile_is_rows(t)     ? rows_blocks(t, R.Lx, R.Ly, R.Lz)
+                             : tile_is_stream(t) ? stream_blocks(t, R.Lx, R.Ly, R.Lz)
+                                                 : (long long)((R.Lx + t.cx - 1) / t.cx) * ((R.Ly + t.cy - 1) / t.cy) *
+                                                       ((R.Lz + t.cz - 1) / t.cz);
         blk_first.push_back((int)blk_rep.size());
         for (long long b = 0; b < nb; ++b) blk_rep.push_back(r);
     }
@@ -361,22 +366,84 @@ bool tile_known(const TileCfg &t)
     HSF_STREAM_CONFIGS(HSF_EQS)
 #undef HSF_EQS
 #undef HSF_EQ
+#define HSF_EQ(CX, CY, CZ, K) \
+    if (t.cx == CX && t.cy == CY && t.cz == CZ && t.k == -K) return true;
+    HSF_ROWS_CONFIGS(HSF_EQ)
+#undef HSF_EQ
     return false;
 }
 
-// Make t the configuration in use (device tile plan rebuilt; captured graphs dropped).
+// Whether this context can use t: row tilings of 128 sites need rows of exactly that
+// length, and the largest register bundles exist in FP32 only.
+bool tile_fits(const hsf_ctx *c, const TileCfg &t, size_t rs)
+{
+    if (tile_lds_bytes(t, rs) > c->lds_limit) return false;
+    if (!tile_is_rows(t)) return true;
+    if (c->precision == HSF_FP64 && !rows_fp64(t)) return false;
+    for (const Rep &R : c->reps)   // row sweeps address a propagator by 31-bit byte offsets
+        if (R.V > 0x7fffffffLL / (long long)sizeof(double)) return false;
+    if (t.cx == 128)
+        for (const Rep &R : c->reps)
+            if (R.Lx != 128) return false;
+    return true;
+}
+
+// The row tiling of the evaluations at hand: the refinement phase of an FP32 context takes
+// the FP64 bundle nearest to its own.
+TileCfg rows_tile(const hsf_ctx *c, bool fp64)
+{
+    const TileCfg t = c->tile;
+    if (!fp64 || rows_fp64(t)) return t;
+    if (t.cx == 128) return TileCfg{128, 8, 4, -2};
+    return t.k == -4 ? TileCfg{64, 4, 4, -4} : TileCfg{64, 8, 4, t.k};
+}
+
+// The plan whose blocks write the forward sweep's partial sums (partG).
+const Plan &sweep_plan(const hsf_ctx *c)
+{
+    if (!tile_is_rows(c->tile) || c->ch.N < 2) return c->tplan;
+    return c->eval64 ? c->rplan64 : c->rplan;
+}
+
+// Tiling of the launch that sums the terms and normalises, after row sweeps: columns of 4
+// planes per thread where the box fills the chip with those, of 2 planes below.
+TileCfg density_tile(const hsf_ctx *c, const TileCfg &t)
+{
+    if (!tile_is_rows(t)) return t;
+    return c->T >= (1LL << 20) ? TileCfg{32, 8, 4, -1} : TileCfg{32, 8, 2, -1};
+}
+
+int put_plan(hsf_ctx *c, Plan &p, const std::vector<int> &br, const std::vector<int> &bf)
+{
+    if ((int)br.size() > c->max_tile_blocks) return fail(c, HSF_EINVAL, "tile plan larger than sized for");
+    HIPCHK(c, hipMemcpy(p.blk_rep, br.data(), sizeof(int) * br.size(), hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemcpy(p.blk_first, bf.data(), sizeof(int) * bf.size(), hipMemcpyHostToDevice));
+    p.nblocks = (int)br.size();
+    p.n_rep = c->n_rep;
+    set_plan_args(p, c->reps.data(), c->n_rep, bf.data());
+    return HSF_OK;
+}
+
+// Make t the configuration in use (device tile plans rebuilt; captured graphs dropped).
 int set_tile(hsf_ctx *c, const TileCfg &t)
 {
     std::vector<int> br, bf;
-    tile_blocks(c, t, br, bf);
-    if ((int)br.size() > c->max_tile_blocks) return fail(c, HSF_EINVAL, "tile plan larger than sized for");
-    HIPCHK(c, hipMemcpy(c->tplan.blk_rep, br.data(), sizeof(int) * br.size(), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(c->tplan.blk_first, bf.data(), sizeof(int) * bf.size(), hipMemcpyHostToDevice));
-    c->tplan.nblocks = (int)br.size();
-    c->tplan.n_rep = c->n_rep;
-    c->tile_blk_first = bf;
-    set_plan_args(c->tplan, c->reps.data(), c->n_rep, bf.data());
+    const TileCfg dt = density_tile(c, t);
+    tile_blocks(c, dt, br, bf);
+    if (int rc = put_plan(c, c->tplan, br, bf)) return rc;
+    if (tile_is_rows(t)) {
+        tile_blocks(c, t, br, bf);
+        if (int rc = put_plan(c, c->rplan, br, bf)) return rc;
+    }
+    c->sweep_most = 0;
+    for (int r = 0; r < c->n_rep; ++r) c->sweep_most = std::max(c->sweep_most, bf[r + 1] - bf[r]);
     c->tile = t;
+    c->dtile = dt;
+    if (tile_is_rows(t) && c->precision == HSF_FP32) {
+        tile_blocks(c, rows_tile(c, true), br, bf);
+        if (int rc = put_plan(c, c->rplan64, br, bf)) return rc;
+        for (int r = 0; r < c->n_rep; ++r) c->sweep_most = std::max(c->sweep_most, bf[r + 1] - bf[r]);
+    }
     c->drop_graphs();
     return HSF_OK;
 }
@@ -440,16 +507,14 @@ void run_eval_paired(hsf_ctx *c, int use_alpha, int final_mode, double *out, con
         launch_pair_block<real>(c->tile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, ps, b, Gf[(j - 1) & 1],
                                 Gf[j & 1], gin, gout, c->partG, sums, c->w, c->d, use_alpha, t.a, t.b);
     }
-    int most = 0;
-    for (int r = 0; r < c->n_rep; ++r) most = std::max(most, c->tile_blk_first[r + 1] - c->tile_blk_first[r]);
-    const bool fold = most <= kFoldQMaxBlocks;
+    const bool fold = c->sweep_most <= kFoldQMaxBlocks;
     if (!fold)
-        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, c->partG, 0.0, 0,
+        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, c->tplan, c->partG, 0.0, 0,
                           c->st_hd);
     Timed t(c, HSF_K_BWD);
     launch_bwd_block<real>(c->tile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, 1, 1, b, b.Gp[parity ^ 1],
-                           b.Gp[parity], c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold ? 2 : 0, t.a,
-                           t.b);
+                           b.Gp[parity], c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold ? 2 : 0,
+                           c->tplan, t.a, t.b);
 }
 
 // Streaming tilings: field factors, ceil(N/K) forward launches, the Q reduction and
@@ -468,7 +533,7 @@ void run_eval_stream(hsf_ctx *c, int use_alpha, int final_mode, double *out, con
         launch_fwd_stream<real>(c->tile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, s0, std::min(K, N - s0), b,
                                 c->partG, sums, t.a, t.b);
     }
-    launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, c->partG, 0.0, 0,
+    launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, c->tplan, c->partG, 0.0, 0,
                       c->st_hd);
     int parity = 0;
     for (int s_hi = N; s_hi >= 1; s_hi -= K) {
@@ -479,14 +544,76 @@ void run_eval_stream(hsf_ctx *c, int use_alpha, int final_mode, double *out, con
     }
 }
 
+// Row tilings (K = -tile.k >= 2 steps per launch): the N - 1 stencil steps of a sweep are
+// cut into m = ceil((N - 1) / K) nearly equal blocks of consecutive beads.  The field
+// factors come first, in a launch of their own (both halves of the first sweep launch
+// read them); then launch j takes forward block j and backward block m + 1 + (m mod 2) - j,
+// the schedule of paired_steps with blocks for beads: a block's two visits never share a
+// launch, the first visit leaves G_s or sigma[G+_{s+1}] in the slots and the second the
+// term.  G_1 and G+_N are products of a field factor and start the first block of their
+// sweep without a stencil.  Step 1 follows in the one-step density launch.
+template <typename real>
+void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums)
+{
+    PropBufs<real> b = bufs<real>(c);
+    const TileCfg tile = rows_tile(c, sizeof(real) == sizeof(double));
+    const Plan &plan = sweep_plan(c);
+    const int N = c->ch.N, K = -tile.k, m = (N - 1 + K - 1) / K, lag = m & 1, se = (m + lag) / 2;
+    const bool alt = sizeof(real) == sizeof(double) && c->precision == HSF_FP32;   // refinement phase
+    real *Gf[2] = {(real *)(alt ? c->Gf64[0] : c->Gf0), (real *)(alt ? c->Gf64[1] : c->Gf1)};
+    // first bead of block i
+    auto lo = [&](int i) { return 2 + (i - 1) * ((N - 1) / m) + std::min(i - 1, (N - 1) % m); };
+    {
+        Timed t(c, HSF_K_PREP);
+        launch_field_exp<real>(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->w, c->d, use_alpha, b.E, t.a, t.b);
+    }
+    int parity = 0;
+    for (int j = 1; j <= m + lag; ++j) {
+        const int bi = m + 1 + lag - j;   // backward block
+        const bool has_f = j <= m, has_g = bi <= m;
+        RowsHalf f{}, g{};
+        if (has_f) {
+            f.first = lo(j);
+            f.n = lo(j + 1) - lo(j);
+            f.start = j == 1;
+            f.late = j > se;
+            f.from_pp = j >= 2 && j - 1 >= se;
+            f.out = j >= se && j < m;
+        }
+        if (has_g) {
+            const int hi = lo(bi + 1) - 1;
+            g.start = hi == N;
+            g.first = hi == N ? N - 1 : hi;
+            g.n = g.first - lo(bi) + 1;
+            g.late = bi <= se;
+            g.out = 1;
+        }
+        const real *gin = b.Gp[parity ^ 1];
+        real *gout = b.Gp[parity];
+        if (has_g) parity ^= 1;
+        Timed t(c, HSF_K_PAIR);
+        launch_rows<real>(tile, c->stream, plan, c->rep_d, c->st_d, c->ch, f, g, has_f, has_g, b,
+                          Gf[(j - 1) & 1], Gf[j & 1], gin, gout, c->partG, sums, t.a, t.b);
+    }
+    const bool fold = c->sweep_most <= kFoldQMaxBlocks;
+    if (!fold)
+        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, plan, c->partG,
+                          0.0, 0, c->st_hd);
+    Timed t(c, HSF_K_BWD);
+    launch_bwd_block<real>(c->dtile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, 1, 1, b, b.Gp[parity ^ 1],
+                           b.Gp[parity], c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold ? 2 : 0,
+                           plan, t.a, t.b);
+}
+
 template <typename real>
 void run_eval(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums)
 {
     if (tile_is_stream(c->tile)) return run_eval_stream<real>(c, use_alpha, final_mode, out, d, sums);
+    if (tile_is_rows(c->tile) && c->ch.N >= 2) return run_eval_rows<real>(c, use_alpha, final_mode, out, d, sums);
     if (c->tile.k < 0 && c->ch.N >= 2) return run_eval_paired<real>(c, use_alpha, final_mode, out, d, sums);
     PropBufs<real> b = bufs<real>(c);
-    const int N = c->ch.N, K = std::max(1, c->tile.k);
-    const bool direct = c->tile.k <= 0;
+    const int N = c->ch.N, K = std::max(1, c->dtile.k);
+    const bool direct = c->dtile.k <= 0;
     const bool fold_q = direct && N > 1;   // with N = 1 step 1 is step N: Q first, in its own launch
     if (!direct) {
         Timed t(c, HSF_K_PREP);
@@ -494,20 +621,20 @@ void run_eval(hsf_ctx *c, int use_alpha, int final_mode, double *out, const doub
     }
     for (int s0 = 0; s0 < N; s0 += K) {
         Timed t(c, HSF_K_FWD);
-        launch_fwd_block<real>(c->tile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, s0, std::min(K, N - s0), b,
+        launch_fwd_block<real>(c->dtile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, s0, std::min(K, N - s0), b,
                                c->partG, sums, direct ? c->w : nullptr, c->d, use_alpha, t.a, t.b);
     }
     if (!fold_q)
-        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, c->partG, 0.0, 0,
+        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_Q, c->ch, c->tplan, c->partG, 0.0, 0,
                           c->st_hd);
     int parity = 0;
     for (int s_hi = N; s_hi >= 1; s_hi -= K) {
         Timed t(c, HSF_K_BWD);
         const real *gin = b.Gp[parity ^ 1];
         real *gout = b.Gp[parity];
-        launch_bwd_block<real>(c->tile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, s_hi, std::min(K, s_hi), b,
+        launch_bwd_block<real>(c->dtile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, s_hi, std::min(K, s_hi), b,
                                gin, gout, c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold_q ? 1 : 0,
-                               t.a, t.b);
+                               c->tplan, t.a, t.b);
         parity ^= 1;
     }
 }
@@ -524,7 +651,7 @@ void run_eval_any(hsf_ctx *c, int use_alpha, int final_mode, double *out, const 
 void target_setup(hsf_ctx *c, double tol, int max_iter)
 {
     launch_target_stats(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->phi, c->w, c->part);
-    launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_TARGET, c->ch, c->partG, tol,
+    launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_TARGET, c->ch, c->plan, c->partG, tol,
                       max_iter, c->st_hd);
 }
 
@@ -657,11 +784,11 @@ int invert_once(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats
     // starting point: evaluation, residual, first direction, first alpha
     int rc = run_seq(c, hsf_ctx::GK_START, [&] {
         run_eval_any(c, 0, 1, c->g, nullptr, 1);
-        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_EVAL0, c->ch, c->partG,
+        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_EVAL0, c->ch, sweep_plan(c), c->partG,
                           0.0, 0, c->st_hd);
         launch_cg_update(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 1, c->w, c->g, c->gt, c->d, c->phi,
                          c->part);
-        launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch, c->partG,
+        launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch, c->plan, c->partG,
                           0.0, 0, c->st_hd);
     });
     if (rc) return rc;
@@ -688,11 +815,11 @@ int invert_once(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats
             rc = run_seq(c, hsf_ctx::GK_PASS, [&] {
                 run_eval_any(c, 1, 1, c->gt, c->d, 0);
                 launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_TRIAL, c->ch,
-                                  c->partG, 0.0, 0, c->st_hd);
+                                  sweep_plan(c), c->partG, 0.0, 0, c->st_hd);
                 launch_cg_update(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 0, c->w, c->g, c->gt, c->d, c->phi,
                                  c->part);
                 launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch,
-                                  c->partG, 0.0, 0, c->st_hd);
+                                  c->plan, c->partG, 0.0, 0, c->st_hd);
             });
             if (rc) return rc;
         }
@@ -772,7 +899,7 @@ int evaluate_impl(hsf_ctx *c, bool check_range = true)
             target_setup(c, 0.0, 0);   // phibar_p, phibar_s from the current densities; all replicas active
             run_eval_any(c, 0, 0, c->eval_out, nullptr, 1);
             launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch,
-                              c->partG, 0.0, 0, c->st_hd);
+                              sweep_plan(c), c->partG, 0.0, 0, c->st_hd);
         });
         if (rc0) return rc0;
         if (!check_range) break;
@@ -783,7 +910,7 @@ int evaluate_impl(hsf_ctx *c, bool check_range = true)
     }
     if (c->ch.nsp == 3) {
         launch_solvent(s, c->plan, c->rep_d, c->st_d, c->ch, 0, c->w, c->phi, c->eval_out, c->part);
-        launch_reduce_ctl(s, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_SOLVENT, c->ch, c->partG, 0.0, 0, c->st_hd);
+        launch_reduce_ctl(s, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_SOLVENT, c->ch, c->plan, c->partG, 0.0, 0, c->st_hd);
         launch_solvent(s, c->plan, c->rep_d, c->st_d, c->ch, 1, c->w, c->phi, c->eval_out, c->part);
     }
     HIPCHK(c, hipGetLastError());
@@ -1074,6 +1201,11 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
         HSF_STREAM_CONFIGS(HSF_SIZES)
 #undef HSF_SIZES
 #undef HSF_SIZE
+#define HSF_SIZE(CX, CY, CZ, K)                                             \
+    tile_blocks(c, TileCfg{CX, CY, CZ, -K}, br, bf);                        \
+    c->max_tile_blocks = std::max(c->max_tile_blocks, (int)br.size());
+        HSF_ROWS_CONFIGS(HSF_SIZE)
+#undef HSF_SIZE
     }
     {
         int dev = 0, lds = 0;
@@ -1116,6 +1248,10 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     ALLOC(c->partG, sizeof(double) * (N + 2) * max_blocks);
     ALLOC(c->tplan.blk_rep, sizeof(int) * c->max_tile_blocks);
     ALLOC(c->tplan.blk_first, sizeof(int) * (n_rep + 1));
+    for (Plan *p : {&c->rplan, &c->rplan64}) {
+        ALLOC(p->blk_rep, sizeof(int) * c->max_tile_blocks);
+        ALLOC(p->blk_first, sizeof(int) * (n_rep + 1));
+    }
     ALLOC(c->E, rs * 2 * T);
     ALLOC(c->G, rs * N * T);
     ALLOC(c->Gp0, rs * T);
@@ -1176,7 +1312,7 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
         TileCfg f{0, 0, 0, 0};
         if (sscanf(forced, "%d,%d,%d,%d", &f.cx, &f.cy, &f.cz, &f.k) == 4 && tile_known(f)) t0 = f;
     }
-    if (tile_lds_bytes(t0, real_size(c)) > c->lds_limit) t0 = TileCfg{8, 8, 8, 1};
+    if (!tile_fits(c, t0, real_size(c))) t0 = TileCfg{8, 8, 8, 1};
     if ((rc = set_tile(c, t0)) != HSF_OK) {
         hsf_destroy(c);
         return rc;
@@ -1610,7 +1746,8 @@ int hsf_set_tile(hsf_ctx *c, const int cfg[4])
     if (!c || !cfg) return HSF_EINVAL;
     TileCfg t{cfg[0], cfg[1], cfg[2], cfg[3]};
     if (!tile_known(t)) return fail(c, HSF_EINVAL, "tile %d,%d,%d,%d is not instantiated", t.cx, t.cy, t.cz, t.k);
-    if (tile_lds_bytes(t, lds_real_size(c)) > c->lds_limit) return fail(c, HSF_EINVAL, "tile exceeds the LDS limit");
+    if (!tile_fits(c, t, lds_real_size(c)))
+        return fail(c, HSF_EINVAL, "tile %d,%d,%d,%d does not fit this context", t.cx, t.cy, t.cz, t.k);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return set_tile(c, t);
 }
@@ -1637,15 +1774,25 @@ int hsf_autotune(hsf_ctx *c, int reps, double *best_ms)
     TileCfg best = c->tile;
     float best_t = 1e30f;
     int rc = HSF_OK;
+    // Candidates: the one-step and paired tilings, and the row tilings where more than half
+    // of the sites lie in rows that fill more than half of a wavefront (at 32 sites per row
+    // they gain under 10 %).  The LDS-blocked and z-streaming tilings were never the fastest
+    // (64^3 pair 0.15 ms and more, 192^3 1.7x and more, against 0.14 ms and 1x for the
+    // paired ones) and are not timed.
     std::vector<TileCfg> cands;
-#define HSF_CAND(CX, CY, CZ, K) cands.push_back(TileCfg{CX, CY, CZ, K});
-#define HSF_CANDS(H, CZ, K) HSF_CAND(64, H, CZ, K)
+#define HSF_CAND(CX, CY, CZ, K) \
+    if (K <= 0) cands.push_back(TileCfg{CX, CY, CZ, K});
     HSF_TILE_CONFIGS(HSF_CAND)
-    HSF_STREAM_CONFIGS(HSF_CANDS)
-#undef HSF_CANDS
 #undef HSF_CAND
+    long long wide = 0;
+    for (const Rep &R : c->reps) wide += R.Lx > 32 ? R.V : 0;
+    if (2 * wide > c->T) {
+#define HSF_CAND(CX, CY, CZ, K) cands.push_back(TileCfg{CX, CY, CZ, -K});
+        HSF_ROWS_CONFIGS(HSF_CAND)
+#undef HSF_CAND
+    }
     for (const TileCfg &t : cands) {
-        if (tile_lds_bytes(t, lds_real_size(c)) > c->lds_limit) continue;
+        if (!tile_fits(c, t, lds_real_size(c))) continue;
         if ((rc = set_tile(c, t)) != HSF_OK) break;
         // `reps` evaluations (exp, sweeps, Q, normalisation; state untouched), captured in a
         // graph and replayed as the inversion replays them
@@ -1700,7 +1847,7 @@ int hsf_set_solver(hsf_ctx *c, int flags)
     const int pc = (flags & HSF_SOLVER_PRECOND) ? 1 : 0;
     const int rf = (flags & HSF_SOLVER_REFINE) && c->precision == HSF_FP32 ? 1 : 0;
     if (rf && !c->refine) {
-        if (tile_lds_bytes(c->tile, sizeof(double)) > c->lds_limit)
+        if (!tile_fits(c, c->tile, sizeof(double)))
             return fail(c, HSF_EINVAL, "the tiling in use does not fit the LDS in FP64");
         // the FP64 propagators of the refinement phase, made once (each buffer only if a
         // call before ran out of memory before reaching it)
@@ -1841,7 +1988,8 @@ int hsf_set_state(hsf_ctx *c, const void *buf, long long size)
     int rc = sync(c);
     if (rc) return rc;
     const TileCfg t{h.tile[0], h.tile[1], h.tile[2], h.tile[3]};
-    if (!tile_known(t)) return fail(c, HSF_EINVAL, "state names an unknown tiling");
+    if (!tile_known(t) || (tile_is_rows(t) && !tile_fits(c, t, real_size(c))))
+        return fail(c, HSF_EINVAL, "state names an unknown tiling");
     if (t.cx != c->tile.cx || t.cy != c->tile.cy || t.cz != c->tile.cz || t.k != c->tile.k)
         if ((rc = set_tile(c, t))) return rc;
     const char *p = static_cast<const char *>(buf) + sizeof h;

@@ -58,7 +58,8 @@ __device__ void control(RepState &S, int phase, const Chain &ch, const double *r
                         double V, double csum, double tol, int max_iter);
 __device__ void reduce_and_control(RepState &S, int r, const int *__restrict__ blk_first, const Rep *__restrict__ rep,
                                    const double *__restrict__ part, int phase, const Chain &ch,
-                                   const double *__restrict__ partG, int nblocks, double tol, int max_iter);
+                                   const int *__restrict__ gblk_first, const double *__restrict__ partG, int nblocks,
+                                   double tol, int max_iter);
 
 // One workgroup of kCtlBlock threads per replica: its reductions are chains of dependent
 // load batches, so more wavefronts per row shorten them.
@@ -67,6 +68,7 @@ constexpr int kCtlBlock = 1024;
 __global__ __launch_bounds__(kCtlBlock) void k_reduce_ctl(const int *__restrict__ blk_first,
                                                        RepState *__restrict__ st, const Rep *__restrict__ rep,
                                                        const double *__restrict__ part, int phase, Chain ch,
+                                                       const int *__restrict__ gblk_first,
                                                        const double *__restrict__ partG, int nblocks,
                                                        double tol, int max_iter, RepState *__restrict__ mirror)
 {
@@ -93,7 +95,7 @@ __global__ __launch_bounds__(kCtlBlock) void k_reduce_ctl(const int *__restrict_
         __syncthreads();
         if (threadIdx.x == 0) S.accepted = 0;
     }
-    if (take) reduce_and_control(S, r, blk_first, rep, part, phase, ch, partG, nblocks, tol, max_iter);
+    if (take) reduce_and_control(S, r, blk_first, rep, part, phase, ch, gblk_first, partG, nblocks, tol, max_iter);
     __syncthreads();
     {
         // the state back to device memory and into the host's pinned mirror, which the
@@ -111,9 +113,11 @@ __global__ __launch_bounds__(kCtlBlock) void k_reduce_ctl(const int *__restrict_
 // The reduction of one phase's partial sums for replica r and the scalar control step.
 __device__ void reduce_and_control(RepState &S, int r, const int *__restrict__ blk_first, const Rep *__restrict__ rep,
                                    const double *__restrict__ part, int phase, const Chain &ch,
-                                   const double *__restrict__ partG, int nblocks, double tol, int max_iter)
+                                   const int *__restrict__ gblk_first, const double *__restrict__ partG, int nblocks,
+                                   double tol, int max_iter)
 {
     const int b0 = blk_first[r], b1 = blk_first[r + 1];
+    const int gb0 = gblk_first[r], gb1 = gblk_first[r + 1];
     const double V = (double)rep[r].V;
     __shared__ double vals[kNQ + 66];
 
@@ -138,12 +142,15 @@ __device__ void reduce_and_control(RepState &S, int r, const int *__restrict__ b
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int nrows = nslots + ng;
     const int parts = nrows > 0 ? (nrows >= kWaves ? 1 : kWaves / nrows) : 1;
-    const int span = (b1 - b0 + parts - 1) / parts;
     __shared__ double psum[kWaves];
     for (int t0 = 0; t0 < nrows * parts; t0 += kWaves) {
         const int t = t0 + wid, row = t / parts, pt = t % parts;
         if (row < nrows) {
-            const int lo = b0 + pt * span, hi = lo + span < b1 ? lo + span : b1;
+            // `part` has a slot per block of the density launch, partG a column per block of
+            // the forward sweep (another plan when the sweeps have their own tiles)
+            const int f0 = row < nslots ? b0 : gb0, f1 = row < nslots ? b1 : gb1;
+            const int span = (f1 - f0 + parts - 1) / parts;
+            const int lo = f0 + pt * span, hi = lo + span < f1 ? lo + span : f1;
             double v = 0.0;
             // unrolled so that the loads of several iterations are in flight together
             if (row < nslots) {
@@ -308,11 +315,11 @@ __device__ void control(RepState &S, int phase, const Chain &ch, const double *r
 }
 
 void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, const Rep *rep,
-                       const double *part, int phase, Chain ch, const double *partG, double tol,
+                       const double *part, int phase, Chain ch, const Plan &pg, const double *partG, double tol,
                        int max_iter, RepState *mirror)
 {
     hipLaunchKernelGGL(k_reduce_ctl, dim3(n_rep), dim3(kCtlBlock), 0, s, p.blk_first, st, rep, part, phase, ch,
-                       partG, p.nblocks, tol, max_iter, mirror);
+                       pg.blk_first, partG, pg.nblocks, tol, max_iter, mirror);
 }
 
 // Partial sums of the inversion target: sum of polymer phi^t, sum of phi^t_S,

@@ -111,9 +111,10 @@ enum Phase {
     PH_SOLVENT = 6   // <exp(-w_S)>
 };
 // The control kernel also writes every replica's state into `mirror` (pinned host
-// memory, or null), which the host reads after synchronising the stream.
+// memory, or null), which the host reads after synchronising the stream.  p: the plan whose
+// blocks wrote `part`; pg: the plan whose blocks wrote the columns of partG.
 void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, const Rep *rep,
-                       const double *part, int phase, Chain ch, const double *partG, double tol,
+                       const double *part, int phase, Chain ch, const Plan &pg, const double *partG, double tol,
                        int max_iter, RepState *mirror);
 
 void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,

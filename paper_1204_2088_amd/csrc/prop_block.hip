@@ -682,7 +682,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
 // in place of a separate control launch.  With fold_q = 2 (the paired sweeps, whose
 // forward step N runs just before step 1), step 1's launch does it: every block sums the
 // partials itself in that same order, so all hold the same Q, and the replica's first
-// block stores it.
+// block stores it; q_first and nblocks are then those of the plan that wrote the partials.
 template <typename real, int CX, int CY, int CZ, bool ARGS, bool FINAL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(real) == 4 ? 8 : 1))) void k_bwd_direct(StepInfo si, const int *__restrict__ blk_rep,
                                                        const int *__restrict__ blk_first,
@@ -693,7 +693,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
                                                        int final_mode, const double *__restrict__ phit,
                                                        const double *__restrict__ d, double *__restrict__ out,
                                                        double *__restrict__ part, const double *__restrict__ partG,
-                                                       int nblocks, int fold_q, ArgReps ar)
+                                                       int nblocks, int fold_q, const int *__restrict__ q_first,
+                                                       ArgReps ar)
 {
     static_assert(CX * CY == kBlock, "one column per thread");
     int r, x0, y0, z0;
@@ -816,8 +817,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
     if (FINAL && fold_q == 2) {
         __shared__ double q_sh;
         if (threadIdx.x < 64) {
-            const int pb = plan_block();
-            const int b0 = ARGS ? ar.blk_first[r] : blk_first[r], b1 = ARGS ? ar.blk_first[r + 1] : blk_first[r + 1];
+            const int pb = plan_block(), own0 = ARGS ? ar.blk_first[r] : blk_first[r];
+            const int b0 = q_first[r], b1 = q_first[r + 1];
             double v = 0.0;
             const double *row = partG + (long long)(N - 1) * nblocks;
 #pragma unroll 8
@@ -829,7 +830,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
                 bool bad;
                 q_from_sum(v, (double)R.V, st[r].scale_e, N, q, lq, bad);
                 q_sh = q;
-                if (pb == b0) {
+                if (pb == own0) {
                     st[r].q = q;
                     st[r].ln_q = lq;
                     if (bad) st[r].nonfinite = 1;
@@ -1133,8 +1134,8 @@ struct BlockKernels {
     }
     static void bwd(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, int s_hi, int n,
                     PropBufs<real> b, const real *gin, real *gout, double *acc, int final_mode, const double *phit,
-                    const double *d, double *out, double *part, const double *partG, int fold_q, hipEvent_t e0,
-                    hipEvent_t e1)
+                    const double *d, double *out, double *part, const double *partG, int fold_q, const Plan &qp,
+                    hipEvent_t e0, hipEvent_t e1)
     {
         if constexpr (K <= 0) {   // direct kernels (K = -1: their single steps)
             auto kern = s_hi == 1 ? (p.args.n ? k_bwd_direct<real, CX, CY, CZ, true, true>
@@ -1144,11 +1145,11 @@ struct BlockKernels {
             if (e0)
                 hipExtLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, e0, e1, 0, step_info(ch, s_hi),
                                       p.blk_rep, p.blk_first, rep, st, ch, b, gin, gout, acc, final_mode, phit, d,
-                                      out, part, partG, p.nblocks, fold_q, p.args);
+                                      out, part, partG, qp.nblocks, fold_q, qp.blk_first, p.args);
             else
                 hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, step_info(ch, s_hi), p.blk_rep,
                                    p.blk_first, rep, st, ch, b, gin, gout, acc, final_mode, phit, d, out, part, partG,
-                                   p.nblocks, fold_q, p.args);
+                                   qp.nblocks, fold_q, qp.blk_first, p.args);
         } else {
             if (e0)
                 hipExtLaunchKernelGGL((k_bwd_block<real, CX, CY, CZ, K>), dim3(p.nblocks), dim3(kBlock), 0, s, e0,
@@ -1235,12 +1236,12 @@ template <typename real>
 void launch_bwd_block(const TileCfg &cfg, hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,
                       int s_hi, int n, PropBufs<real> b, const real *gin, real *gout, double *acc, int final_mode,
                       const double *phit, const double *d, double *out, double *part, const double *partG,
-                      int fold_q, hipEvent_t e0, hipEvent_t e1)
+                      int fold_q, const Plan &qp, hipEvent_t e0, hipEvent_t e1)
 {
 #define HSF_CASE(CX, CY, CZ, K)                                                                        \
     if (cfg.cx == CX && cfg.cy == CY && cfg.cz == CZ && cfg.k == K)                                    \
         return BlockKernels<real, CX, CY, CZ, K>::bwd(s, p, rep, st, ch, s_hi, n, b, gin, gout, acc,       \
-                                                      final_mode, phit, d, out, part, partG, fold_q, e0, e1);
+                                                      final_mode, phit, d, out, part, partG, fold_q, qp, e0, e1);
     HSF_TILE_CONFIGS(HSF_CASE)
 #undef HSF_CASE
 }
@@ -1255,7 +1256,8 @@ void launch_bwd_block(const TileCfg &cfg, hipStream_t s, const Plan &p, const Re
     template void launch_bwd_block<real>(const TileCfg &, hipStream_t, const Plan &, const Rep *,         \
                                          RepState *, Chain, int, int, PropBufs<real>, const real *,       \
                                          real *, double *, int, const double *, const double *, double *, \
-                                         double *, const double *, int, hipEvent_t, hipEvent_t);          \
+                                         double *, const double *, int, const Plan &, hipEvent_t,         \
+                                         hipEvent_t);                                                     \
     template void launch_pair_block<real>(const TileCfg &, hipStream_t, const Plan &, const Rep *,        \
                                           RepState *, Chain, const PairSteps &, PropBufs<real>,          \
                                           const real *, real *, const real *, real *, double *, int,     \

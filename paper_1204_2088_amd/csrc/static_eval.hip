@@ -102,19 +102,20 @@ void static_pass(hipStream_t s, const Plan &plan, const Plan &tplan, Rep *rep, R
 {
     const int N = ch.N;
     launch_target_stats(s, plan, rep, st, ch, phi, w, part);
-    launch_reduce_ctl(s, 1, plan, st, rep, part, PH_TARGET, ch, partG, 0.0, 0, nullptr);
+    launch_reduce_ctl(s, 1, plan, st, rep, part, PH_TARGET, ch, plan, partG, 0.0, 0, nullptr);
     for (int s0 = 0; s0 < N; ++s0)
         launch_fwd_block<real>(kStaticTile, s, tplan, rep, st, ch, s0, 1, b, partG, 1, w, nullptr, 0, nullptr,
                                nullptr);
     const bool fold_q = N > 1;   // with N = 1 step 1 is step N: Q first, in its own launch
-    if (!fold_q) launch_reduce_ctl(s, 1, tplan, st, rep, part, PH_Q, ch, partG, 0.0, 0, nullptr);
+    if (!fold_q) launch_reduce_ctl(s, 1, tplan, st, rep, part, PH_Q, ch, tplan, partG, 0.0, 0, nullptr);
     int parity = 0;
     for (int s_hi = N; s_hi >= 1; --s_hi) {
         launch_bwd_block<real>(kStaticTile, s, tplan, rep, st, ch, s_hi, 1, b, b.Gp[parity ^ 1], b.Gp[parity],
-                               nullptr, 0, phi, nullptr, phi_out, part, partG, fold_q ? 1 : 0, nullptr, nullptr);
+                               nullptr, 0, phi, nullptr, phi_out, part, partG, fold_q ? 1 : 0, tplan, nullptr,
+                               nullptr);
         parity ^= 1;
     }
-    launch_reduce_ctl(s, 1, tplan, st, rep, part, PH_SCALES, ch, partG, 0.0, 0, nullptr);
+    launch_reduce_ctl(s, 1, tplan, st, rep, part, PH_SCALES, ch, tplan, partG, 0.0, 0, nullptr);
 }
 
 }  // namespace
@@ -202,7 +203,7 @@ extern "C" int hsf_evaluate_static(const hsf_params *p, const double *w, const d
     }
     if (ch.nsp == 3) {
         launch_solvent(s, plan, rep, st, ch, 0, w, phi, phi_out, part);
-        launch_reduce_ctl(s, 1, plan, st, rep, part, PH_SOLVENT, ch, partG, 0.0, 0, nullptr);
+        launch_reduce_ctl(s, 1, plan, st, rep, part, PH_SOLVENT, ch, plan, partG, 0.0, 0, nullptr);
         launch_solvent(s, plan, rep, st, ch, 1, w, phi, phi_out, part);
     }
     hipLaunchKernelGGL(k_static_q, dim3(1), dim3(1), 0, s, st, q_out);
