@@ -888,30 +888,33 @@ int invert_impl(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats
 }
 
 // One evaluation of the density functional at the current fields, with phibar from the
-// current densities, into eval_out; ln Q, phibar and <exp(-w_S)> stay in the replica
-// states.  An evaluation whose propagators left the floating-point range is repeated
-// with the per-step scales it adapted (at most three more times).
-int evaluate_impl(hsf_ctx *c, bool check_range = true)
+// current densities, into eval_out (and, with `out`, copied to the caller); ln Q, phibar and
+// <exp(-w_S)> stay in the replica states.  An evaluation whose propagators left the
+// floating-point range is repeated with the per-step scales it adapted (at most three more
+// times).  The solvent's density and the copy are issued with the sweeps, before the
+// states are read, so a call waits for the stream once.
+int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, int where = HSF_DEVICE)
 {
-    hipStream_t s = c->stream;
     for (int attempt = 0; attempt < (check_range ? 4 : 1); ++attempt) {
         int rc0 = run_seq(c, hsf_ctx::GK_EVAL, [&] {
             target_setup(c, 0.0, 0);   // phibar_p, phibar_s from the current densities; all replicas active
             run_eval_any(c, 0, 0, c->eval_out, nullptr, 1);
             launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch,
                               sweep_plan(c), c->partG, 0.0, 0, c->st_hd);
+            if (c->ch.nsp == 3) {
+                launch_solvent(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 0, c->w, c->phi, c->eval_out, c->part);
+                launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_SOLVENT, c->ch, c->plan,
+                                  c->partG, 0.0, 0, c->st_hd);
+                launch_solvent(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 1, c->w, c->phi, c->eval_out, c->part);
+            }
         });
         if (rc0) return rc0;
+        if (out && (rc0 = copy_out(c, out, c->eval_out, (size_t)c->ch.nsp * c->T, where))) return rc0;
         if (!check_range) break;
         if ((rc0 = read_status(c))) return rc0;
         bool bad = false;
         for (int r = 0; r < c->n_rep; ++r) bad |= c->st_h[r].nonfinite != 0;
         if (!bad) break;
-    }
-    if (c->ch.nsp == 3) {
-        launch_solvent(s, c->plan, c->rep_d, c->st_d, c->ch, 0, c->w, c->phi, c->eval_out, c->part);
-        launch_reduce_ctl(s, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_SOLVENT, c->ch, c->plan, c->partG, 0.0, 0, c->st_hd);
-        launch_solvent(s, c->plan, c->rep_d, c->st_d, c->ch, 1, c->w, c->phi, c->eval_out, c->part);
     }
     HIPCHK(c, hipGetLastError());
     return HSF_OK;
@@ -1405,10 +1408,9 @@ int hsf_evaluate(hsf_ctx *c, double *phi_out, double *Q_out, int where)
 {
     if (!c) return HSF_EINVAL;
     if (!phi_out) return fail(c, HSF_EINVAL, "null output");
-    int rc = evaluate_impl(c);
+    if (where != HSF_DEVICE && where != HSF_HOST) return fail(c, HSF_EINVAL, "bad memory location %d", where);
+    int rc = evaluate_impl(c, true, phi_out, where);
     if (rc) return rc;
-    if ((rc = copy_out(c, phi_out, c->eval_out, (size_t)c->ch.nsp * c->T, where))) return rc;
-    if ((rc = read_status(c))) return rc;
     for (int r = 0; r < c->n_rep; ++r) {
         if (Q_out) Q_out[r] = exp(c->st_h[r].ln_q);
         if (c->st_h[r].nonfinite) return fail(c, HSF_ENONFINITE, "non-finite Q in replica %d", r);
