@@ -135,3 +135,20 @@ def test_rows_refined_inversion(hsf):
     assert np.array_equal(ctx.get_densities(), ctx2.get_densities())
     ctx.close()
     ctx2.close()
+
+
+@pytest.mark.parametrize("precision,tile", [("fp64", (128, 8, 4, -2)), ("fp32", (128, 8, 4, -2)), ("fp32", (128, 8, 8, -3))])
+def test_rows_repeat_bitwise(hsf, precision, tile):
+    """The same evaluation 60 times over gives the same bits (a store whose data registers are
+    overwritten too early shows in about one of ten evaluations of the FP64 bundle)."""
+    wl = workload((128, 10, 6), W.chain(3, 9), precision, True)
+    ctx = hsf.Context(wl)
+    ctx.set_tile(tile)
+    ctx.set_densities(W.initial_composition(wl).ravel())
+    ctx.set_fields(fields(wl, 5).ravel())
+    ctx.evaluate()
+    ref, q = ctx.evaluate()
+    for k in range(60):
+        got, qk = ctx.evaluate()
+        assert np.array_equal(got, ref) and np.array_equal(q, qk), k
+    ctx.close()
