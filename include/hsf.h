@@ -212,8 +212,8 @@ int hsf_evaluate(hsf_ctx *ctx, double *phi_out, double *Q_out, int where);
  *   q_out    device pointer to one double: Q (NaN when it left the floating-point range);
  *   hip_stream  the hipStream_t the work is ordered on (NULL: the null stream).
  * The call only enqueues work and returns; results are ready when the stream is.  FP32
- * propagators run the evaluation twice, the first pass measuring the per-step
- * power-of-two scales the second uses.  Calls that overlap on one GPU share the array
+ * propagators run the forward sweep twice, the first time measuring the per-step
+ * power-of-two scales the evaluation uses.  Calls that overlap on one GPU share the array
  * and race; the caller orders them (one stream, or waits between streams).  Returns
  * HSF_OK, HSF_EINVAL (bad parameters, null pointers, box too large) or HSF_EHIP (a
  * launch failed). */

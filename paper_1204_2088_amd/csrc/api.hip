@@ -50,6 +50,7 @@ struct hsf_ctx {
     int *bad_h = nullptr;            // pinned flag set by the LB and CD kernels on a non-finite result
     int *bad_hd = nullptr;           // its device-side address
     Plan plan;                       // site plan: kBlock consecutive sites per block
+    Plan cplan;                      // the same with span sites per block, for the kernels that reduce
     TileCfg tile{8, 8, 8, 2};        // propagator tile configuration in use
     Plan tplan;                      // tile plan of `dtile`
     TileCfg dtile{8, 8, 8, 2};       // tiling of the density launch: `tile`, or with row tilings a one-step one
@@ -448,6 +449,13 @@ int set_tile(hsf_ctx *c, const TileCfg &t)
     return HSF_OK;
 }
 
+// The fields when the evaluation writes densities of a solution: its last launch then adds
+// the solvent's (from <exp(-w_S)> of the target statistics).
+const double *solvent_fields(const hsf_ctx *c, int final_mode)
+{
+    return final_mode == 0 && c->ch.nsp == 3 ? c->w : nullptr;
+}
+
 // One density-functional evaluation for the active replicas.
 //   final_mode 0: densities into out (field layout); 1: gradient phi^t - phi into out
 //   (polymer layout) with the partial dot products against d.
@@ -514,7 +522,7 @@ void run_eval_paired(hsf_ctx *c, int use_alpha, int final_mode, double *out, con
     Timed t(c, HSF_K_BWD);
     launch_bwd_block<real>(c->tile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, 1, 1, b, b.Gp[parity ^ 1],
                            b.Gp[parity], c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold ? 2 : 0,
-                           c->tplan, t.a, t.b);
+                           c->tplan, solvent_fields(c, final_mode), t.a, t.b);
 }
 
 // Streaming tilings: field factors, ceil(N/K) forward launches, the Q reduction and
@@ -542,57 +550,33 @@ void run_eval_stream(hsf_ctx *c, int use_alpha, int final_mode, double *out, con
                                 b.Gp[parity ^ 1], b.Gp[parity], final_mode, c->phi, d, out, c->part, t.a, t.b);
         parity ^= 1;
     }
+    if (solvent_fields(c, final_mode)) launch_solvent(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->w, out);
 }
 
-// Row tilings (K = -tile.k >= 2 steps per launch): the N - 1 stencil steps of a sweep are
-// cut into m = ceil((N - 1) / K) nearly equal blocks of consecutive beads.  The field
-// factors come first, in a launch of their own (both halves of the first sweep launch
-// read them); then launch j takes forward block j and backward block m + 1 + (m mod 2) - j,
-// the schedule of paired_steps with blocks for beads: a block's two visits never share a
-// launch, the first visit leaves G_s or sigma[G+_{s+1}] in the slots and the second the
-// term.  G_1 and G+_N are products of a field factor and start the first block of their
-// sweep without a stencil.  Step 1 follows in the one-step density launch.
+// Row tilings (K = -tile.k >= 2 steps per launch): the field factors in a launch of their own
+// (both halves of the first sweep launch read them), the sweeps (rows_schedule), and step 1
+// in the one-step density launch.
 template <typename real>
 void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums)
 {
     PropBufs<real> b = bufs<real>(c);
     const TileCfg tile = rows_tile(c, sizeof(real) == sizeof(double));
     const Plan &plan = sweep_plan(c);
-    const int N = c->ch.N, K = -tile.k, m = (N - 1 + K - 1) / K, lag = m & 1, se = (m + lag) / 2;
+    const int N = c->ch.N, K = -tile.k;
     const bool alt = sizeof(real) == sizeof(double) && c->precision == HSF_FP32;   // refinement phase
     real *Gf[2] = {(real *)(alt ? c->Gf64[0] : c->Gf0), (real *)(alt ? c->Gf64[1] : c->Gf1)};
-    // first bead of block i
-    auto lo = [&](int i) { return 2 + (i - 1) * ((N - 1) / m) + std::min(i - 1, (N - 1) % m); };
     {
         Timed t(c, HSF_K_PREP);
         launch_field_exp<real>(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->w, c->d, use_alpha, b.E, t.a, t.b);
     }
     int parity = 0;
-    for (int j = 1; j <= m + lag; ++j) {
-        const int bi = m + 1 + lag - j;   // backward block
-        const bool has_f = j <= m, has_g = bi <= m;
-        RowsHalf f{}, g{};
-        if (has_f) {
-            f.first = lo(j);
-            f.n = lo(j + 1) - lo(j);
-            f.start = j == 1;
-            f.late = j > se;
-            f.from_pp = j >= 2 && j - 1 >= se;
-            f.out = j >= se && j < m;
-        }
-        if (has_g) {
-            const int hi = lo(bi + 1) - 1;
-            g.start = hi == N;
-            g.first = hi == N ? N - 1 : hi;
-            g.n = g.first - lo(bi) + 1;
-            g.late = bi <= se;
-            g.out = 1;
-        }
+    for (int j = 1; j <= rows_launches(N, K); ++j) {
+        const RowsLaunch l = rows_schedule(N, K, j);
         const real *gin = b.Gp[parity ^ 1];
         real *gout = b.Gp[parity];
-        if (has_g) parity ^= 1;
+        if (l.has_g) parity ^= 1;
         Timed t(c, HSF_K_PAIR);
-        launch_rows<real>(tile, c->stream, plan, c->rep_d, c->st_d, c->ch, f, g, has_f, has_g, b,
+        launch_rows<real>(tile, c->stream, plan, c->rep_d, c->st_d, c->ch, l, b,
                           Gf[(j - 1) & 1], Gf[j & 1], gin, gout, c->partG, sums, t.a, t.b);
     }
     const bool fold = c->sweep_most <= kFoldQMaxBlocks;
@@ -602,7 +586,7 @@ void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const
     Timed t(c, HSF_K_BWD);
     launch_bwd_block<real>(c->dtile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, 1, 1, b, b.Gp[parity ^ 1],
                            b.Gp[parity], c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold ? 2 : 0,
-                           plan, t.a, t.b);
+                           plan, solvent_fields(c, final_mode), t.a, t.b);
 }
 
 template <typename real>
@@ -634,9 +618,11 @@ void run_eval(hsf_ctx *c, int use_alpha, int final_mode, double *out, const doub
         real *gout = b.Gp[parity];
         launch_bwd_block<real>(c->dtile, c->stream, c->tplan, c->rep_d, c->st_d, c->ch, s_hi, std::min(K, s_hi), b,
                                gin, gout, c->acc, final_mode, c->phi, d, out, c->part, c->partG, fold_q ? 1 : 0,
-                               c->tplan, t.a, t.b);
+                               c->tplan, direct ? solvent_fields(c, final_mode) : nullptr, t.a, t.b);
         parity ^= 1;
     }
+    if (!direct && solvent_fields(c, final_mode))
+        launch_solvent(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->w, out);
 }
 
 // sums: also produce the per-step propagator sums that update the FP32 scales
@@ -648,11 +634,12 @@ void run_eval_any(hsf_ctx *c, int use_alpha, int final_mode, double *out, const 
         run_eval<double>(c, use_alpha, final_mode, out, d, sums);
 }
 
-void target_setup(hsf_ctx *c, double tol, int max_iter)
+// solvent: also <exp(-w_S)> (evaluations of solutions)
+void target_setup(hsf_ctx *c, double tol, int max_iter, bool solvent = false)
 {
-    launch_target_stats(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->phi, c->w, c->part);
-    launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_TARGET, c->ch, c->plan, c->partG, tol,
-                      max_iter, c->st_hd);
+    launch_target_stats(c->stream, c->cplan, c->rep_d, c->st_d, c->ch, c->phi, c->w, solvent, c->part);
+    launch_reduce_ctl(c->stream, c->n_rep, c->cplan, c->st_d, c->rep_d, c->part,
+                      solvent ? PH_TARGET_SOLVENT : PH_TARGET, c->ch, c->cplan, c->partG, tol, max_iter, c->st_hd);
 }
 
 // Starting fields of an inversion (the warm start), before the gauge is fixed.
@@ -786,9 +773,9 @@ int invert_once(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats
         run_eval_any(c, 0, 1, c->g, nullptr, 1);
         launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_EVAL0, c->ch, sweep_plan(c), c->partG,
                           0.0, 0, c->st_hd);
-        launch_cg_update(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 1, c->w, c->g, c->gt, c->d, c->phi,
+        launch_cg_update(c->stream, c->cplan, c->rep_d, c->st_d, c->ch, 1, c->w, c->g, c->gt, c->d, c->phi,
                          c->part);
-        launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch, c->plan, c->partG,
+        launch_reduce_ctl(c->stream, c->n_rep, c->cplan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch, c->cplan, c->partG,
                           0.0, 0, c->st_hd);
     });
     if (rc) return rc;
@@ -816,10 +803,10 @@ int invert_once(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats
                 run_eval_any(c, 1, 1, c->gt, c->d, 0);
                 launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_TRIAL, c->ch,
                                   sweep_plan(c), c->partG, 0.0, 0, c->st_hd);
-                launch_cg_update(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 0, c->w, c->g, c->gt, c->d, c->phi,
+                launch_cg_update(c->stream, c->cplan, c->rep_d, c->st_d, c->ch, 0, c->w, c->g, c->gt, c->d, c->phi,
                                  c->part);
-                launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch,
-                                  c->plan, c->partG, 0.0, 0, c->st_hd);
+                launch_reduce_ctl(c->stream, c->n_rep, c->cplan, c->st_d, c->rep_d, c->part, PH_BEGIN, c->ch,
+                                  c->cplan, c->partG, 0.0, 0, c->st_hd);
             });
             if (rc) return rc;
         }
@@ -897,16 +884,11 @@ int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, in
 {
     for (int attempt = 0; attempt < (check_range ? 4 : 1); ++attempt) {
         int rc0 = run_seq(c, hsf_ctx::GK_EVAL, [&] {
-            target_setup(c, 0.0, 0);   // phibar_p, phibar_s from the current densities; all replicas active
+            // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
+            target_setup(c, 0.0, 0, c->ch.nsp == 3);
             run_eval_any(c, 0, 0, c->eval_out, nullptr, 1);
             launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch,
                               sweep_plan(c), c->partG, 0.0, 0, c->st_hd);
-            if (c->ch.nsp == 3) {
-                launch_solvent(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 0, c->w, c->phi, c->eval_out, c->part);
-                launch_reduce_ctl(c->stream, c->n_rep, c->plan, c->st_d, c->rep_d, c->part, PH_SOLVENT, c->ch, c->plan,
-                                  c->partG, 0.0, 0, c->st_hd);
-                launch_solvent(c->stream, c->plan, c->rep_d, c->st_d, c->ch, 1, c->w, c->phi, c->eval_out, c->part);
-            }
         });
         if (rc0) return rc0;
         if (out && (rc0 = copy_out(c, out, c->eval_out, (size_t)c->ch.nsp * c->T, where))) return rc0;
@@ -1191,6 +1173,17 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     c->plan.nblocks = (int)blk_rep.size();
     c->plan.n_rep = n_rep;
     set_plan_args(c->plan, c->reps.data(), n_rep, blk_first.data());
+    // sites per block of the reducing site kernels: 256 to 2048, at least 1024 blocks where
+    // the sites allow
+    std::vector<int> cblk_rep, cblk_first;
+    while (c->cplan.span < 8 * kBlock && c->T / (2 * c->cplan.span) >= 1024) c->cplan.span *= 2;
+    for (int r = 0; r < n_rep; ++r) {
+        cblk_first.push_back((int)cblk_rep.size());
+        cblk_rep.insert(cblk_rep.end(), (size_t)((c->reps[r].V + c->cplan.span - 1) / c->cplan.span), r);
+    }
+    cblk_first.push_back((int)cblk_rep.size());
+    c->cplan.nblocks = (int)cblk_rep.size();
+    c->cplan.n_rep = n_rep;
     c->lb_all = c->reps[0].lb_mode;
     for (const Rep &R : c->reps)
         if (R.lb_mode != c->lb_all) c->lb_all = -1;
@@ -1229,6 +1222,8 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     ALLOC(c->st_save, sizeof(RepState) * n_rep);
     ALLOC(c->plan.blk_rep, sizeof(int) * blk_rep.size());
     ALLOC(c->plan.blk_first, sizeof(int) * blk_first.size());
+    ALLOC(c->cplan.blk_rep, sizeof(int) * cblk_rep.size());
+    ALLOC(c->cplan.blk_first, sizeof(int) * cblk_first.size());
     ALLOC(c->w, sizeof(double) * nsp * T);
     ALLOC(c->w_start, sizeof(double) * nsp * T);
     ALLOC(c->phi, sizeof(double) * nsp * T);
@@ -1294,6 +1289,10 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
         e = hipMemcpy(c->plan.blk_rep, blk_rep.data(), sizeof(int) * blk_rep.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(c->plan.blk_first, blk_first.data(), sizeof(int) * blk_first.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(c->cplan.blk_rep, cblk_rep.data(), sizeof(int) * cblk_rep.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(c->cplan.blk_first, cblk_first.data(), sizeof(int) * cblk_first.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->w, 0, sizeof(double) * nsp * T);
     if (e == hipSuccess) e = hipMemset(c->phi, 0, sizeof(double) * nsp * T);
     if (e == hipSuccess) e = hipMemset(c->d, 0, sizeof(double) * 2 * T);
@@ -1798,7 +1797,7 @@ int hsf_autotune(hsf_ctx *c, int reps, double *best_ms)
         if ((rc = set_tile(c, t)) != HSF_OK) break;
         // `reps` evaluations (exp, sweeps, Q, normalisation; state untouched), captured in a
         // graph and replayed as the inversion replays them
-        target_setup(c, 0.0, 0);
+        target_setup(c, 0.0, 0, c->ch.nsp == 3);
         run_eval_any(c, 0, 0, c->eval_out, nullptr, 0);
         hipStream_t user = c->stream;
         if (!user && !c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));

@@ -125,12 +125,12 @@ __device__ void reduce_and_control(RepState &S, int r, const int *__restrict__ b
     int nslots = 0, g_first = 0, ng = 0;
     switch (phase) {
     case PH_TARGET: nslots = 6; break;
+    case PH_TARGET_SOLVENT: nslots = 7; break;
     case PH_EVAL0: nslots = 4; ng = ch.N + 2; break;
     case PH_TRIAL: nslots = 4; break;
     case PH_SCALES: ng = ch.N + 2; break;
     case PH_Q: g_first = ch.N - 1; ng = 1; break;
     case PH_BEGIN: nslots = 2; break;
-    case PH_SOLVENT: nslots = 1; break;
     default: break;
     }
     // Each row is split into contiguous parts of the replica's blocks, one wavefront per
@@ -194,6 +194,7 @@ __device__ void control(RepState &S, int phase, const Chain &ch, const double *r
         if (bad) S.nonfinite = 1;
         break;
     }
+    case PH_TARGET_SOLVENT: S.sol_mean = red[6] / V; [[fallthrough]];
     case PH_TARGET: {
         S.phibar_p = red[0] / V;
         S.phibar_s = red[1] / V;
@@ -218,7 +219,6 @@ __device__ void control(RepState &S, int phase, const Chain &ch, const double *r
         break;
     }
     case PH_SCALES: update_scales(S, ch, gsum, V, csum); break;
-    case PH_SOLVENT: S.sol_mean = red[0] / V; break;
     case PH_EVAL0: {
         update_scales(S, ch, gsum, V, csum);
         S.evals += 1;
@@ -323,37 +323,48 @@ void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, co
 }
 
 // Partial sums of the inversion target: sum of polymer phi^t, sum of phi^t_S,
-// |phi^t_A|^2, |phi^t_B|^2, sum of w_A and of w_B.
+// |phi^t_A|^2, |phi^t_B|^2, sum of w_A and of w_B, and (SOLVENT) of exp(-w_S).  One read of
+// the arrays; a block takes p.span sites, so that its reduction of seven sums and the
+// control kernel's pass over the blocks are paid once per span (128^3: 30.5 us for 8192
+// blocks of 256 sites and 11 us in the control kernel).
+template <bool SOLVENT>
 __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__ blk_rep,
                                                          const int *__restrict__ blk_first,
-                                                         const Rep *__restrict__ rep, Chain ch,
+                                                         const Rep *__restrict__ rep, int nsp, int span,
                                                          const double *__restrict__ phit,
                                                          const double *__restrict__ w, double *__restrict__ part)
 {
-    const SiteRef sr = site_ref(blk_rep, blk_first);
+    const SiteRef sr = span_ref(blk_rep, blk_first, span);
     const Rep &R = rep[sr.r];
-    const long long V = R.V, i = sr.i;
-    double v[6] = {0, 0, 0, 0, 0, 0};
-    if (i < V) {
-        const long long fo = off_field(R, ch.nsp);
+    const long long V = R.V;
+    const long long fo = off_field(R, nsp);
+    constexpr int NV = SOLVENT ? 7 : 6;
+    double v[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = 0.0;
+#pragma unroll 4
+    for (int u = 0; u < span; u += kBlock) {
+        const long long i = sr.i + u;
+        if (i >= V) break;
         const double a = phit[fo + i], bb = phit[fo + V + i];
-        v[0] = a + bb;
-        v[1] = ch.nsp == 3 ? phit[fo + 2 * V + i] : 0.0;
-        v[2] = a * a;
-        v[3] = bb * bb;
-        v[4] = w[fo + i];
-        v[5] = w[fo + V + i];
+        v[0] += a + bb;
+        if (nsp == 3) v[1] += phit[fo + 2 * V + i];
+        v[2] += a * a;
+        v[3] += bb * bb;
+        v[4] += w[fo + i];
+        v[5] += w[fo + V + i];
+        if (SOLVENT) v[NV - 1] += exp(-w[fo + 2 * V + i]);
     }
     block_sums(v);
     if (threadIdx.x == 0)
-        for (int q = 0; q < 6; ++q) part[(long long)plan_block() * kNQ + q] = v[q];
+        for (int q = 0; q < NV; ++q) part[(long long)plan_block() * kNQ + q] = v[q];
 }
 
 void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, RepState *, Chain ch,
-                         const double *phit, const double *w, double *part)
+                         const double *phit, const double *w, bool solvent, double *part)
 {
-    hipLaunchKernelGGL(k_target_stats, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, ch,
-                       phit, w, part);
+    hipLaunchKernelGGL(solvent ? k_target_stats<true> : k_target_stats<false>, dim3(p.nblocks), dim3(kBlock), 0, s,
+                       p.blk_rep, p.blk_first, rep, ch.nsp, p.span, phit, w, part);
 }
 
 // Local ideal-gas starting guess w_I = -ln phi_I (the constant -ln <phi_I> is removed
@@ -414,42 +425,40 @@ void launch_init_fields(hipStream_t s, const Plan &p, const Rep *rep, RepState *
 __global__ __launch_bounds__(kBlock) void k_cg_update(const int *__restrict__ blk_rep,
                                                       const int *__restrict__ blk_first,
                                                       const Rep *__restrict__ rep, const RepState *__restrict__ st,
-                                                      Chain ch, int init, double *__restrict__ w,
-                                                      const double *__restrict__ g, const double *__restrict__ gt,
-                                                      double *__restrict__ d, const double *__restrict__ phit,
-                                                      double *__restrict__ part)
+                                                      int nsp, int precond, int span, int init,
+                                                      double *__restrict__ w, const double *__restrict__ g,
+                                                      const double *__restrict__ gt, double *__restrict__ d,
+                                                      const double *__restrict__ phit, double *__restrict__ part)
 {
-    const SiteRef sr = site_ref(blk_rep, blk_first);
+    const SiteRef sr = span_ref(blk_rep, blk_first, span);
     const RepState &S = st[sr.r];
     if (init ? !S.pending : !S.accepted) return;
     const Rep &R = rep[sr.r];
-    const long long V = R.V, i = sr.i;
-    double dg = 0.0, dhd = 0.0;
-    if (i < V) {
-        const long long fo = off_field(R, ch.nsp), po = off_poly(R);
-        const double alpha = S.alpha, beta = S.beta;
-        const bool upd_d = init || !S.done;
+    const long long V = R.V;
+    const long long fo = off_field(R, nsp), po = off_poly(R);
+    const double alpha = S.alpha, beta = S.beta;
+    const bool upd_d = init || !S.done;
+    const double *gs = init ? g : gt;
+    double t[2] = {0.0, 0.0};
+#pragma unroll 2
+    for (int u = 0; u < span; u += kBlock) {
+        const long long i = sr.i + u;
+        if (i >= V) break;
 #pragma unroll
         for (int I = 0; I < 2; ++I) {
-            const long long k = po + I * V + i;
-            double gI;
+            const long long k = po + I * V + i, kf = fo + I * V + i;
             double dI = d[k];
-            if (init) {
-                gI = g[k];
-            } else {
-                w[fo + I * V + i] = fma(alpha, dI, w[fo + I * V + i]);
-                gI = gt[k];
-            }
+            const double gI = gs[k], pI = phit[kf];
+            if (!init) w[kf] = fma(alpha, dI, w[kf]);
             if (upd_d) {
-                const double zI = ch.precond ? gI / phit[fo + I * V + i] : gI;
+                const double zI = precond ? gI / pI : gI;
                 dI = init ? -zI : fma(beta, dI, -zI);
                 d[k] = dI;
             }
-            dg += dI * gI;
-            dhd += dI * dI * phit[fo + I * V + i];
+            t[0] += dI * gI;
+            t[1] += dI * dI * pI;
         }
     }
-    double t[2] = {dg, dhd};
     block_sums(t);
     if (threadIdx.x == 0) {
         part[(long long)plan_block() * kNQ + 0] = t[0];
@@ -460,41 +469,31 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(const int *__restrict__ bl
 void launch_cg_update(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, int init,
                       double *w, double *g, const double *gt, double *d, const double *phit, double *part)
 {
-    hipLaunchKernelGGL(k_cg_update, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, st, ch,
-                       init, w, g, gt, d, phit, part);
+    hipLaunchKernelGGL(k_cg_update, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, st, ch.nsp,
+                       ch.precond, p.span, init, w, g, gt, d, phit, part);
 }
 
-// Solvent density of eq. 2: pass 0 sums exp(-w_S); pass 1 writes
-// phi_S = phibar_s exp(-w_S) / <exp(-w_S)> into the field-layout output.
+// Solvent density of eq. 2, phi_S = phibar_s exp(-w_S) / <exp(-w_S)>, into the field-layout
+// output (after the sweeps whose density launch does not write it itself).
 __global__ __launch_bounds__(kBlock) void k_solvent(const int *__restrict__ blk_rep,
                                                     const int *__restrict__ blk_first,
                                                     const Rep *__restrict__ rep, const RepState *__restrict__ st,
-                                                    Chain ch, int pass, const double *__restrict__ w,
-                                                    double *__restrict__ out, double *__restrict__ part)
+                                                    int nsp, const double *__restrict__ w, double *__restrict__ out)
 {
     const SiteRef sr = site_ref(blk_rep, blk_first);
     const Rep &R = rep[sr.r];
     const long long V = R.V, i = sr.i;
-    const long long fo = off_field(R, ch.nsp);
-    if (pass == 0) {
-        const double v = i < V ? exp(-w[fo + 2 * V + i]) : 0.0;
-        const double t = block_sum(v);
-        if (threadIdx.x == 0) part[(long long)plan_block() * kNQ] = t;
-    } else if (i < V) {
-        const RepState &S = st[sr.r];
-        out[fo + 2 * V + i] = S.phibar_s * exp(-w[fo + 2 * V + i]) / S.sol_mean;
-    }
+    if (i >= V) return;
+    const long long k = off_field(R, nsp) + 2 * V + i;
+    const RepState &S = st[sr.r];
+    out[k] = S.phibar_s * exp(-w[k]) / S.sol_mean;
 }
 
-void launch_solvent(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, int pass,
-                    const double *w, const double *, double *out, double *part)
+void launch_solvent(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, const double *w,
+                    double *out)
 {
-    hipLaunchKernelGGL(k_solvent, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, st, ch,
-                       pass, w, out, part);
+    hipLaunchKernelGGL(k_solvent, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, st, ch.nsp, w,
+                       out);
 }
-
-}  // namespace hsf
-
-namespace hsf {
 
 }  // namespace hsf

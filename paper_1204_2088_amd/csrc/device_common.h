@@ -71,6 +71,17 @@ __device__ __forceinline__ SiteRef site_ref(const int *blk_rep, const int *blk_f
     return s;
 }
 
+// The first of the block's sites in a plan of `span` sites per block (span / kBlock rounds of
+// one site per thread).
+__device__ __forceinline__ SiteRef span_ref(const int *blk_rep, const int *blk_first, int span)
+{
+    SiteRef s;
+    const int pb = plan_block();
+    s.r = blk_rep[pb];
+    s.i = (long long)(pb - blk_first[s.r]) * span + threadIdx.x;
+    return s;
+}
+
 // Deterministic block sum (fixed shuffle tree inside each 64-lane wavefront, then
 // the four wavefront sums in order).  Every thread must call it; the result is
 // valid in thread 0.

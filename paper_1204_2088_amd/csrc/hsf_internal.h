@@ -59,9 +59,11 @@ struct ArgReps {
     Rep rep[kArgReps];
 };
 
-// Launch plan of a site kernel: each block covers kBlock consecutive sites of one replica.
+// Launch plan of a site kernel: each block covers span (kBlock, or a multiple of it in the
+// kernels that loop) consecutive sites of one replica.
 struct Plan {
     int nblocks = 0;
+    int span = kBlock;
     int *blk_rep = nullptr;      // device: replica of each block
     int *blk_first = nullptr;    // device: first block of each replica, n_rep + 1 entries
     int n_rep = 0;
@@ -108,7 +110,7 @@ enum Phase {
     PH_BEGIN = 3,    // start of an iteration: alpha_0 from d.g and d H d
     PH_TRIAL = 4,    // a trial point of the line search
     PH_SCALES = 5,   // update of the per-step scales from the G_s means
-    PH_SOLVENT = 6   // <exp(-w_S)>
+    PH_TARGET_SOLVENT = 6   // PH_TARGET, and <exp(-w_S)>
 };
 // The control kernel also writes every replica's state into `mirror` (pinned host
 // memory, or null), which the host reads after synchronising the stream.  p: the plan whose
@@ -117,8 +119,9 @@ void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, co
                        const double *part, int phase, Chain ch, const Plan &pg, const double *partG, double tol,
                        int max_iter, RepState *mirror);
 
+// solvent: also the sum of exp(-w_S) (for PH_TARGET_SOLVENT)
 void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,
-                         const double *phit, const double *w, double *part);
+                         const double *phit, const double *w, bool solvent, double *part);
 void launch_local_guess(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phit,
                         double *w, double *part);
 void launch_init_fields(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,
@@ -126,8 +129,9 @@ void launch_init_fields(hipStream_t s, const Plan &p, const Rep *rep, RepState *
 void launch_cg_update(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, int init,
                       double *w, double *g, const double *gt, double *d, const double *phit,
                       double *part);
-void launch_solvent(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, int pass,
-                    const double *w, const double *phi, double *out, double *part);
+// phi_S of eq. 2 into the field-layout out
+void launch_solvent(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, const double *w,
+                    double *out);
 
 // dynamics
 void launch_mu(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi,

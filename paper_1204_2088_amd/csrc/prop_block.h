@@ -83,11 +83,13 @@ void launch_fwd_block(const TileCfg &cfg, hipStream_t s, const Plan &p, const Re
 // fold_q: with one-step kernels the first backward launch (1), or with paired kernels the
 // last one (2), also computes Q from the forward sweep's partials, in place of the control
 // launch of that phase; qp: the plan whose blocks wrote those partials.
+// wsol (one-step and paired kernels, densities asked for): the fields, from which step 1's
+// launch also writes the solvent's density (null: not).
 template <typename real>
 void launch_bwd_block(const TileCfg &cfg, hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,
                       int s_hi, int n, PropBufs<real> b, const real *gin, real *gout, double *acc, int final_mode,
                       const double *phit, const double *d, double *out, double *part, const double *partG,
-                      int fold_q, const Plan &qp, hipEvent_t e0, hipEvent_t e1);
+                      int fold_q, const Plan &qp, const double *wsol, hipEvent_t e0, hipEvent_t e1);
 
 // Streaming sweeps: forward steps s0 + 1 .. s0 + n, and backward steps s_hi .. s_hi - n + 1
 // with the density sums of the earlier backward launches in the store (see prop_stream.hip).

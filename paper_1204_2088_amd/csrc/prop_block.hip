@@ -694,7 +694,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
                                                        const double *__restrict__ d, double *__restrict__ out,
                                                        double *__restrict__ part, const double *__restrict__ partG,
                                                        int nblocks, int fold_q, const int *__restrict__ q_first,
-                                                       ArgReps ar)
+                                                       const double *__restrict__ wsol, ArgReps ar)
 {
     static_assert(CX * CY == kBlock, "one column per thread");
     int r, x0, y0, z0;
@@ -857,12 +857,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
     }
     if (in && FINAL) {
         const double coef = st[r].phibar_p / ((double)N * (fold_q == 2 ? q_own : st[r].q));
+        const double ps = st[r].phibar_s, sm = st[r].sol_mean;
 #pragma unroll
         for (int j = 0; j < CZ; ++j) {
             if (j >= nz) break;
             const int site = x + R.Lx * (y + R.Ly * (z0 + j));
             double a[2] = {a0[j], a1[j]};
             a[ts] += (double)g1[j] * (double)S[j];
+            if (wsol) {   // the solvent's density (evaluations of solutions)
+                const long long k = fo + 2LL * V + site;
+                out[k] = ps * exp(-wsol[k]) / sm;
+            }
 #pragma unroll
             for (int I = 0; I < 2; ++I) {
                 const double ph = coef * a[I];
@@ -1135,7 +1140,7 @@ struct BlockKernels {
     static void bwd(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch, int s_hi, int n,
                     PropBufs<real> b, const real *gin, real *gout, double *acc, int final_mode, const double *phit,
                     const double *d, double *out, double *part, const double *partG, int fold_q, const Plan &qp,
-                    hipEvent_t e0, hipEvent_t e1)
+                    const double *wsol, hipEvent_t e0, hipEvent_t e1)
     {
         if constexpr (K <= 0) {   // direct kernels (K = -1: their single steps)
             auto kern = s_hi == 1 ? (p.args.n ? k_bwd_direct<real, CX, CY, CZ, true, true>
@@ -1145,11 +1150,11 @@ struct BlockKernels {
             if (e0)
                 hipExtLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, e0, e1, 0, step_info(ch, s_hi),
                                       p.blk_rep, p.blk_first, rep, st, ch, b, gin, gout, acc, final_mode, phit, d,
-                                      out, part, partG, qp.nblocks, fold_q, qp.blk_first, p.args);
+                                      out, part, partG, qp.nblocks, fold_q, qp.blk_first, wsol, p.args);
             else
                 hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, step_info(ch, s_hi), p.blk_rep,
                                    p.blk_first, rep, st, ch, b, gin, gout, acc, final_mode, phit, d, out, part, partG,
-                                   qp.nblocks, fold_q, qp.blk_first, p.args);
+                                   qp.nblocks, fold_q, qp.blk_first, wsol, p.args);
         } else {
             if (e0)
                 hipExtLaunchKernelGGL((k_bwd_block<real, CX, CY, CZ, K>), dim3(p.nblocks), dim3(kBlock), 0, s, e0,
@@ -1236,12 +1241,12 @@ template <typename real>
 void launch_bwd_block(const TileCfg &cfg, hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,
                       int s_hi, int n, PropBufs<real> b, const real *gin, real *gout, double *acc, int final_mode,
                       const double *phit, const double *d, double *out, double *part, const double *partG,
-                      int fold_q, const Plan &qp, hipEvent_t e0, hipEvent_t e1)
+                      int fold_q, const Plan &qp, const double *wsol, hipEvent_t e0, hipEvent_t e1)
 {
 #define HSF_CASE(CX, CY, CZ, K)                                                                        \
     if (cfg.cx == CX && cfg.cy == CY && cfg.cz == CZ && cfg.k == K)                                    \
         return BlockKernels<real, CX, CY, CZ, K>::bwd(s, p, rep, st, ch, s_hi, n, b, gin, gout, acc,       \
-                                                      final_mode, phit, d, out, part, partG, fold_q, qp, e0, e1);
+                                                      final_mode, phit, d, out, part, partG, fold_q, qp, wsol, e0, e1);
     HSF_TILE_CONFIGS(HSF_CASE)
 #undef HSF_CASE
 }
@@ -1256,7 +1261,7 @@ void launch_bwd_block(const TileCfg &cfg, hipStream_t s, const Plan &p, const Re
     template void launch_bwd_block<real>(const TileCfg &, hipStream_t, const Plan &, const Rep *,         \
                                          RepState *, Chain, int, int, PropBufs<real>, const real *,       \
                                          real *, double *, int, const double *, const double *, double *, \
-                                         double *, const double *, int, const Plan &, hipEvent_t,         \
+                                         double *, const double *, int, const Plan &, const double *, hipEvent_t, \
                                          hipEvent_t);                                                     \
     template void launch_pair_block<real>(const TileCfg &, hipStream_t, const Plan &, const Rep *,        \
                                           RepState *, Chain, const PairSteps &, PropBufs<real>,          \

@@ -435,16 +435,16 @@ static void rows_launch(hipStream_t s, const Plan &p, const Rep *rep, RepState *
 
 template <typename real>
 void launch_rows(const TileCfg &cfg, hipStream_t s, const Plan &p, const Rep *rep, RepState *st, const Chain &ch,
-                 RowsHalf f, RowsHalf g, bool has_f, bool has_g, PropBufs<real> b, const real *fin, real *fout,
+                 const RowsLaunch &l, PropBufs<real> b, const real *fin, real *fout,
                  const real *gin, real *gout, double *partG, int sums, hipEvent_t e0, hipEvent_t e1)
 {
     RowsInfo info{};
-    info.f = f;
-    info.g = g;
+    info.f = l.f;
+    info.g = l.g;
     info.N = ch.N;
     for (int k = 0; k < ch.N; ++k) info.types |= (unsigned long long)(ch.types[k] & 1) << k;
-    info.nf = has_f ? p.nblocks : 0;
-    const int grid = info.nf + (has_g ? p.nblocks : 0);
+    info.nf = l.has_f ? p.nblocks : 0;
+    const int grid = info.nf + (l.has_g ? p.nblocks : 0);
 #define HSF_CASE(CX, CY, CZ, K)                                                                              \
     if constexpr (sizeof(real) == 4 || rows_fp64(CX, CY, CZ, K))                                             \
         if (cfg.cx == CX && cfg.cy == CY && cfg.cz == CZ && cfg.k == -K)                                     \
@@ -456,7 +456,7 @@ void launch_rows(const TileCfg &cfg, hipStream_t s, const Plan &p, const Rep *re
 
 #define HSF_INST(real)                                                                                        \
     template void launch_rows<real>(const TileCfg &, hipStream_t, const Plan &, const Rep *, RepState *,      \
-                                    const Chain &, RowsHalf, RowsHalf, bool, bool, PropBufs<real>, const real *, \
+                                    const Chain &, const RowsLaunch &, PropBufs<real>, const real *,         \
                                     real *, const real *, real *, double *, int, hipEvent_t, hipEvent_t);
 HSF_INST(double)
 HSF_INST(float)

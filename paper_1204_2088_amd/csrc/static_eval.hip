@@ -1,13 +1,18 @@
 // static_eval.hip -- the density functional of hsf_evaluate for callers that cannot
 // allocate device memory: one replica, no context, every scratch buffer (propagators,
 // partial sums, plans, descriptor and control state) carved out of one file-scope device
-// array.  The kernels are the library's own (one contour step per launch, the 32x8
-// column tiling with 2 planes per thread).
+// array.  The kernels are the library's own: the row sweeps where the array holds their two
+// extra planes, else one contour step per launch.  FP32 propagators need their per-step
+// scales first: a forward sweep measures them (the backward sweep and the densities are
+// not needed for that).  The launches are issued one by one, so their number is what a call
+// costs: a 40x36x30 A3B9 + S evaluation in FP32 took 60 launches and 241 to 266 us with
+// one-step sweeps run twice.
 #include <algorithm>
 #include <mutex>
 
 #include "hsf_internal.h"
 #include "prop_block.h"
+#include "prop_rows.h"
 
 using namespace hsf;
 
@@ -18,6 +23,9 @@ namespace {
 static __device__ __align__(256) unsigned char scratch[HSF_STATIC_SCRATCH_BYTES];
 
 constexpr TileCfg kStaticTile{32, 8, 2, 0};
+
+// Row bundles of the sweeps: at least as fast as any other up to 32^3 and from 48^3 to 64^3.
+TileCfg static_rows(long long V) { return V < 65536 ? TileCfg{64, 4, 4, -4} : TileCfg{64, 8, 4, -3}; }
 constexpr int kMaxDevices = 64;
 
 // Device address of `scratch` per device, taken once with that device current (in host
@@ -41,10 +49,11 @@ int scratch_address(void **out)
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// Descriptor, cleared control state and the two one-replica block tables (site plan and
-// tile plan), written by a kernel: no host copies and no memset nodes.
+// Descriptor, cleared control state and the one-replica block tables (site plan, tile plan
+// and row plan), written by a kernel: no host copies and no memset nodes.
 __global__ __launch_bounds__(kBlock) void k_static_setup(Rep R, Rep *rep, RepState *st, int *blk_rep, int *blk_first,
-                                                         int nbs, int *tblk_rep, int *tblk_first, int nbt)
+                                                         int nbs, int *tblk_rep, int *tblk_first, int nbt,
+                                                         int *rblk_rep, int *rblk_first, int nbr)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t == 0) {
@@ -53,11 +62,16 @@ __global__ __launch_bounds__(kBlock) void k_static_setup(Rep R, Rep *rep, RepSta
         blk_first[1] = nbs;
         tblk_first[0] = 0;
         tblk_first[1] = nbt;
+        if (nbr) {
+            rblk_first[0] = 0;
+            rblk_first[1] = nbr;
+        }
     }
     int *sw = reinterpret_cast<int *>(st);
     for (int k = t; k < (int)(sizeof(RepState) / 4); k += gridDim.x * blockDim.x) sw[k] = 0;
     for (int k = t; k < nbs; k += gridDim.x * blockDim.x) blk_rep[k] = 0;
     for (int k = t; k < nbt; k += gridDim.x * blockDim.x) tblk_rep[k] = 0;
+    for (int k = t; k < nbr; k += gridDim.x * blockDim.x) rblk_rep[k] = 0;
 }
 
 // Q of the evaluation (NaN when it left the floating-point range).
@@ -67,13 +81,15 @@ __global__ void k_static_q(const RepState *st, double *q_out)
 }
 
 struct Layout {
-    size_t rep, st, blk_rep, blk_first, tblk_rep, tblk_first, part, partG, E, G, Gp0, Gp1, total;
+    size_t rep, st, blk_rep, blk_first, tblk_rep, tblk_first, rblk_rep, rblk_first, part, partG, E, G, Gp0, Gp1, Gf0, Gf1,
+        total;
 };
 
-Layout layout(long long V, int N, size_t rs, int nbs, int nbt)
+// nbr: blocks of the row plan, 0 for one-step sweeps (which need no Gf planes)
+Layout layout(long long V, int N, size_t rs, int nbs, int nbt, int nbr)
 {
     Layout L{};
-    const int nb = std::max(nbs, nbt);
+    const int nb = std::max(std::max(nbs, nbt), nbr);
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -86,36 +102,92 @@ Layout layout(long long V, int N, size_t rs, int nbs, int nbt)
     L.blk_first = take(sizeof(int) * 2);
     L.tblk_rep = take(sizeof(int) * nbt);
     L.tblk_first = take(sizeof(int) * 2);
+    L.rblk_rep = take(sizeof(int) * nbr);
+    L.rblk_first = take(nbr ? sizeof(int) * 2 : 0);
     L.part = take(sizeof(double) * kNQ * nb);
     L.partG = take(sizeof(double) * (N + 2) * nb);
     L.E = take(rs * 2 * V);
     L.G = take(rs * (size_t)N * V);
     L.Gp0 = take(rs * V);
     L.Gp1 = take(rs * V);
+    L.Gf0 = take(nbr ? rs * V : 0);
+    L.Gf1 = take(nbr ? rs * V : 0);
     L.total = o;
     return L;
 }
 
+// One evaluation; scales_only: the forward sweep alone, and from it the per-step scales.
 template <typename real>
 void static_pass(hipStream_t s, const Plan &plan, const Plan &tplan, Rep *rep, RepState *st, const Chain &ch,
-                 PropBufs<real> b, const double *w, const double *phi, double *phi_out, double *part, double *partG)
+                 PropBufs<real> b, const double *w, const double *phi, double *phi_out, double *part, double *partG,
+                 bool scales_only)
 {
     const int N = ch.N;
-    launch_target_stats(s, plan, rep, st, ch, phi, w, part);
-    launch_reduce_ctl(s, 1, plan, st, rep, part, PH_TARGET, ch, plan, partG, 0.0, 0, nullptr);
     for (int s0 = 0; s0 < N; ++s0)
         launch_fwd_block<real>(kStaticTile, s, tplan, rep, st, ch, s0, 1, b, partG, 1, w, nullptr, 0, nullptr,
                                nullptr);
+    if (scales_only) {
+        launch_reduce_ctl(s, 1, plan, st, rep, part, PH_SCALES, ch, tplan, partG, 0.0, 0, nullptr);
+        return;
+    }
     const bool fold_q = N > 1;   // with N = 1 step 1 is step N: Q first, in its own launch
     if (!fold_q) launch_reduce_ctl(s, 1, tplan, st, rep, part, PH_Q, ch, tplan, partG, 0.0, 0, nullptr);
     int parity = 0;
     for (int s_hi = N; s_hi >= 1; --s_hi) {
         launch_bwd_block<real>(kStaticTile, s, tplan, rep, st, ch, s_hi, 1, b, b.Gp[parity ^ 1], b.Gp[parity],
-                               nullptr, 0, phi, nullptr, phi_out, part, partG, fold_q ? 1 : 0, tplan, nullptr,
-                               nullptr);
+                               nullptr, 0, phi, nullptr, phi_out, part, partG, fold_q ? 1 : 0, tplan,
+                               ch.nsp == 3 ? w : nullptr, nullptr, nullptr);
         parity ^= 1;
     }
-    launch_reduce_ctl(s, 1, tplan, st, rep, part, PH_SCALES, ch, tplan, partG, 0.0, 0, nullptr);
+}
+
+// The same with the row sweeps (the field factors are there).
+template <typename real>
+void static_rows_pass(hipStream_t s, const TileCfg &tile, const Plan &plan, const Plan &tplan, const Plan &rplan,
+                      Rep *rep, RepState *st, const Chain &ch, PropBufs<real> b, real *Gf0, real *Gf1, const double *w,
+                      const double *phi, double *phi_out, double *part, double *partG, bool scales_only)
+{
+    const int N = ch.N, K = -tile.k;
+    real *Gf[2] = {Gf0, Gf1};
+    if (scales_only) {
+        for (int j = 1; j <= rows_blocks_of(N, K); ++j) {
+            RowsLaunch l = rows_schedule(N, K, j);
+            l.has_g = false;
+            l.f.late = l.f.from_pp = l.f.out = 0;   // every G_s in its slot
+            launch_rows<real>(tile, s, rplan, rep, st, ch, l, b, nullptr, nullptr, nullptr, nullptr, partG, 1, nullptr,
+                              nullptr);
+        }
+        launch_reduce_ctl(s, 1, plan, st, rep, part, PH_SCALES, ch, rplan, partG, 0.0, 0, nullptr);
+        return;
+    }
+    int parity = 0;
+    for (int j = 1; j <= rows_launches(N, K); ++j) {
+        const RowsLaunch l = rows_schedule(N, K, j);
+        launch_rows<real>(tile, s, rplan, rep, st, ch, l, b, Gf[(j - 1) & 1], Gf[j & 1], b.Gp[parity ^ 1],
+                          b.Gp[parity], partG, 0, nullptr, nullptr);
+        if (l.has_g) parity ^= 1;
+    }
+    launch_bwd_block<real>(kStaticTile, s, tplan, rep, st, ch, 1, 1, b, b.Gp[parity ^ 1], b.Gp[parity], nullptr, 0, phi,
+                           nullptr, phi_out, part, partG, 2, rplan, ch.nsp == 3 ? w : nullptr, nullptr, nullptr);
+}
+
+template <typename real>
+void static_evaluate(hipStream_t s, unsigned char *base, const Layout &L, const TileCfg *rows, const Plan &plan,
+                     const Plan &tplan, const Plan &rplan, Rep *rep, RepState *st, const Chain &ch, const double *w,
+                     const double *phi, double *phi_out, double *part, double *partG)
+{
+    PropBufs<real> b{(real *)(base + L.E), (real *)(base + L.G), {(real *)(base + L.Gp0), (real *)(base + L.Gp1)}};
+    launch_target_stats(s, plan, rep, st, ch, phi, w, ch.nsp == 3, part);
+    launch_reduce_ctl(s, 1, plan, st, rep, part, ch.nsp == 3 ? PH_TARGET_SOLVENT : PH_TARGET, ch, plan, partG, 0.0, 0,
+                      nullptr);
+    if (rows) launch_field_exp<real>(s, plan, rep, st, ch, w, nullptr, 0, b.E, nullptr, nullptr);
+    for (int k = sizeof(real) == sizeof(float) ? 0 : 1; k < 2; ++k) {
+        if (rows)
+            static_rows_pass<real>(s, *rows, plan, tplan, rplan, rep, st, ch, b, (real *)(base + L.Gf0),
+                                   (real *)(base + L.Gf1), w, phi, phi_out, part, partG, k == 0);
+        else
+            static_pass<real>(s, plan, tplan, rep, st, ch, b, w, phi, phi_out, part, partG, k == 0);
+    }
 }
 
 }  // namespace
@@ -164,7 +236,14 @@ extern "C" int hsf_evaluate_static(const hsf_params *p, const double *w, const d
                              ((R.Ly + kStaticTile.cy - 1) / kStaticTile.cy) * ((R.Lz + kStaticTile.cz - 1) / kStaticTile.cz);
     if (nbs_ll > (1LL << 30) || nbt_ll > (1LL << 30)) return HSF_EINVAL;
     const int nbs = (int)nbs_ll, nbt = (int)nbt_ll;
-    const Layout L = layout(R.V, ch.N, rs, nbs, nbt);
+    // row sweeps when the array holds them (chains of at least two beads)
+    const TileCfg rows = static_rows(R.V);
+    int nbr = ch.N >= 2 ? (int)std::min(rows_blocks(rows, R.Lx, R.Ly, R.Lz), 1LL << 30) : 0;
+    Layout L = layout(R.V, ch.N, rs, nbs, nbt, nbr);
+    if (nbr && L.total > (size_t)HSF_STATIC_SCRATCH_BYTES) {
+        nbr = 0;
+        L = layout(R.V, ch.N, rs, nbs, nbt, 0);
+    }
     if (L.total > (size_t)HSF_STATIC_SCRATCH_BYTES) return HSF_EINVAL;
 
     unsigned char *base = nullptr;
@@ -172,7 +251,7 @@ extern "C" int hsf_evaluate_static(const hsf_params *p, const double *w, const d
     hipStream_t s = (hipStream_t)hip_stream;
     Rep *rep = (Rep *)(base + L.rep);
     RepState *st = (RepState *)(base + L.st);
-    Plan plan, tplan;
+    Plan plan, tplan, rplan;
     plan.nblocks = nbs;
     plan.n_rep = 1;
     plan.blk_rep = (int *)(base + L.blk_rep);
@@ -181,31 +260,24 @@ extern "C" int hsf_evaluate_static(const hsf_params *p, const double *w, const d
     tplan.n_rep = 1;
     tplan.blk_rep = (int *)(base + L.tblk_rep);
     tplan.blk_first = (int *)(base + L.tblk_first);
-    const int bf_s[2] = {0, nbs}, bf_t[2] = {0, nbt};
+    rplan.nblocks = nbr;
+    rplan.n_rep = 1;
+    rplan.blk_rep = (int *)(base + L.rblk_rep);
+    rplan.blk_first = (int *)(base + L.rblk_first);
+    const int bf_s[2] = {0, nbs}, bf_t[2] = {0, nbt}, bf_r[2] = {0, nbr};
     set_plan_args(plan, &R, 1, bf_s);
     set_plan_args(tplan, &R, 1, bf_t);
+    set_plan_args(rplan, &R, 1, bf_r);
     double *part = (double *)(base + L.part), *partG = (double *)(base + L.partG);
 
     hipLaunchKernelGGL(k_static_setup, dim3(64), dim3(kBlock), 0, s, R, rep, st, plan.blk_rep, plan.blk_first, nbs,
-                       tplan.blk_rep, tplan.blk_first, nbt);
-    // FP32 propagators: the first pass measures the per-step power-of-two scales, the second
-    // evaluates with them (the context-based evaluation carries them between calls)
-    const int passes = p->precision == HSF_FP32 ? 2 : 1;
-    for (int k = 0; k < passes; ++k) {
-        if (p->precision == HSF_FP32) {
-            PropBufs<float> b{(float *)(base + L.E), (float *)(base + L.G), {(float *)(base + L.Gp0), (float *)(base + L.Gp1)}};
-            static_pass<float>(s, plan, tplan, rep, st, ch, b, w, phi, phi_out, part, partG);
-        } else {
-            PropBufs<double> b{(double *)(base + L.E), (double *)(base + L.G),
-                               {(double *)(base + L.Gp0), (double *)(base + L.Gp1)}};
-            static_pass<double>(s, plan, tplan, rep, st, ch, b, w, phi, phi_out, part, partG);
-        }
-    }
-    if (ch.nsp == 3) {
-        launch_solvent(s, plan, rep, st, ch, 0, w, phi, phi_out, part);
-        launch_reduce_ctl(s, 1, plan, st, rep, part, PH_SOLVENT, ch, plan, partG, 0.0, 0, nullptr);
-        launch_solvent(s, plan, rep, st, ch, 1, w, phi, phi_out, part);
-    }
+                       tplan.blk_rep, tplan.blk_first, nbt, rplan.blk_rep, rplan.blk_first, nbr);
+    if (p->precision == HSF_FP32)
+        static_evaluate<float>(s, base, L, nbr ? &rows : nullptr, plan, tplan, rplan, rep, st, ch, w, phi, phi_out, part,
+                               partG);
+    else
+        static_evaluate<double>(s, base, L, nbr ? &rows : nullptr, plan, tplan, rplan, rep, st, ch, w, phi, phi_out,
+                                part, partG);
     hipLaunchKernelGGL(k_static_q, dim3(1), dim3(1), 0, s, st, q_out);
     return hipGetLastError() == hipSuccess ? HSF_OK : HSF_EHIP;
 }

@@ -152,3 +152,25 @@ def test_rows_repeat_bitwise(hsf, precision, tile):
         got, qk = ctx.evaluate()
         assert np.array_equal(got, ref) and np.array_equal(q, qk), k
     ctx.close()
+
+
+@pytest.mark.parametrize("L,n,precision", [((64, 64, 64), 27, "fp64"), ((64, 64, 64), 25, "fp64"),
+                                           ((41, 40, 40), 16, "fp32"), ((9, 7, 5), 2, "fp32"), ((9, 7, 5), 1, "fp64")])
+def test_static_evaluation_at_its_limits(hsf, L, n, precision):
+    """The allocation-free evaluation: the largest chains its array holds with one-step sweeps
+    only (64^3, N = 27 in FP64) and with row sweeps (N = 25), both row bundles, the shortest
+    chains; the same densities as hsf_evaluate (1e-10 relative, FP32 1e-5)."""
+    import torch
+    wl = workload(L, W.chain(n // 2, n - n // 2), precision)
+    phi, w = W.initial_composition(wl) if n > 1 else np.ones((2,) + wl.shape) * [[[[0.0]]], [[[1.0]]]], fields(wl, 12)
+    ctx = hsf.Context(wl)
+    ctx.set_densities(phi.ravel())
+    ctx.set_fields(w.ravel())
+    ref, q = ctx.evaluate()
+    ctx.close()
+    wd, pd = torch.from_numpy(w.ravel().copy()).cuda(), torch.from_numpy(phi.ravel().copy()).cuda()
+    out, qd = torch.zeros_like(wd), torch.zeros(1, dtype=torch.float64, device="cuda")
+    assert hsf.evaluate_static(wl, wd, pd, out, qd) == hsf.HSF_OK
+    torch.cuda.synchronize()
+    tol = 1e-10 if precision == "fp64" else 1e-5
+    assert rel(out.cpu().numpy(), ref) < tol and abs(qd.item() / q[0] - 1) < tol
