@@ -49,6 +49,8 @@ struct hsf_ctx {
     double *w_start = nullptr;       // fields at the start of a coupled step (rollback of a failed step)
     int *bad_h = nullptr;            // pinned flag set by the LB and CD kernels on a non-finite result
     int *bad_hd = nullptr;           // its device-side address
+    Plan muplan, cdplan;             // column plans (chemical potential, convection-diffusion)
+    int col_p = 1;                   // their sites per lane
     Plan plan;                       // site plan: kBlock consecutive sites per block
     Plan cplan;                      // the same with span sites per block, for the kernels that reduce
     TileCfg tile{8, 8, 8, 2};        // propagator tile configuration in use
@@ -946,8 +948,8 @@ int cn_residual(hsf_ctx *c, double *F_out, long long *evals)
     *evals += c->n_rep;
     c->work_evals += c->n_rep;
     for (int r = 0; r < c->n_rep; ++r) c->work_site_evals += (double)c->reps[r].V;
-    launch_mu(c->stream, c->plan, c->rep_d, c->ch, c->eval_out, c->w, c->mu);
-    launch_cd(c->stream, c->plan, c->rep_d, c->ch, c->eval_out, c->mu, nullptr, c->cn_half, nullptr, 0, nullptr,
+    launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->eval_out, c->w, c->mu);
+    launch_cd(c->stream, c->cdplan, c->col_p, c->plan, c->rep_d, c->ch, c->eval_out, c->mu, nullptr, c->cn_half, nullptr, 0, nullptr,
               nullptr, 0.5);
     launch_cn_residual(c->stream, F_out, c->eval_out, c->cn_half, c->cn_rhs, cn_n(c));
     HIPCHK(c, hipGetLastError());
@@ -1184,6 +1186,22 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     cblk_first.push_back((int)cblk_rep.size());
     c->cplan.nblocks = (int)cblk_rep.size();
     c->cplan.n_rep = n_rep;
+    // columns: two sites per lane where every row is a whole wavefront of them
+    c->col_p = 2;
+    for (const Rep &R : c->reps)
+        if (R.Lx != 128) c->col_p = 1;
+    std::vector<int> kblk_rep[2], kblk_first[2];
+    for (int k = 0; k < 2; ++k) {
+        for (int r = 0; r < n_rep; ++r) {
+            const Rep &R = c->reps[r];
+            kblk_first[k].push_back((int)kblk_rep[k].size());
+            kblk_rep[k].insert(kblk_rep[k].end(), (size_t)col_blocks(c->col_p, k ? kCdZ : kMuZ, R.Lx, R.Ly, R.Lz), r);
+        }
+        kblk_first[k].push_back((int)kblk_rep[k].size());
+        Plan &p = k ? c->cdplan : c->muplan;
+        p.nblocks = (int)kblk_rep[k].size();
+        p.n_rep = n_rep;
+    }
     c->lb_all = c->reps[0].lb_mode;
     for (const Rep &R : c->reps)
         if (R.lb_mode != c->lb_all) c->lb_all = -1;
@@ -1222,6 +1240,11 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     ALLOC(c->st_save, sizeof(RepState) * n_rep);
     ALLOC(c->plan.blk_rep, sizeof(int) * blk_rep.size());
     ALLOC(c->plan.blk_first, sizeof(int) * blk_first.size());
+    for (int k = 0; k < 2; ++k) {
+        Plan &p = k ? c->cdplan : c->muplan;
+        ALLOC(p.blk_rep, sizeof(int) * kblk_rep[k].size());
+        ALLOC(p.blk_first, sizeof(int) * kblk_first[k].size());
+    }
     ALLOC(c->cplan.blk_rep, sizeof(int) * cblk_rep.size());
     ALLOC(c->cplan.blk_first, sizeof(int) * cblk_first.size());
     ALLOC(c->w, sizeof(double) * nsp * T);
@@ -1289,6 +1312,13 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
         e = hipMemcpy(c->plan.blk_rep, blk_rep.data(), sizeof(int) * blk_rep.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(c->plan.blk_first, blk_first.data(), sizeof(int) * blk_first.size(), hipMemcpyHostToDevice);
+    for (int k = 0; k < 2; ++k) {
+        Plan &p = k ? c->cdplan : c->muplan;
+        if (e == hipSuccess)
+            e = hipMemcpy(p.blk_rep, kblk_rep[k].data(), sizeof(int) * kblk_rep[k].size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(p.blk_first, kblk_first[k].data(), sizeof(int) * kblk_first[k].size(), hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess)
         e = hipMemcpy(c->cplan.blk_rep, cblk_rep.data(), sizeof(int) * cblk_rep.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
@@ -1446,9 +1476,13 @@ int hsf_invert(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats 
 int hsf_mu_force(hsf_ctx *c, double *mu, double *force, int where)
 {
     if (!c) return HSF_EINVAL;
-    launch_mu(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->w, c->mu);
-    launch_force(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->mu, c->force);
+    // device buffers are written by the kernels themselves
+    const bool direct = where == HSF_DEVICE;
+    double *m = direct && mu ? mu : c->mu, *f = direct && force ? force : c->force;
+    launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->phi, c->w, m);
+    launch_force(c->stream, c->plan, c->rep_d, c->ch, c->phi, m, f);
     HIPCHK(c, hipGetLastError());
+    if (direct) return HSF_OK;
     int rc = HSF_OK;
     if (mu) rc = copy_out(c, mu, c->mu, (size_t)c->ch.nsp * c->T, where);
     if (rc == HSF_OK && force) rc = copy_out(c, force, c->force, (size_t)3 * c->T, where);
@@ -1493,7 +1527,9 @@ int hsf_lb_advance(hsf_ctx *c, int n_steps, const double *force, int where)
 {
     if (!c || n_steps < 0) return HSF_EINVAL;
     const double *f = nullptr;
-    if (force) {
+    if (force && where == HSF_DEVICE) {
+        f = force;   // read in place, on the context's stream
+    } else if (force) {
         int rc = copy_in(c, c->uin, force, (size_t)3 * c->T, where);
         if (rc) return rc;
         f = c->uin;
@@ -1523,25 +1559,25 @@ int hsf_get_flow(hsf_ctx *c, double *rho, double *u, int where)
 int hsf_cd_advance(hsf_ctx *c, const double *mu, const double *u, int where)
 {
     if (!c || !mu) return HSF_EINVAL;
-    int rc = copy_in(c, c->mu, mu, (size_t)c->ch.nsp * c->T, where);
-    if (rc) return rc;
-    const double *uu = nullptr;
-    if (u) {
-        if ((rc = copy_in(c, c->uin, u, (size_t)3 * c->T, where))) return rc;
-        uu = c->uin;
+    // device buffers are read in place, on the context's stream
+    const double *mm = mu, *uu = u;
+    if (where != HSF_DEVICE) {
+        int rc = copy_in(c, c->mu, mu, (size_t)c->ch.nsp * c->T, where);
+        if (rc) return rc;
+        mm = c->mu;
+        if (u) {
+            if ((rc = copy_in(c, c->uin, u, (size_t)3 * c->T, where))) return rc;
+            uu = c->uin;
+        }
     }
-    launch_cd(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->mu, uu, c->phi_tmp,
+    launch_cd(c->stream, c->cdplan, c->col_p, c->plan, c->rep_d, c->ch, c->phi, mm, uu, c->phi_tmp,
               (c->noise & HSF_NOISE_CD) ? c->noise_flux : nullptr, c->noise_step);
     if (c->noise) ++c->noise_step;
     HIPCHK(c, hipGetLastError());
-    HIPCHK(c, hipMemcpyAsync(c->phi, c->phi_tmp, sizeof(double) * c->ch.nsp * c->T, hipMemcpyDeviceToDevice,
-                             c->stream));
+    std::swap(c->phi, c->phi_tmp);   // captured sequences exist once per density buffer
     return HSF_OK;
 }
 
-// A failed coupled step leaves the state of its start: the fields and replica states
-// (scales, control) are copied back, and the densities and LB populations are only
-// replaced once the step has finished with finite results.
 static int rollback_step(hsf_ctx *c)
 {
     HIPCHK(c, hipMemcpyAsync(c->w, c->w_start, sizeof(double) * c->ch.nsp * c->T, hipMemcpyDeviceToDevice,
@@ -1649,7 +1685,7 @@ int hsf_step(hsf_ctx *c, int n_steps, double tol, int max_iter, hsf_invert_stats
             HIPCHK(c, hipEventRecord(c->log_ev[1], c->stream));
         }
         *c->bad_h = 0;   // the kernels below set it on a non-finite result
-        launch_mu(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->w, c->mu);
+        launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->phi, c->w, c->mu);
         const double *uu = nullptr;
         if (c->hydro) {
             launch_force(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->mu, c->force);
@@ -1665,7 +1701,7 @@ int hsf_step(hsf_ctx *c, int n_steps, double tol, int max_iter, hsf_invert_stats
             // the densities below)
             if ((rc = commit_history(c))) return rc;
             // right-hand side phi^n + dt/2 B^n - div J^C + xi, then the implicit solve
-            launch_cd(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->mu, uu, c->cn_rhs,
+            launch_cd(c->stream, c->cdplan, c->col_p, c->plan, c->rep_d, c->ch, c->phi, c->mu, uu, c->cn_rhs,
                       (c->noise & HSF_NOISE_CD) ? c->noise_flux : nullptr, c->noise_step, nullptr, nullptr, 0.5,
                       c->bad_hd);
             long long ev = 0;
@@ -1689,7 +1725,7 @@ int hsf_step(hsf_ctx *c, int n_steps, double tol, int max_iter, hsf_invert_stats
         }
         {
             Timed t(c, HSF_K_CD);
-            launch_cd(c->stream, c->plan, c->rep_d, c->ch, c->phi, c->mu, uu, c->phi_tmp,
+            launch_cd(c->stream, c->cdplan, c->col_p, c->plan, c->rep_d, c->ch, c->phi, c->mu, uu, c->phi_tmp,
                       (c->noise & HSF_NOISE_CD) ? c->noise_flux : nullptr, c->noise_step, t.a, t.b, 1.0,
                       c->bad_hd);
         }

@@ -31,6 +31,48 @@ __device__ __forceinline__ double from_right(double v)
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Value of the neighbouring lane, the wavefront taken as a ring (wave_ror:1 / wave_rol:1).
+__device__ __forceinline__ float ring_left(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x13c, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float ring_right(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x134, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double ring_left(double v)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x13c, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x13c, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double ring_right(double v)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x134, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x134, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+// P consecutive sites of a row.
+template <typename real, int P>
+struct Sites {
+    real s[P];
+};
+
+// x neighbours' sum of each of the lane's sites.
+template <typename real>
+__device__ __forceinline__ Sites<real, 1> x_sums(const Sites<real, 1> &v)
+{
+    return {{ring_left(v.s[0]) + ring_right(v.s[0])}};
+}
+template <typename real>
+__device__ __forceinline__ Sites<real, 2> x_sums(const Sites<real, 2> &v)
+{
+    return {{ring_left(v.s[1]) + v.s[1], v.s[0] + ring_right(v.s[0])}};
+}
+
 // Periodic wrap of an index that is at most one step outside [0, L).
 __device__ __forceinline__ int wrap1(int i, int L) { return i < 0 ? i + L : (i >= L ? i - L : i); }
 

@@ -41,116 +41,147 @@ __device__ __forceinline__ long long sidx(const Rep &R, int x, int y, int z)
     return (long long)x + (long long)R.Lx * ((long long)y + (long long)R.Ly * z);
 }
 
-// x-neighbours by lane exchange.  In a site plan the lanes of a wavefront hold
-// consecutive sites of one replica, so the lane to the left holds site x - 1 of the same
-// row unless the site is the first of its row or the lane the first of its wavefront,
-// and likewise to the right; those lanes load the neighbour instead.  Every lane takes
-// part in the exchange (lanes past the box's end work on its last site and store
-// nothing); the values are the loads they replace, so results are unchanged bit for bit.
-struct XLanes {
-    bool lw, rw;   // the neighbour is held by the adjacent lane
-    int dl, dr;    // offsets of the periodic x - 1 and x + 1 from the site
+// A wavefront's part of the column plan: P consecutive x sites per lane of one row, CZ core
+// planes.  Rows of exactly 64 P sites are whole (the lanes form the periodic ring); others
+// are cut into pieces with a halo site at both ends, whose lanes compute and store nothing.
+// Every lane's address is inside the box.
+template <int P, int CZ>
+struct Col {
+    int r, y, z0, nz, plane, Lz;
+    long long V, row, up, dn;    // offsets of the row and of its y neighbours within a plane
+    unsigned xb;                 // the lane's byte offset in a row
+    bool core;                   // its sites are the wavefront's to store
+
+    __device__ __forceinline__ bool init(const int *blk_rep, const int *blk_first, const Rep *rep)
+    {
+        const int pb = plan_block();
+        r = blk_rep[pb];
+        const Rep &R = rep[r];
+        const RowsCut cut = rows_cut(R.Lx, P, 1);
+        int lb = pb - blk_first[r];
+        const int x0 = (lb % cut.ntx) * cut.width;
+        lb /= cut.ntx;
+        const int nty = (R.Ly + kColY - 1) / kColY;
+        y = (lb % nty) * kColY + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        z0 = (lb / nty) * CZ;
+        if (y >= R.Ly) return false;
+        Lz = R.Lz;
+        nz = min(CZ, Lz - z0);
+        V = R.V;
+        plane = R.Lx * R.Ly;
+        row = (long long)y * R.Lx;
+        dn = (long long)wrap1(y - 1, R.Ly) * R.Lx;
+        up = (long long)wrap1(y + 1, R.Ly) * R.Lx;
+        const int xu = x0 - cut.halo + ((int)threadIdx.x & 63) * P;
+        core = xu >= x0 && xu < x0 + cut.width && xu < R.Lx;
+        int x = xu % R.Lx;
+        if (x < 0) x += R.Lx;
+        xb = (unsigned)x * (unsigned)sizeof(double);
+        return true;
+    }
+    // offset of plane z0 - 1 + q, q = 0 .. CZ + 1 (past a short last chunk: its end)
+    __device__ __forceinline__ long long z(int q) const
+    {
+        return (long long)wrap1(min(z0 - 1 + q, z0 + nz), Lz) * plane;
+    }
+    __device__ __forceinline__ Sites<double, P> load(const double *f, long long off) const
+    {
+        Sites<double, P> v;
+        __builtin_memcpy(&v, reinterpret_cast<const char *>(f + off) + xb, sizeof v);
+        return v;
+    }
+    __device__ __forceinline__ void store(double *f, long long off, const Sites<double, P> &v) const
+    {
+        __builtin_memcpy(reinterpret_cast<char *>(f + off) + xb, &v, sizeof v);
+    }
 };
 
-__device__ __forceinline__ XLanes x_lanes(int x, int Lx)
+template <int P>
+__device__ __forceinline__ void x_pair(const Sites<double, P> &c, Sites<double, P> &l, Sites<double, P> &h)
 {
-    const int lane = threadIdx.x & 63;
-    XLanes n;
-    n.lw = lane > 0 && x > 0;
-    n.rw = lane < 63 && x < Lx - 1;
-    n.dl = x > 0 ? -1 : Lx - 1;
-    n.dr = x < Lx - 1 ? 1 : 1 - Lx;
-    return n;
-}
-
-// f at x - 1 and x + 1 of site k, given c = f[k].
-template <typename Idx>
-__device__ __forceinline__ void x_pair(const double *f, Idx k, double c, const XLanes &n, double &l, double &r)
-{
-    l = from_left(c);
-    r = from_right(c);
-    if (!n.lw) l = f[k + n.dl];
-    if (!n.rw) r = f[k + n.dr];
-}
-
-// The same for NR rows at once, in one round trip to memory: with every row's centre each
-// lane also loads one more value, its outer x neighbour if it is an edge lane (the left one
-// if it lacks the left, else the right one) and its own site otherwise, so the edge values
-// arrive with the centres; only a lane lacking both neighbours (rows shorter than a
-// wavefront) loads its right neighbour afterwards.
-template <int NR, typename Idx>
-__device__ __forceinline__ void x_rows(const double *f, const Idx (&k)[NR], const XLanes &n, double (&c)[NR],
-                                       double (&l)[NR], double (&r)[NR])
-{
-    const int eo = !n.lw ? n.dl : (!n.rw ? n.dr : 0);
-    double e[NR];
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        c[q] = f[k[q]];
-        e[q] = f[k[q] + eo];
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        const double fl = from_left(c[q]), fr = from_right(c[q]);
-        l[q] = n.lw ? fl : e[q];
-        r[q] = n.rw ? fr : e[q];
-    }
-    if (!n.lw && !n.rw) {
-#pragma unroll
-        for (int q = 0; q < NR; ++q) r[q] = f[k[q] + n.dr];
+    if constexpr (P == 1) {
+        l.s[0] = ring_left(c.s[0]);
+        h.s[0] = ring_right(c.s[0]);
+    } else {
+        l = {{ring_left(c.s[1]), c.s[0]}};
+        h = {{c.s[1], ring_right(c.s[0])}};
     }
 }
 
-// mu_I = -w_I + sum_J chi_IJ sigma[phi_J] + kappa (sum_J phi_J - 1); the stencil sums
-// are formed per class (centre, faces, edges, corners) as in stencil27.  Sites are
-// addressed by 32-bit offsets from each species' base (a replica holds fewer than 2^31
-// sites), and the nine rows of every species are loaded together.
-template <int NSP>
+// mu_I = -w_I + sum_J chi_IJ sigma[phi_J] + kappa (sum_J phi_J - 1).  One species at a time,
+// each wavefront loads the three rows around its own on kMuZ + 2 planes (3 (kMuZ + 2) /
+// kMuZ = 4.5 loads per site, x neighbours from the adjacent lanes) and combines three
+// planes' class sums per site.  With one site per lane and its nine rows loaded anew (18
+// loads per site and species) the kernel was bound by its loads' latency: 85 us for 3 species
+// at 128^3 (151 MB); now 36 us, 4.2 TB/s.
+template <int NSP, int P>
 __global__ __launch_bounds__(kBlock) void k_mu(const int *__restrict__ blk_rep, const int *__restrict__ blk_first,
-                                               const Rep *__restrict__ rep, Chain ch,
-                                               const double *__restrict__ phi, const double *__restrict__ w,
-                                               double *__restrict__ mu)
+                                               const Rep *__restrict__ rep, const double *__restrict__ phi,
+                                               const double *__restrict__ w, double *__restrict__ mu)
 {
-    const SiteRef sr = site_ref(blk_rep, blk_first);
-    const Rep &R = rep[sr.r];
-    const int V = (int)R.V, Lx = R.Lx, Ly = R.Ly, Lz = R.Lz;
-    const bool live = sr.i < V;
-    const int i = live ? (int)sr.i : V - 1;
-    const int x = i % Lx, y = (i / Lx) % Ly, z = i / (Lx * Ly);
-    const XLanes xn = x_lanes(x, Lx);
+    typedef Sites<double, P> row_t;
+    constexpr int CZ = kMuZ;
+    Col<P, CZ> t;
+    if (!t.init(blk_rep, blk_first, rep)) return;
+    const Rep &R = rep[t.r];
     const long long fo = off_field(R, NSP);
-    const int dym = (wrap1(y - 1, Ly) - y) * Lx, dyp = (wrap1(y + 1, Ly) - y) * Lx;
-    const int dzm = (wrap1(z - 1, Lz) - z) * Lx * Ly, dzp = (wrap1(z + 1, Lz) - z) * Lx * Ly;
-    // rows: the site's, four with exactly one of (dy, dz) non-zero, four with both
-    const int k[9] = {i, i + dym, i + dyp, i + dzm, i + dzp, i + dym + dzm, i + dym + dzp, i + dyp + dzm, i + dyp + dzp};
-    double sp[3] = {0, 0, 0}, tot = 0.0;
+    const double c0 = R.c[0], c1 = R.c[1], c2 = R.c[2], c3 = R.c[3];
+    row_t inter[NSP][CZ], tot[CZ];
+#pragma unroll
+    for (int j = 0; j < CZ; ++j)
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            tot[j].s[u] = 0.0;
+#pragma unroll
+            for (int I = 0; I < NSP; ++I) inter[I][j].s[u] = 0.0;
+        }
 #pragma unroll 1
     for (int J = 0; J < NSP; ++J) {
-        const double *f = phi + fo + (long long)J * V;
-        double c[9], l[9], r[9];
-        x_rows(f, k, xn, c, l, r);
-        double s0 = c[0], s1 = l[0] + r[0], s2 = 0, s3 = 0;
-        tot += c[0];
+        const double *f = phi + fo + (long long)J * t.V;
+        row_t c[CZ + 2], m[CZ + 2], p[CZ + 2];
 #pragma unroll
-        for (int q = 1; q < 5; ++q) {
-            s1 += c[q];
-            s2 += l[q] + r[q];
+        for (int q = 0; q < CZ + 2; ++q) {
+            const long long zq = t.z(q);
+            c[q] = t.load(f, zq + t.row);
+            m[q] = t.load(f, zq + t.dn);
+            p[q] = t.load(f, zq + t.up);
+        }
+        row_t a1[CZ + 2], a2[CZ + 2];
+#pragma unroll
+        for (int q = 0; q < CZ + 2; ++q) {
+            const row_t ec = x_sums(c[q]), em = x_sums(m[q]), ep = x_sums(p[q]);
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                a1[q].s[u] = ec.s[u] + (m[q].s[u] + p[q].s[u]);
+                a2[q].s[u] = em.s[u] + ep.s[u];
+            }
         }
 #pragma unroll
-        for (int q = 5; q < 9; ++q) {
-            s2 += c[q];
-            s3 += l[q] + r[q];
-        }
-        sp[J] = R.c[0] * s0 + R.c[1] * s1 + R.c[2] * s2 + R.c[3] * s3;
+        for (int j = 0; j < CZ; ++j)
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const double sp = c0 * c[j + 1].s[u] + c1 * (a1[j + 1].s[u] + (c[j].s[u] + c[j + 2].s[u])) +
+                                  c2 * (a2[j + 1].s[u] + (a1[j].s[u] + a1[j + 2].s[u])) +
+                                  c3 * (a2[j].s[u] + a2[j + 2].s[u]);
+                tot[j].s[u] += c[j + 1].s[u];
+#pragma unroll
+                for (int I = 0; I < NSP; ++I) inter[I][j].s[u] += R.chi[I][J] * sp;
+            }
     }
-    if (!live) return;
+    if (!t.core) return;
 #pragma unroll
-    for (int I = 0; I < NSP; ++I) {
-        double inter = 0.0;
+    for (int j = 0; j < CZ; ++j) {
+        if (j >= t.nz) continue;
+        const long long o = (long long)(t.z0 + j) * t.plane + t.row;
 #pragma unroll
-        for (int J = 0; J < NSP; ++J) inter += R.chi[I][J] * sp[J];
-        const long long k = fo + (long long)I * V;
-        mu[k + i] = -w[k + i] + inter + R.kappa * (tot - 1.0);
+        for (int I = 0; I < NSP; ++I) {
+            const long long k = fo + (long long)I * t.V + o;
+            const row_t wv = t.load(w, k);
+            row_t v;
+#pragma unroll
+            for (int u = 0; u < P; ++u) v.s[u] = -wv.s[u] + inter[I][j].s[u] + R.kappa * (tot[j].s[u] - 1.0);
+            t.store(mu, k, v);
+        }
     }
 }
 
@@ -398,116 +429,114 @@ __global__ __launch_bounds__(kBlock) void k_lb(const int *__restrict__ blk_rep, 
 // phi_new(r) = phi(r) - sum_a (J(r + e_a/2) - J(r - e_a/2)).
 // NOISE adds the composition noise of eq. 5 as a random flux on every bond, drawn
 // beforehand by k_cd_noise into jn.
-template <bool NOISE, int NSP>
+// Columns as in k_mu: z neighbours are the lane's other planes, x neighbours come from the
+// adjacent lanes, the rows y +- 1 are loaded (23 loads per site for 3 species, against 44 with
+// one site per lane, which took 74 us at 128^3 for 201 MB; now 46 us, 4.4 TB/s).
+template <bool NOISE, int NSP, int P>
 __global__ __launch_bounds__(kBlock) void k_cd(const int *__restrict__ blk_rep, const int *__restrict__ blk_first,
-                                               const Rep *__restrict__ rep, Chain ch,
-                                               const double *__restrict__ phi, const double *__restrict__ mu,
-                                               const double *__restrict__ u, double *__restrict__ phi_out,
-                                               const double *__restrict__ jn, double diff_scale,
-                                               int *__restrict__ bad)
+                                               const Rep *__restrict__ rep, const double *__restrict__ phi,
+                                               const double *__restrict__ mu, const double *__restrict__ u,
+                                               double *__restrict__ phi_out, const double *__restrict__ jn,
+                                               double diff_scale, int *__restrict__ bad)
 {
-    const SiteRef sr = site_ref(blk_rep, blk_first);
-    const Rep &R = rep[sr.r];
-    const int V = (int)R.V, Lx = R.Lx, Ly = R.Ly, Lz = R.Lz;
-    const bool live = sr.i < V;
-    const int i = live ? (int)sr.i : V - 1;
-    const int x = i % Lx, y = (i / Lx) % Ly, z = i / (Lx * Ly);
-    const XLanes xn = x_lanes(x, Lx);
+    typedef Sites<double, P> row_t;
+    constexpr int CZ = kCdZ;
+    Col<P, CZ> t;
+    if (!t.init(blk_rep, blk_first, rep)) return;
+    const Rep &R = rep[t.r];
     const long long fo = off_field(R, NSP), vo = 3LL * R.site_off;
-    // y and z neighbours (32-bit offsets: a replica holds fewer than 2^31 sites)
-    const int nb[6] = {i + xn.dl, i + xn.dr,
-                       i + (wrap1(y - 1, Ly) - y) * Lx, i + (wrap1(y + 1, Ly) - y) * Lx,
-                       i + (wrap1(z - 1, Lz) - z) * Lx * Ly, i + (wrap1(z + 1, Lz) - z) * Lx * Ly};
     const double dt = R.dt * diff_scale;   // diffusive flux over dt (or dt/2 in the CN step)
-    // Every load is issued before the first lane exchange: the rows that take their x
-    // neighbours from the adjacent lanes (phi and mu of each species, u_x) with one more
-    // value per row (an edge lane's outer x neighbour, else its own site), and the y and z
-    // neighbours of all of them.  Without a velocity field the u rows read phi and are
-    // replaced by zero.
-    constexpr int NR = 2 * NSP + 1;
-    const double *rows[NR];
-#pragma unroll
-    for (int I = 0; I < NSP; ++I) {
-        rows[2 * I] = phi + fo + (long long)I * V;
-        rows[2 * I + 1] = mu + fo + (long long)I * V;
-    }
-    const double *ub = u ? u + vo : phi + fo;
-    rows[2 * NSP] = ub;
-    double c[NR], lo[NR], hi[NR], ex[NR];
-    const int eo = !xn.lw ? xn.dl : (!xn.rw ? xn.dr : 0);   // an edge lane's outer neighbour
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        c[q] = rows[q][i];
-        ex[q] = rows[q][i + eo];
-    }
-    double uyz[2][3];   // u_y, u_z at (lower neighbour, site, upper neighbour)
-#pragma unroll
-    for (int a = 1; a < 3; ++a) {
-        const double *ua = u ? ub + (long long)a * V : ub;
-        uyz[a - 1][0] = ua[nb[2 * a]];
-        uyz[a - 1][1] = ua[i];
-        uyz[a - 1][2] = ua[nb[2 * a + 1]];
-    }
-    double pyz[NSP][4], myz[NSP][4];   // (y-, y+, z-, z+)
-#pragma unroll
-    for (int I = 0; I < NSP; ++I) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            pyz[I][q] = rows[2 * I][nb[2 + q]];
-            myz[I][q] = rows[2 * I + 1][nb[2 + q]];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        const double fl = from_left(c[q]), fr = from_right(c[q]);
-        lo[q] = xn.lw ? fl : ex[q];
-        hi[q] = xn.rw ? fr : ex[q];
-    }
-    if (!xn.lw && !xn.rw) {   // rows shorter than a wavefront: both neighbours from memory
-#pragma unroll
-        for (int q = 0; q < NR; ++q) hi[q] = rows[q][nb[1]];
-    }
-    // the velocity at the site and its six neighbours, shared by the species
-    double ul[3] = {0, 0, 0}, ur[3] = {0, 0, 0}, uh[3] = {0, 0, 0};
+    // the velocity at the core planes' sites and their neighbours along each axis (l, c, h),
+    // shared by the species
+    row_t ul[3][CZ], uc[3][CZ], uh[3][CZ];
     if (u) {
-        ul[0] = lo[2 * NSP];
-        ur[0] = c[2 * NSP];
-        uh[0] = hi[2 * NSP];
+        const double *ux = u + vo, *uy = ux + t.V, *uz = uy + t.V;
+        row_t zz[CZ + 2];
 #pragma unroll
-        for (int a = 1; a < 3; ++a) {
-            ul[a] = uyz[a - 1][0];
-            ur[a] = uyz[a - 1][1];
-            uh[a] = uyz[a - 1][2];
+        for (int q = 0; q < CZ + 2; ++q) zz[q] = t.load(uz, t.z(q) + t.row);
+#pragma unroll
+        for (int j = 0; j < CZ; ++j) {
+            const long long zq = t.z(j + 1);
+            uc[0][j] = t.load(ux, zq + t.row);
+            ul[1][j] = t.load(uy, zq + t.dn);
+            uc[1][j] = t.load(uy, zq + t.row);
+            uh[1][j] = t.load(uy, zq + t.up);
+            ul[2][j] = zz[j];
+            uc[2][j] = zz[j + 1];
+            uh[2][j] = zz[j + 2];
         }
+#pragma unroll
+        for (int j = 0; j < CZ; ++j) x_pair<P>(uc[0][j], ul[0][j], uh[0][j]);
     }
-#pragma unroll
+#pragma unroll 1
     for (int I = 0; I < NSP; ++I) {
-        const double pr = c[2 * I], mr = c[2 * I + 1];
-        const double pn_l[3] = {lo[2 * I], pyz[I][0], pyz[I][2]}, pn_h[3] = {hi[2 * I], pyz[I][1], pyz[I][3]};
-        const double mn_l[3] = {lo[2 * I + 1], myz[I][0], myz[I][2]},
-                     mn_h[3] = {hi[2 * I + 1], myz[I][1], myz[I][3]};
-        double div = 0.0;
-        const double *jI = NOISE ? jn + 3 * fo + 3 * (long long)I * V : nullptr;
+        const double *f = phi + fo + (long long)I * t.V, *g = mu + fo + (long long)I * t.V;
+        row_t pz[CZ + 2], mz[CZ + 2];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            // face between lo and r, then between r and hi
-            const double pl = pn_l[a], ph = pn_h[a];
-            double jl = dt * (-0.5 * (pl + pr) * (mr - mn_l[a]));
-            double jh = dt * (-0.5 * (pr + ph) * (mn_h[a] - mr));
-            if (u) {
-                jl += (0.5 * (pl + pr) - 0.5 * (pr * ur[a] - pl * ul[a])) * (0.5 * (ul[a] + ur[a]));
-                jh += (0.5 * (pr + ph) - 0.5 * (ph * uh[a] - pr * ur[a])) * (0.5 * (ur[a] + uh[a]));
-            }
-            if (NOISE) {
-                jl += jI[(long long)a * V + nb[2 * a]];
-                jh += jI[(long long)a * V + i];
-            }
-            div += jh - jl;
+        for (int q = 0; q < CZ + 2; ++q) {
+            const long long zq = t.z(q) + t.row;
+            pz[q] = t.load(f, zq);
+            mz[q] = t.load(g, zq);
         }
-        const double pn = pr - div;
-        if (!live) continue;
-        if (bad && !isfinite(pn)) bad[0] = 1;
-        phi_out[fo + (long long)I * V + i] = pn;
+        row_t pl[CZ], ph[CZ], ml[CZ], mh[CZ];   // y neighbours
+#pragma unroll
+        for (int j = 0; j < CZ; ++j) {
+            const long long zq = t.z(j + 1);
+            pl[j] = t.load(f, zq + t.dn);
+            ph[j] = t.load(f, zq + t.up);
+            ml[j] = t.load(g, zq + t.dn);
+            mh[j] = t.load(g, zq + t.up);
+        }
+        const double *jI = NOISE ? jn + 3 * fo + 3 * (long long)I * t.V : nullptr;
+#pragma unroll
+        for (int j = 0; j < CZ; ++j) {
+            row_t xl, xh, yl, yh;   // x neighbours of phi and mu
+            x_pair<P>(pz[j + 1], xl, xh);
+            x_pair<P>(mz[j + 1], yl, yh);
+            row_t nl[3], nh[3];     // noise fluxes of the lower and upper faces
+            if (NOISE) {
+                const long long zq = t.z(j + 1);
+                row_t dummy;
+                nh[0] = t.load(jI, zq + t.row);
+                x_pair<P>(nh[0], nl[0], dummy);
+                nh[1] = t.load(jI, t.V + zq + t.row);
+                nl[1] = t.load(jI, t.V + zq + t.dn);
+                nh[2] = t.load(jI, 2 * t.V + zq + t.row);
+                nl[2] = t.load(jI, 2 * t.V + t.z(j) + t.row);
+            }
+            row_t out;
+#pragma unroll
+            for (int e = 0; e < P; ++e) {
+                const double pr = pz[j + 1].s[e], mr = mz[j + 1].s[e];
+                const double pn_l[3] = {xl.s[e], pl[j].s[e], pz[j].s[e]}, pn_h[3] = {xh.s[e], ph[j].s[e], pz[j + 2].s[e]};
+                const double mn_l[3] = {yl.s[e], ml[j].s[e], mz[j].s[e]}, mn_h[3] = {yh.s[e], mh[j].s[e], mz[j + 2].s[e]};
+                double div = 0.0;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    // face between lo and r, then between r and hi
+                    const double lo = pn_l[a], hi = pn_h[a];
+                    double jl = dt * (-0.5 * (lo + pr) * (mr - mn_l[a]));
+                    double jh = dt * (-0.5 * (pr + hi) * (mn_h[a] - mr));
+                    if (u) {
+                        const double vl = ul[a][j].s[e], vc = uc[a][j].s[e], vh = uh[a][j].s[e];
+                        jl += (0.5 * (lo + pr) - 0.5 * (pr * vc - lo * vl)) * (0.5 * (vl + vc));
+                        jh += (0.5 * (pr + hi) - 0.5 * (hi * vh - pr * vc)) * (0.5 * (vc + vh));
+                    }
+                    if (NOISE) {
+                        jl += nl[a].s[e];
+                        jh += nh[a].s[e];
+                    }
+                    div += jh - jl;
+                }
+                out.s[e] = pr - div;
+            }
+            if (t.core && j < t.nz) {
+#pragma unroll
+                for (int e = 0; e < P; ++e)
+                    if (bad && !isfinite(out.s[e])) bad[0] = 1;
+                t.store(phi_out, fo + (long long)I * t.V + (long long)(t.z0 + j) * t.plane + t.row, out);
+            }
+        }
     }
 }
 
@@ -575,11 +604,11 @@ __global__ __launch_bounds__(kBlock) void k_lb_convert(const int *__restrict__ b
     }
 }
 
-void launch_mu(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi, const double *w,
+void launch_mu(hipStream_t s, const Plan &p, int P, const Rep *rep, Chain ch, const double *phi, const double *w,
                double *mu)
 {
-    hipLaunchKernelGGL(ch.nsp == 3 ? k_mu<3> : k_mu<2>, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first,
-                       rep, ch, phi, w, mu);
+    auto kern = P == 2 ? (ch.nsp == 3 ? k_mu<3, 2> : k_mu<2, 2>) : (ch.nsp == 3 ? k_mu<3, 1> : k_mu<2, 1>);
+    hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, phi, w, mu);
 }
 
 void launch_force(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi, const double *mu,
@@ -622,27 +651,31 @@ void launch_lb_convert(hipStream_t s, const Plan &p, const Rep *rep, bool to_f32
                        to_f32 ? 1 : 0, src, dst);
 }
 
-void launch_cd(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi, const double *mu,
-               const double *u, double *phi_out, double *noise_flux, unsigned long long step, hipEvent_t e0,
-               hipEvent_t e1, double diff_scale, int *bad)
+void launch_cd(hipStream_t s, const Plan &p, int P, const Plan &ps, const Rep *rep, Chain ch, const double *phi,
+               const double *mu, const double *u, double *phi_out, double *noise_flux, unsigned long long step,
+               hipEvent_t e0, hipEvent_t e1, double diff_scale, int *bad)
 {
     // with noise the events bracket both kernels: e0 at the start of the flux draw
     if (noise_flux) {
         if (e0)
-            hipExtLaunchKernelGGL(k_cd_noise, dim3(p.nblocks), dim3(kBlock), 0, s, e0, nullptr, 0, p.blk_rep,
-                                  p.blk_first, rep, ch, phi, noise_flux, step);
+            hipExtLaunchKernelGGL(k_cd_noise, dim3(ps.nblocks), dim3(kBlock), 0, s, e0, nullptr, 0, ps.blk_rep,
+                                  ps.blk_first, rep, ch, phi, noise_flux, step);
         else
-            hipLaunchKernelGGL(k_cd_noise, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, ch,
+            hipLaunchKernelGGL(k_cd_noise, dim3(ps.nblocks), dim3(kBlock), 0, s, ps.blk_rep, ps.blk_first, rep, ch,
                                phi, noise_flux, step);
         e0 = nullptr;
     }
-    auto kern = noise_flux ? (ch.nsp == 3 ? k_cd<true, 3> : k_cd<true, 2>) : (ch.nsp == 3 ? k_cd<false, 3> : k_cd<false, 2>);
+    auto pick = [&](auto three2, auto two2, auto three1, auto two1) {
+        return P == 2 ? (ch.nsp == 3 ? three2 : two2) : (ch.nsp == 3 ? three1 : two1);
+    };
+    auto kern = noise_flux ? pick(k_cd<true, 3, 2>, k_cd<true, 2, 2>, k_cd<true, 3, 1>, k_cd<true, 2, 1>)
+                           : pick(k_cd<false, 3, 2>, k_cd<false, 2, 2>, k_cd<false, 3, 1>, k_cd<false, 2, 1>);
     if (e0 || e1)
-        hipExtLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, e0, e1, 0, p.blk_rep, p.blk_first, rep,
-                              ch, phi, mu, u, phi_out, (const double *)noise_flux, diff_scale, bad);
+        hipExtLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, e0, e1, 0, p.blk_rep, p.blk_first, rep, phi,
+                              mu, u, phi_out, noise_flux, diff_scale, bad);
     else
-        hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, ch, phi, mu, u,
-                           phi_out, (const double *)noise_flux, diff_scale, bad);
+        hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, phi, mu, u,
+                           phi_out, noise_flux, diff_scale, bad);
 }
 
 void launch_lb_rest(hipStream_t s, const Plan &p, const Rep *rep, void *n, bool f32)

@@ -59,6 +59,17 @@ struct ArgReps {
     Rep rep[kArgReps];
 };
 
+// How a box is cut in x: ntx pieces of `width` core sites with `halo` sites per side.
+struct RowsCut {
+    int ntx, width, halo;
+};
+__host__ __device__ inline RowsCut rows_cut(int Lx, int P, int K)
+{
+    if (Lx == 64 * P) return {1, Lx, 0};   // the whole periodic row in the wavefront
+    const int most = 64 - 2 * K, ntx = (Lx + most - 1) / most;   // P = 1
+    return {ntx, (Lx + ntx - 1) / ntx, K};
+}
+
 // Launch plan of a site kernel: each block covers span (kBlock, or a multiple of it in the
 // kernels that loop) consecutive sites of one replica.
 struct Plan {
@@ -134,7 +145,17 @@ void launch_solvent(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, 
                     double *out);
 
 // dynamics
-void launch_mu(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi,
+// Column plans of the chemical-potential and convection-diffusion kernels: a wavefront takes
+// a row piece (rows_cut with K = 1 and P sites per lane) of kMuZ or kCdZ planes, a block
+// kColY rows.  The convection-diffusion kernel holds more arrays per plane: at 4 planes its
+// registers leave one wavefront per SIMD.
+constexpr int kColY = 4, kMuZ = 4, kCdZ = 2;
+inline long long col_blocks(int P, int CZ, int Lx, int Ly, int Lz)
+{
+    return (long long)rows_cut(Lx, P, 1).ntx * ((Ly + kColY - 1) / kColY) * ((Lz + CZ - 1) / CZ);
+}
+// p: the column plan, P its sites per lane
+void launch_mu(hipStream_t s, const Plan &p, int P, const Rep *rep, Chain ch, const double *phi,
                const double *w, double *mu);
 void launch_force(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi,
                   const double *mu, double *f);
@@ -151,7 +172,8 @@ void launch_lb_convert(hipStream_t s, const Plan &p, const Rep *rep, bool to_f32
 // not finite (so that a coupled step can be rolled back)
 // noise_flux: scratch for the composition noise's bond fluxes (3 nsp T doubles), or null
 // for no noise; diff_scale multiplies dt in the diffusive flux (1/2 in the CN step)
-void launch_cd(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi,
+// p: the column plan with P sites per lane; ps: the site plan (of the noise draw)
+void launch_cd(hipStream_t s, const Plan &p, int P, const Plan &ps, const Rep *rep, Chain ch, const double *phi,
                const double *mu, const double *u, double *phi_out, double *noise_flux, unsigned long long step,
                hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, double diff_scale = 1.0, int *bad = nullptr);
 void launch_lb_rest(hipStream_t s, const Plan &p, const Rep *rep, void *n, bool f32);

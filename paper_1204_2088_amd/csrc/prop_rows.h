@@ -33,17 +33,6 @@ constexpr bool rows_fp64(int cx, int cy, int cz, int k)
 constexpr int rows_waves(size_t rs, int P, int K, int CZ) { return rs == 4 && P == 2 && K == 2 && CZ == 4 ? 6 : 1; }
 inline bool rows_fp64(const TileCfg &t) { return rows_fp64(t.cx, t.cy, t.cz, -t.k); }
 
-// How a box is cut in x: ntx pieces of `width` core sites with `halo` sites per side.
-struct RowsCut {
-    int ntx, width, halo;
-};
-__host__ __device__ inline RowsCut rows_cut(int Lx, int P, int K)
-{
-    if (Lx == 64 * P) return {1, Lx, 0};   // the whole periodic row in the wavefront
-    const int most = 64 - 2 * K, ntx = (Lx + most - 1) / most;   // P = 1
-    return {ntx, (Lx + ntx - 1) / ntx, K};
-}
-
 inline long long rows_blocks(const TileCfg &t, int Lx, int Ly, int Lz)
 {
     return (long long)rows_cut(Lx, t.cx / 64, -t.k).ntx * ((Ly + t.cy - 1) / t.cy) * ((Lz + t.cz - 1) / t.cz);

@@ -31,36 +31,6 @@
 
 namespace hsf {
 
-// Value of the neighbouring lane, the wavefront taken as a ring (wave_ror:1 / wave_rol:1).
-__device__ __forceinline__ float ring_left(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x13c, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float ring_right(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x134, 0xf, 0xf, true));
-}
-__device__ __forceinline__ double ring_left(double v)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x13c, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x13c, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double ring_right(double v)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x134, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x134, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-
-// P consecutive sites of a row.
-template <typename real, int P>
-struct Sites {
-    real s[P];
-};
-
 // Global memory through buffer descriptors: a uniform base and byte offset (scalar
 // registers) plus the lane's own offset, so a row costs one instruction and no address
 // arithmetic, and a lane whose offset lies past the end (kOutside) reads zero and stores
@@ -98,18 +68,6 @@ __device__ __forceinline__ void buf_store(buf_t b, unsigned lane_off, int off, c
         // with the overwritten values now and then), so the offset goes through the lane's.
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4, v), b, lane_off + (unsigned)off, 0, 0);
     }
-}
-
-// x neighbours' sum of each of the lane's sites.
-template <typename real>
-__device__ __forceinline__ Sites<real, 1> x_sums(const Sites<real, 1> &v)
-{
-    return {{ring_left(v.s[0]) + ring_right(v.s[0])}};
-}
-template <typename real>
-__device__ __forceinline__ Sites<real, 2> x_sums(const Sites<real, 2> &v)
-{
-    return {{ring_left(v.s[1]) + v.s[1], v.s[0] + ring_right(v.s[0])}};
 }
 
 // The tile of a workgroup and the wavefront's part of it.  All but the lane offsets is
