@@ -405,6 +405,11 @@ int hsf_get_work(hsf_ctx *ctx, long long *evals, double *site_evals, int reset);
  * 128 sites in x only, cx = 128 sites of a row per wavefront, cy x cz rows per workgroup;
  * densities those of k = 0 up to the summation order of Q; not for boxes above 2^28 sites
  * per replica, and the largest ones in FP32 contexts only).
+ * Contexts whose replicas are all at most 16 sites in each direction start with resident
+ * sweeps instead, where the LDS holds them: one workgroup per replica runs a whole evaluation,
+ * or the iterations of an inversion, in one launch (timed as HSF_K_PAIR; densities those of
+ * k = 0 up to the summation order of Q).  hsf_set_tile and HSF_TILE switch them off,
+ * hsf_autotune switches them on again, and a saved state keeps the choice.
  * hsf_set_tile accepts only the configurations compiled into the library
  * (HSF_EINVAL otherwise); results do not depend on the choice beyond rounding.
  * hsf_autotune times one density-functional evaluation `reps` times with every
@@ -515,7 +520,7 @@ enum {
     HSF_K_BWD = 2,    /* backward propagator step + density accumulation */
     HSF_K_LB = 3,     /* fused LB collide-and-stream                     */
     HSF_K_CD = 4,     /* convection-diffusion update                     */
-    HSF_K_PAIR = 5,   /* paired launch: one forward and one backward step */
+    HSF_K_PAIR = 5,   /* paired launch: forward and backward steps (hsf_set_tile) */
     HSF_K_COUNT = 6
 };
 

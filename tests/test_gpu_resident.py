@@ -1,0 +1,151 @@
+"""Evaluations and inversions of small boxes in one workgroup per replica, the default there,
+against the one-step kernels (an explicit tiling) and the FP64 oracle.
+
+The two paths store the same expressions of the same operands; sums over sites differ in
+order only (at most 4096 terms in trees about 100 deep: 2 * 100 * 2^-53 < 5e-14 relative on Q and
+the densities, in FP32 contexts too).
+"""
+import numpy as np
+import pytest
+
+from paper_1204_2088_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SAME = 5e-14
+
+
+@pytest.fixture(scope="module")
+def hsf():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1204_2088_amd import hsf as H
+    H.load()
+    return H
+
+
+def workload(L, types, precision, solvent=False, seed=3):
+    N = len(types)
+    return W.Workload("resident", L, types, solvent, W.chi_matrix(ab=15 / N, bs=10 / N if solvent else 0.0), tau=1.0,
+                      noise=0.02 if solvent else 0.2, seed=seed, phi_p=0.3 if solvent else 1.0, precision=precision)
+
+
+def fields(wl, seed, amp=1.0):
+    return W.random_fields((wl.nsp,) + wl.shape, seed=seed, amplitude=amp, smooth=1)
+
+
+def rel(a, b):
+    return np.max(np.abs(a - b)) / np.max(np.abs(b))
+
+
+# the largest box, rows and planes that do not fill the layout, one to four planes in the last
+# column, boxes that wrap onto themselves, single-bead species, the longest chain
+CASES = [((16, 16, 16), W.chain(4, 4), False), ((16, 16, 16), W.chain(3, 9), True), ((16, 15, 13), W.chain(3, 4), False),
+         ((15, 16, 4), W.chain(2, 3), False), ((5, 3, 9), W.chain(2, 3), True), ((1, 1, 2), W.chain(1, 1), False),
+         ((3, 1, 1), W.chain(1, 0), False), ((12, 11, 10), W.chain(5, 59), False), ((13, 14, 15), W.chain(4, 4), False),
+         ((7, 8, 8), W.chain(3, 5), False)]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("L,types,solvent", CASES)
+def test_resident_evaluation(hsf, orc, precision, L, types, solvent):
+    wl = workload(L, types, precision, solvent)
+    w = fields(wl, 5)
+    phi = W.initial_composition(wl) if len(types) > 1 else np.stack([np.ones(wl.shape), np.zeros(wl.shape)])
+    out = []
+    for explicit in (False, True):
+        ctx = hsf.Context(wl)
+        if explicit:
+            ctx.set_tile((32, 8, 2, 0))
+        ctx.set_densities(phi.ravel())
+        ctx.set_fields(w.ravel())
+        ctx.evaluate()
+        out.append(ctx.evaluate())
+        out[-1] += (ctx.observables()[0],)
+        ctx.close()
+    (a, qa, fa), (b, qb, fb) = out
+    sysw = orc.System(L=wl.L, types=wl.types, has_solvent=wl.has_solvent, a=wl.a, chi=wl.chi, kappa=wl.kappa, dt=wl.dt,
+                      tau=wl.tau)
+    ref, qref = orc.evaluate(sysw, w, phi[:2].sum(0).mean(), phi[2].mean() if solvent else 0.0)
+    print(f"[resident] {L} N={len(types)} {precision}: {rel(a, b):.2e} from one step", flush=True)
+    assert rel(a, b) <= SAME and abs(qa[0] / qb[0] - 1) <= SAME
+    assert abs(fa[0] - fb[0]) < 1e-11 * (1 + abs(fb[0]))
+    tol = 1e-10 if precision == "fp64" else 1e-5
+    assert rel(a, ref.ravel()) < tol and abs(qa[0] / qref - 1) < tol
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("precond", [False, True])
+def test_resident_inversion(hsf, precision, precond):
+    """Uneven replicas, each with its own line search, plain and preconditioned, refined below
+    1e-5 in FP32 contexts: the residual is reached, the fields are those of the one-step path
+    (both are within the tolerance of the solution), the counts differ by rounding only, and a
+    limit on the iterations stops both alike."""
+    boxes = [(16, 16, 16), (9, 7, 5), (12, 6, 10)]
+    wls = [workload(L, W.chain(3, 5), precision, True, seed=r) for r, L in enumerate(boxes)]
+    phi = np.concatenate([W.initial_composition(wl).ravel() for wl in wls])
+    out = []
+    for explicit in (False, True):
+        ctx = hsf.Context(wls)
+        if explicit:
+            ctx.set_tile((32, 8, 2, 0))
+        ctx.set_solver(precond=precond, refine=True)
+        ctx.set_densities(phi)
+        st, _ = ctx.invert(tol=1e-9, max_iter=3000, warm=hsf.WARM_LOCAL)
+        w = ctx.get_fields()
+        new, _ = ctx.evaluate()
+        ctx.set_fields(np.zeros_like(w))
+        few, rc = ctx.invert(tol=1e-9, max_iter=3, allow_noconv=True)
+        assert rc == hsf.HSF_ENOCONV and all(s["iterations"] in (3, 6) for s in few)
+        out.append((st, w, new, few))
+        ctx.close()
+    (sa, wa, na, fa), (sb, wb, nb, fb) = out
+    assert all(s["converged"] and s["residual"] <= 1e-9 for s in sa + sb)
+    assert np.max(np.abs(wa - wb)) < 1e-6 * np.max(np.abs(wb))
+    assert all(abs(a["iterations"] - b["iterations"]) <= 3 + 0.1 * b["iterations"] for a, b in zip(sa, sb))
+    assert all(abs(a["residual"] / b["residual"] - 1) < 1e-3 for a, b in zip(fa, fb))
+
+
+def test_resident_many_passes_and_nonfinite(hsf):
+    """An inversion of more passes than one launch takes; a NaN field in one replica leaves the
+    others' results as they are without it."""
+    wls = [workload((8, 8, 8), W.chain(3, 5), "fp64", True, seed=r) for r in range(3)]
+    phi = np.concatenate([W.initial_composition(wl).ravel() for wl in wls])
+    ctx = hsf.Context(wls)
+    ctx.set_densities(phi)
+    st, _ = ctx.invert(tol=0.0, max_iter=200, warm=hsf.WARM_LOCAL, allow_noconv=True)
+    assert max(s["evaluations"] for s in st) > 129
+    w = ctx.get_fields()
+    ref, q = ctx.evaluate()
+    bad = w.copy()
+    fo = ctx.field_offset(1)
+    bad[fo + 5] = np.nan
+    ctx.set_fields(bad)
+    out = np.zeros_like(ref)
+    with pytest.raises(hsf.HsfError) as e:
+        ctx.evaluate(out)
+    assert e.value.code == hsf.HSF_ENONFINITE
+    n = 3 * wls[0].V
+    assert np.array_equal(out[:n], ref[:n]) and np.array_equal(out[2 * n:], ref[2 * n:])
+    ctx.close()
+
+
+def test_resident_state_round_trip(hsf):
+    """A run continued from a checkpoint repeats bit for bit, with the path it was written with."""
+    wl = workload((12, 12, 12), W.chain(4, 4), "fp32")
+    for tile in (None, (32, 8, 2, -1)):
+        ctx = hsf.Context(wl)
+        if tile:
+            ctx.set_tile(tile)
+        ctx.set_densities(W.initial_composition(wl).ravel())
+        ctx.step(2, tol=1e-5)
+        buf = ctx.get_state()
+        ctx.step(3, tol=1e-5)
+        ctx2 = hsf.Context(wl)
+        ctx2.set_state(buf)
+        ctx2.step(3, tol=1e-5)
+        assert np.array_equal(ctx.get_densities(), ctx2.get_densities())
+        assert np.array_equal(ctx.get_fields(), ctx2.get_fields())
+        ctx.close()
+        ctx2.close()
