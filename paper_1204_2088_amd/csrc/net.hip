@@ -35,6 +35,7 @@ constexpr int kMaxLevels = 4;
 // auxiliary device scratch of a network: 4096 partial sums, then results
 constexpr int kAuxParts = 4096, kAuxDoubles = kAuxParts + 8 + 2 * 64 + 64;
 constexpr int kLayers = 4 * kMaxLevels - 1;   // the most convolutions a network has
+static_assert(kLayers == kNetMaxLayers, "the sums of the weight gradients take every layer");
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
@@ -49,7 +50,6 @@ struct Layer {
     // every layer that reads it reads it plainly
     int pack = 0;
     __bf16 *Wm = nullptr, *Wt = nullptr;
-    float *dWm = nullptr;            // weight gradient, matrix-core layout
 };
 
 struct Tensor {
@@ -76,10 +76,11 @@ struct hsf_net {
     int cur_B = 0, cur_L = 0;
     std::vector<void *> act_allocs;
     Tensor x0, y[kLayers], a[kLayers];
-    Tensor dy[kLayers], da[kLayers], dout;
+    Tensor dy[kLayers];              // gradients of the pre-activations (of the activations while summed)
+    WgradSums wsums;                 // layout of wpart and bpart
     float *din = nullptr;            // gradient of one convolution's (composed) input
     float *target = nullptr, *wpart = nullptr;
-    double *bpart = nullptr;         // per-channel partial sums of the bias gradient
+    double *bpart = nullptr;         // partial sums of the bias gradients
     double *loss_part = nullptr;
     double *aux = nullptr;           // sample assembly and channel moments: partials, rms, results
     int weights_staged = 0;
@@ -127,23 +128,17 @@ void free_acts(hsf_net *n)
     n->cur_B = n->cur_L = 0;
     // forget every pointer into the freed buffers (a later allocation without the
     // gradient tensors must not find stale ones)
-    n->x0 = n->dout = Tensor();
-    for (int l = 0; l < kLayers; ++l) n->y[l] = n->a[l] = n->dy[l] = n->da[l] = Tensor();
+    n->x0 = Tensor();
+    for (int l = 0; l < kLayers; ++l) n->y[l] = n->a[l] = n->dy[l] = Tensor();
     n->din = n->target = n->wpart = nullptr;
     n->bpart = nullptr;
     n->loss_part = nullptr;
 }
 
-// Elements of a layer's (composed) input for the current batch.
-long long input_numel(const hsf_net *n, const Layer &Ly)
-{
-    return (long long)n->cur_B * Ly.ci * vol(n->cur_L, Ly.level);
-}
-
 // (Re)allocate the activation and gradient tensors for batch B on an L^3 box.
 int ensure_acts(hsf_net *n, int B, int L, bool grads)
 {
-    if (n->cur_B == B && n->cur_L == L && (!grads || n->dout.p)) return HSF_OK;
+    if (n->cur_B == B && n->cur_L == L && (!grads || n->din)) return HSF_OK;
     free_acts(n);
     int rc = HSF_OK;
     auto T = [&](Tensor &t, int c, int level) {
@@ -166,21 +161,23 @@ int ensure_acts(hsf_net *n, int B, int L, bool grads)
         }
     }
     if (grads) {
-        size_t din = 0, wp = 0;
+        size_t din = 0, wp = 0, bp = 0;
+        n->wsums.n = n->n_layers;
         for (int l = 0; l < n->n_layers; ++l) {
             const Layer &Ly = n->layer[l];
             T(n->dy[l], Ly.co, Ly.level);
-            if (Ly.act) T(n->da[l], Ly.co, Ly.level);
             din = std::max(din, (size_t)((long long)B * Ly.ci * vol(L, Ly.level)));
-            wp = std::max(wp, (size_t)net_wgrad_slices(B, L >> Ly.level, Ly.cop, Ly.kp) * Ly.cop * Ly.kp);
+            const int slices = net_wgrad_slices(B, L >> Ly.level, Ly.ci);
+            n->wsums.l[l] = WgradSum{(long long)wp, (long long)bp, Ly.w_off, Ly.b_off, Ly.ci, Ly.co, slices, 0};
+            wp += (size_t)net_wgrad_part(slices, Ly.ci, Ly.co);
+            bp += (size_t)slices * Ly.co;
         }
-        T(n->dout, n->out_ch, 0);
         if (rc == HSF_OK) rc = nalloc(n, n->act_allocs, (void **)&n->din, sizeof(float) * din);
         if (rc == HSF_OK)
             rc = nalloc(n, n->act_allocs, (void **)&n->target, sizeof(float) * (size_t)B * n->out_ch * vol(L, 0));
         if (rc == HSF_OK) rc = nalloc(n, n->act_allocs, (void **)&n->wpart, sizeof(float) * wp);
         if (rc == HSF_OK)
-            rc = nalloc(n, n->act_allocs, (void **)&n->bpart, sizeof(double) * net_channel_parts(kNetMaxWidth));
+            rc = nalloc(n, n->act_allocs, (void **)&n->bpart, sizeof(double) * bp);
         const size_t lb = ((size_t)B * n->out_ch * vol(L, 0) + 255) / 256;
         if (rc == HSF_OK) rc = nalloc(n, n->act_allocs, (void **)&n->loss_part, sizeof(double) * lb);
     }
@@ -281,50 +278,61 @@ int forward_infer(hsf_net *n, const float *x, float *y)
     return HSF_OK;
 }
 
-// Backward pass from dout (gradient of the loss with respect to the output).  Layers
-// are visited from the last; every consumer of an activation comes after it, so
-// da[j] is complete when layer j is reached.  dgrad writes the gradient of a layer's
-// composed input into din, which is then distributed to the activations it read.
+// Backward pass from the gradient of the loss with respect to the output (dy of the last
+// layer).  Layers are visited from the last; every consumer of an activation comes after it, so
+// dy[j] is complete when layer j is reached.  The data gradient of a layer's composed input
+// goes to the activations it read: from the convolution's epilogue, or through din where the
+// input was pooled or upsampled; an activation's last contribution also applies the
+// derivative of its SiLU.
 void backward(hsf_net *n)
 {
     hipStream_t s = n->stream;
     const int B = n->cur_B, L = n->cur_L;
+    int left[kLayers] = {0};   // contributions to come
     bool have[kLayers] = {false};
+    for (int l = 0; l < n->n_layers; ++l) {
+        const Layer &Ly = n->layer[l];
+        if (Ly.src1 >= 0) ++left[Ly.src1];
+        if (Ly.src1 >= 0 && Ly.in_mode == CONV_IN_ADD) ++left[Ly.src2];
+    }
+    auto give = [&](int j) {
+        ConvGive t;
+        t.dst = n->dy[j].p;
+        t.add = have[j] ? 1 : 0;
+        have[j] = true;
+        if (--left[j] == 0) t.Y = n->y[j].p;
+        return t;
+    };
     for (int l = n->n_layers - 1; l >= 0; --l) {
         const Layer &Ly = n->layer[l];
         const int Ll = L >> Ly.level;
-        const long long V = vol(L, Ly.level);
-        if (Ly.act) {
-            net_silu_bwd(s, n->da[l].p, n->y[l].p, n->dy[l].p, numel(n, n->dy[l]));
-        } else {
-            (void)hipMemcpyAsync(n->dy[l].p, n->dout.p, sizeof(float) * numel(n, n->dout), hipMemcpyDeviceToDevice,
-                                 s);
-        }
-        net_conv_wgrad(s, conv_input(n, Ly), B, Ly.ci, Ly.cip, n->dy[l].p, Ly.co, Ly.cop, Ly.kp, Ll, n->wpart,
-                       Ly.dWm);
-        net_unstage_grad(s, Ly.dWm, Ly.co, Ly.ci, Ly.cip, Ly.kp, n->grad + Ly.w_off);
-        net_channel_sum(s, n->dy[l].p, B, Ly.co, V, n->bpart, n->grad + Ly.b_off);
         if (Ly.src1 < 0) continue;   // the network input needs no gradient
+        const bool direct = Ly.in_mode != CONV_IN_UP && Ly.in_mode != CONV_IN_POOL;
+        const ConvGive to = give(Ly.src1);
         ConvIn g;
         g.x1 = n->dy[l].p;
         ConvOut gout;
-        gout.Y = n->din;
+        if (direct) gout.give[0] = to;
+        else gout.Y = n->din;
+        if (Ly.in_mode == CONV_IN_ADD) gout.give[1] = give(Ly.src2);
         net_conv_fwd(s, g, B, Ly.co, Ly.cip_t, Ly.Wt, Ly.kp_t, Ly.ci, Ly.cop_t, nullptr, gout, Ll);
-        const long long nin = input_numel(n, Ly);
-        auto give = [&](int j) {   // da[j] (+)= din through the input's composition
-            float *dst = n->da[j].p;
-            const int add = have[j] ? 1 : 0;
-            if (Ly.in_mode == CONV_IN_UP)
-                net_up_bwd(s, n->din, dst, Ll, numel(n, n->da[j]), add);
-            else if (Ly.in_mode == CONV_IN_POOL)
-                net_pool_bwd(s, n->din, dst, L >> n->layer[j].level, numel(n, n->da[j]), add);
-            else
-                net_accum(s, dst, n->din, nin, add);
-            have[j] = true;
-        };
-        give(Ly.src1);
-        if (Ly.in_mode == CONV_IN_ADD) give(Ly.src2);
+        if (Ly.in_mode == CONV_IN_UP) net_up_bwd(s, n->din, to, Ll, numel(n, n->dy[Ly.src1]));
+        if (Ly.in_mode == CONV_IN_POOL)
+            net_pool_bwd(s, n->din, to, L >> n->layer[Ly.src1].level, numel(n, n->dy[Ly.src1]));
     }
+    for (int lev = 0; lev < n->depth; ++lev) {   // every dy stands: a level's layers in one launch
+        WgradJobs W;
+        W.n = 0;
+        for (int l = 0; l < n->n_layers; ++l) {
+            const Layer &Ly = n->layer[l];
+            const WgradSum &ws = n->wsums.l[l];
+            if (Ly.level == lev)
+                W.j[W.n++] = WgradJob{conv_input(n, Ly), n->dy[l].p, n->wpart + ws.part, n->bpart + ws.bpart,
+                                      Ly.ci,             Ly.co,      ws.slices,          0};
+        }
+        net_conv_wgrad(s, W, B, L >> lev);
+    }
+    net_wgrad_sum(s, n->wsums, n->wpart, n->bpart, n->grad);
 }
 
 int copy_f32(hsf_net *n, float *dst, const float *src, size_t count, int where, hipMemcpyKind host_kind)
@@ -361,8 +369,8 @@ int loss_and_grad(hsf_net *n, double *loss)
     n->training = 1;
     forward_train(n);
     n->training = 0;
-    const long long cnt = numel(n, n->dout);
-    const int blocks = net_mse(n->stream, output(n).p, n->target, n->dout.p, cnt, 1.0f / (float)cnt, n->loss_part);
+    const long long cnt = numel(n, output(n));
+    const int blocks = net_mse(n->stream, output(n).p, n->target, n->dy[n->n_layers - 1].p, cnt, 1.0f / (float)cnt, n->loss_part);
     backward(n);
     NCHK(n, hipGetLastError());
     std::vector<double> lp(blocks);
@@ -467,7 +475,6 @@ int hsf_net_create(int in_ch, int out_ch, const int widths[4], unsigned long lon
         Layer &Ly = n->layer[l];
         rc = nalloc(n, n->allocs, (void **)&Ly.Wm, sizeof(__bf16) * (size_t)Ly.cop * Ly.kp);
         if (rc == HSF_OK) rc = nalloc(n, n->allocs, (void **)&Ly.Wt, sizeof(__bf16) * (size_t)Ly.cop_t * Ly.kp_t);
-        if (rc == HSF_OK) rc = nalloc(n, n->allocs, (void **)&Ly.dWm, sizeof(float) * (size_t)Ly.cop * Ly.kp);
     }
     if (rc != HSF_OK) {
         hsf_net_destroy(n);

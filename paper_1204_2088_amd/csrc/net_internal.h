@@ -30,29 +30,59 @@ struct ConvIn {
 //   A   FP32 [batch][co][site]  silu(acc + bias)
 //   Ap  BF16 [batch][site][cp]  silu(acc + bias) rounded to BF16, cp = co rounded up to
 //       8, channels co..cp-1 written as zero (the CONV_IN_PACKED input of the next layer)
+//   give  the backward pass: acc is added to (add) or stored as the gradient of up to two
+//       activations of the layer's box; see ConvGive
+struct ConvGive {
+    float *dst = nullptr;
+    const float *Y = nullptr;   // set for the last contribution: the pre-activation, whose gradient
+                                // (the sum times silu'(Y)) is stored instead of the sum
+    int add = 0;
+};
 struct ConvOut {
     float *Y = nullptr, *A = nullptr;
     __bf16 *Ap = nullptr;
     const float *shift = nullptr, *scale = nullptr;
+    ConvGive give[2];
+};
+
+// Weight gradients: net_conv_wgrad leaves the partial sums per slice of the layers of one level
+// (box L) in part and bpart, net_wgrad_sum adds those of all layers into the parameter
+// vector's layout.  block0 is set by the launchers.
+struct WgradJob {
+    ConvIn in;
+    const float *dY;
+    float *part;
+    double *bpart;
+    int ci, co, slices, block0;
+};
+struct WgradJobs {
+    WgradJob j[5];   // a level's layers: two of the encoder, two of the decoder, the output
+    int n;
+};
+constexpr int kNetMaxLayers = 15;
+struct WgradSum {
+    long long part, bpart;      // offsets of the layer's partials
+    long long w_off, b_off;     // offsets in the gradient vector
+    int ci, co, slices, block0;
+};
+struct WgradSums {
+    WgradSum l[kNetMaxLayers];
+    int n;
 };
 
 void net_conv_fwd(hipStream_t s, ConvIn in, int B, int ci, int cip, const __bf16 *Wm, int kp, int co, int cop,
                   const float *bias, ConvOut out, int L);
-int net_wgrad_slices(int B, int L, int cop, int kp);
-void net_conv_wgrad(hipStream_t s, ConvIn in, int B, int ci, int cip, const float *dY, int co, int cop, int kp,
-                    int L, float *part, float *dWm);
-void net_silu_bwd(hipStream_t s, const float *dA, const float *Y, float *dY, long long n);
-void net_pool_bwd(hipStream_t s, const float *dout, float *din, int L, long long n_in, int add);
-void net_up_bwd(hipStream_t s, const float *dout, float *din, int L, long long n_in, int add);
-void net_accum(hipStream_t s, float *dst, const float *src, long long n, int add);
-int net_channel_parts(int C);
-void net_channel_sum(hipStream_t s, const float *g, int B, int C, long long V, double *part, float *out);
+int net_wgrad_slices(int B, int L, int ci);
+long long net_wgrad_part(int slices, int ci, int co);   // floats of a layer's partials
+void net_conv_wgrad(hipStream_t s, WgradJobs &W, int B, int L);
+void net_wgrad_sum(hipStream_t s, WgradSums &W, const float *part, const double *bpart, float *grad);
+void net_pool_bwd(hipStream_t s, const float *dout, const ConvGive &to, int L, long long n_in);
+void net_up_bwd(hipStream_t s, const float *dout, const ConvGive &to, int L, long long n_in);
 int net_mse(hipStream_t s, const float *p, const float *t, float *dp, long long n, float inv_count, double *part);
 void net_adam(hipStream_t s, float *w, const float *g, float *m, float *v, long long n, float lr, float b1, float b2,
               float eps, float c1, float c2);
 void net_stage_weights(hipStream_t s, const float *W, int co, int ci, int cip, int kp, int cop_rows, __bf16 *Wm,
                        int cip_t, int kp_t, int cop_rows_t, __bf16 *Wt);
-void net_unstage_grad(hipStream_t s, const float *dWm, int co, int ci, int cip, int kp, float *dW);
 // Warm start from the network.  mode 0: input phi; 1: (h0, (phi - h0) / rms);
 // 2: (h0, (phi - 2 h0 + h1) / rms), rms computed on the device into *rms.
 void net_warm_input(hipStream_t s, const double *phi, const double *h0, const double *h1, int nsp, long long V,

@@ -16,6 +16,8 @@
 #include <algorithm>
 #include <math.h>
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "net_internal.h"
 
@@ -38,6 +40,14 @@ __device__ __forceinline__ float silu_grad(float y)
     return s * (1.0f + y * (1.0f - s));
 }
 
+// Adds a contribution g to the gradient of element e of an activation; the last one turns the
+// sum into the gradient of the pre-activation.
+__device__ __forceinline__ void give_gradient(const ConvGive &t, long long e, float g)
+{
+    const float v = t.add ? t.dst[e] + g : g;
+    t.dst[e] = t.Y ? v * silu_grad(t.Y[e]) : v;
+}
+
 // ---------------------------------------------------------------- forward convolution
 // Y[b][co][x] = bias[co] + sum_{ci,k} W[co][ci][k] X[b][ci][x + off_k], written as
 // ConvOut asks (pre-activation, FP32 activation, packed BF16 activation).  The input
@@ -50,9 +60,6 @@ __device__ __forceinline__ float silu_grad(float y)
 // banks), so the K loop reads only LDS; the next slab's loads are in flight while the
 // current one is multiplied.  Small slabs keep a 16x8x4 block of a 16-channel layer
 // under 40 KB of LDS, four blocks per CU.
-// The weight gradient works on TX x TY x TZ tiles (128 sites) staged channel-major.
-constexpr int TX = 8, TY = 4, TZ = 4, TS = TX * TY * TZ;
-constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2, HS = HX * HY * HZ;
 constexpr int kSlab = 4;
 constexpr int kSlabRow = kSlab * 32 + 8;
 
@@ -92,46 +99,60 @@ __device__ __forceinline__ float conv_input(const ConvIn &in, int b, int c, int 
     return in.mode == CONV_IN_ADD ? in.x1[e] + in.x2[e] : in.x1[e];
 }
 
-// Input rows of a TX x TY x TZ tile for the weight gradient, in LDS as BF16 in three
-// x-shifted copies: xr[d][c][hz][hy][8] holds, for d = dx + 1, the input at x = x0 +
-// dx + 0..7 of halo row (hy, hz) and channel c (channels ci..cip-1 zero; the channel
-// pitch kWgChan pads 6 x 6 x 8 by 8 so the 16 lanes of a B operand read, 16 channels of
-// one row, fall on distinct banks).  Every B operand of the K loop (8 consecutive
-// sites of one channel at one tap) is then one aligned 16-byte read.
-constexpr int kWgRows = (TZ + 2) * (TY + 2);   // halo rows of a tile
-constexpr int kWgChan = kWgRows * TX + 8;      // channel pitch of a copy (elements)
-constexpr int kWgYPitch = TS + 8;               // row pitch of the staged dY tile (odd in 16-byte units)
-__device__ __forceinline__ void stage_rows3(const ConvIn &in, int b, int ci, int cip, int L, int x0, int y0, int z0,
-                                            __bf16 *xr)
+typedef float floatv4 __attribute__((ext_vector_type(4)));
+typedef float floatv2 __attribute__((ext_vector_type(2)));
+
+// The same in parts, for loops over channels: element conv_offset of a channel's data, channels
+// conv_stride apart, is read for site (x, y, z); conv_load1 and conv_load4 (sites x .. x + 3 of a
+// row, x and L multiples of 4, in wide loads) give the input's values from there.
+template <int MODE>
+__device__ __forceinline__ long long conv_stride(int L)
 {
-    // a work item is one value (halo position q of a row; consecutive items are
-    // consecutive x, so a wave's loads are contiguous), stored into each copy that holds
-    // it; eight values per thread in flight at once
-    const bool small = L < TX;
-    const int total = cip * kWgRows * (TX + 2);
-    for (int e0 = threadIdx.x; e0 < total; e0 += 256 * 8) {
-        float v[8];
+    const long long n = MODE == CONV_IN_UP ? L >> 1 : MODE == CONV_IN_POOL ? L << 1 : L;
+    return n * n * n;
+}
+template <int MODE>
+__device__ __forceinline__ long long conv_offset(int x, int y, int z, int L)
+{
+    if constexpr (MODE == CONV_IN_UP) return (x >> 1) + (long long)(L >> 1) * ((y >> 1) + (L >> 1) * (z >> 1));
+    if constexpr (MODE == CONV_IN_POOL) return 2 * x + (long long)(L << 1) * (2 * y + (L << 1) * (2 * z));
+    return x + (long long)L * (y + L * z);
+}
+template <int MODE>
+__device__ __forceinline__ float conv_load1(const ConvIn &in, long long e, int L)
+{
+    if constexpr (MODE == CONV_IN_POOL) {
+        const int f = L << 1;
+        float s = 0.0f;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * 256;
-            const int q = e % (TX + 2), r = e / (TX + 2), c = r / kWgRows, row = r % kWgRows;
-            const int hz = row / HY, hy = row % HY;
-            v[u] = 0.0f;
-            if (e < total && c < ci)
-                v[u] = conv_input(in, b, c, ci, wrap_tile(x0 + q - 1, L, small), wrap_tile(y0 + hy - 1, L, small),
-                                  wrap_tile(z0 + hz - 1, L, small), L);
+        for (int q = 0; q < 8; ++q) s += in.x1[e + (q & 1) + (long long)f * (((q >> 1) & 1) + (long long)f * (q >> 2))];
+        return 0.125f * s;
+    }
+    return MODE == CONV_IN_ADD ? in.x1[e] + in.x2[e] : in.x1[e];
+}
+template <int MODE>
+__device__ __forceinline__ floatv4 conv_load4(const ConvIn &in, long long e, int L)
+{
+    if constexpr (MODE == CONV_IN_UP) {
+        const floatv2 v = *reinterpret_cast<const floatv2 *>(in.x1 + e);
+        return floatv4{v.x, v.x, v.y, v.y};
+    } else if constexpr (MODE == CONV_IN_POOL) {
+        const int f = L << 1;
+        floatv4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // (dz, dy) = (q / 2, q % 2)
+            const float *r = in.x1 + e + ((long long)(q >> 1) * f + (q & 1)) * f;
+            const floatv4 u = *reinterpret_cast<const floatv4 *>(r), v = *reinterpret_cast<const floatv4 *>(r + 4);
+            s[0] = (s[0] + u[0]) + u[1];
+            s[1] = (s[1] + u[2]) + u[3];
+            s[2] = (s[2] + v[0]) + v[1];
+            s[3] = (s[3] + v[2]) + v[3];
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + u * 256;
-            if (e >= total) continue;
-            const int q = e % (TX + 2), r = e / (TX + 2), c = r / kWgRows, row = r % kWgRows;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int x = q - d;   // position of this value in copy d
-                if (x >= 0 && x < TX) xr[(d * cip + c) * kWgChan + row * TX + x] = (__bf16)v[u];
-            }
-        }
+        return 0.125f * s;
+    } else {
+        floatv4 v = *reinterpret_cast<const floatv4 *>(in.x1 + e);
+        if constexpr (MODE == CONV_IN_ADD) v += *reinterpret_cast<const floatv4 *>(in.x2 + e);
+        return v;
     }
 }
 
@@ -179,22 +200,23 @@ __device__ __forceinline__ void stage_halo_sm(const ConvIn &in, int b, int ci, i
     }
 }
 
-// Row-vector staging of the same tile: aligned float4 loads of 4 consecutive x sites
-// per channel, for plain and summed inputs on boxes at least a tile wide with L a
-// multiple of 4 (three times fewer load instructions than one site per load).
-typedef float floatv4 __attribute__((ext_vector_type(4)));
-template <int BX, int BY, int BZ>
+// Row-vector staging of the same tile: four consecutive x sites per channel in aligned wide
+// loads, on boxes at least a tile wide with L a multiple of 4 (three times fewer load
+// instructions than one site per load; of an upsampled input 41 -> 32 us at 64^3, batch
+// 2, 16 -> 8 channels; of a pooled one 21 -> 15 at 32^3, 8 -> 16).
+template <int BX, int BY, int BZ, int MODE>
 __device__ __forceinline__ void stage_halo_rows(const ConvIn &in, int b, int ci, int cip, int L, int x0, int y0,
                                                 int z0, __bf16 *xs)
 {
     constexpr int GX = BX + 2, GY = BY + 2, GZ = BZ + 2, GS = GX * GY * GZ;
     constexpr int NG = (BX + 8) / 4;   // float4 groups covering x in [x0 - 4, x0 + BX + 4)
+    constexpr int U = MODE == CONV_IN_POOL ? 1 : 2;
     const int oct = cip / 8, total = GY * GZ * NG * oct;
-    const long long V = (long long)L * L * L;
-    for (int e0 = threadIdx.x; e0 < total; e0 += 256 * 2) {
-        floatv4 v[2][8];
+    const long long stride = conv_stride<MODE>(L), base = (long long)b * ci * stride;
+    for (int e0 = threadIdx.x; e0 < total; e0 += 256 * U) {
+        floatv4 v[U][8];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int e = e0 + u * 256;
             const bool ok = e < total;
             const int c8 = e % oct, r = e / oct;
@@ -203,21 +225,19 @@ __device__ __forceinline__ void stage_halo_rows(const ConvIn &in, int b, int ci,
             int xb = x0 - 4 + 4 * g;   // a multiple of 4; wraps as a whole group
             xb = xb < 0 ? xb + L : (xb >= L ? xb - L : xb);
             const int gy = wrap_tile(y0 + hy - 1, L, false), gz = wrap_tile(z0 + hz - 1, L, false);
-            const long long site = xb + (long long)L * (gy + (long long)L * gz);
+            const long long site = base + conv_offset<MODE>(xb, gy, gz, L);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int c = c8 * 8 + j;
                 v[u][j] = floatv4{0.f, 0.f, 0.f, 0.f};
                 if (ok && c < ci) {
-                    const long long a = ((long long)b * ci + c) * V + site;
-                    v[u][j] = *reinterpret_cast<const floatv4 *>(in.x1 + a);
-                    if (in.mode == CONV_IN_ADD) v[u][j] += *reinterpret_cast<const floatv4 *>(in.x2 + a);
+                    v[u][j] = conv_load4<MODE>(in, site + c * stride, L);
                     if (in.shift) v[u][j] = (v[u][j] - in.shift[c]) * in.scale[c];
                 }
             }
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int e = e0 + u * 256;
             if (e < total) {
                 const int c8 = e % oct, r = e / oct;
@@ -284,8 +304,12 @@ constexpr size_t conv_fwd_lds_t(int cip, int cop)
 
 // Block: a BX x BY x BZ tile of one sample; its 16-site MFMA column tiles are dealt to
 // the four waves (NTW each), each with NM = cop / 16 (1 or 2) 16-channel output tiles.
-template <int BX, int BY, int BZ, int NM>
-__global__ __launch_bounds__(256) void k_conv_fwd(ConvIn in, int ci, int cip, const __bf16 *__restrict__ Wm, int kp,
+// GIVE: the data gradient, which adds to ConvOut::give instead of writing Y, A or Ap (the sum and
+// the derivative of the activation in the epilogue cost 3 us at 64^3, batch 2, 8 -> 8 channels,
+// the passes over memory they replace 20).
+// Four blocks of the 16-channel 16x8x4 tile per CU (LDS) need at most 128 registers.
+template <int BX, int BY, int BZ, int NM, bool GIVE>
+__global__ __launch_bounds__(256, BX == 16 && NM == 1 ? 4 : 1) void k_conv_fwd(ConvIn in, int ci, int cip, const __bf16 *__restrict__ Wm, int kp,
                                                    int co, int cop, const float *__restrict__ bias, ConvOut out, int L,
                                                    int tiles_x, int tiles_y, int tiles_per_sample)
 {
@@ -348,8 +372,14 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvIn in, int ci, int cip, co
     }
     if (in.mode == CONV_IN_PACKED)
         stage_halo_packed<BX, BY, BZ>(in.xp, b, cip, L, x0, y0, z0, xs);
-    else if ((in.mode == CONV_IN_PLAIN || in.mode == CONV_IN_ADD) && L % 4 == 0 && L >= BX && L >= BY && L >= BZ)
-        stage_halo_rows<BX, BY, BZ>(in, b, ci, cip, L, x0, y0, z0, xs);
+    else if (L % 4 == 0 && L >= BX && L >= BY && L >= BZ) {
+        switch (in.mode) {
+        case CONV_IN_ADD: stage_halo_rows<BX, BY, BZ, CONV_IN_ADD>(in, b, ci, cip, L, x0, y0, z0, xs); break;
+        case CONV_IN_UP: stage_halo_rows<BX, BY, BZ, CONV_IN_UP>(in, b, ci, cip, L, x0, y0, z0, xs); break;
+        case CONV_IN_POOL: stage_halo_rows<BX, BY, BZ, CONV_IN_POOL>(in, b, ci, cip, L, x0, y0, z0, xs); break;
+        default: stage_halo_rows<BX, BY, BZ, CONV_IN_PLAIN>(in, b, ci, cip, L, x0, y0, z0, xs);
+        }
+    }
     else
         stage_halo_sm<BX, BY, BZ>(in, b, ci, cip, L, x0, y0, z0, xs);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -390,6 +420,53 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvIn in, int ci, int cip, co
             }
         }
     }
+    if constexpr (GIVE) {   // a batch of sites' loads in flight before the first is needed
+        constexpr int QB = NTW < 4 / NM ? NTW : 4 / NM;
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const ConvGive to = out.give[d];
+            if (!to.dst) continue;
+#pragma unroll
+            for (int q0 = 0; q0 < NTW; q0 += QB) {
+                long long at[QB];
+                float old[QB][NM][4], pre[QB][NM][4];
+#pragma unroll
+                for (int q = 0; q < QB; ++q) {
+                    const int n = (wave * NTW + q0 + q) * 16 + col;
+                    const int gx = x0 + n % BX, gy = y0 + (n / BX) % BY, gz = z0 + n / (BX * BY);
+                    at[q] = gx < L && gy < L && gz < L
+                                ? (long long)b * co * V + gx + (long long)L * (gy + (long long)L * gz)
+                                : -1;
+                }
+#pragma unroll
+                for (int q = 0; q < QB; ++q)
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int o = m * 16 + 4 * grp + i;
+                            old[q][m][i] = pre[q][m][i] = 0.0f;
+                            if (at[q] >= 0 && o < co) {
+                                if (to.add) old[q][m][i] = to.dst[at[q] + o * V];
+                                if (to.Y) pre[q][m][i] = to.Y[at[q] + o * V];
+                            }
+                        }
+#pragma unroll
+                for (int q = 0; q < QB; ++q)
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int o = m * 16 + 4 * grp + i;
+                            float v = acc[q0 + q][m][i];
+                            if (to.add) v = old[q][m][i] + v;
+                            if (to.Y) v *= silu_grad(pre[q][m][i]);
+                            if (at[q] >= 0 && o < co) to.dst[at[q] + o * V] = v;
+                        }
+            }
+        }
+        return;
+    }
     // epilogue: lane holds rows 4 grp + i of each M tile, column = its site
     float *Yb = out.Y ? out.Y + (long long)b * co * V : nullptr;
     float *Ab = out.A ? out.A + (long long)b * co * V : nullptr;
@@ -428,157 +505,342 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvIn in, int ci, int cip, co
 }
 
 // ---------------------------------------------------------------- weight gradient
-// dW[co][k cip + ci] = sum_b sum_x dY[b][co][x] X[b][ci][x + off_k], as the GEMM
-// C (cop x kp) = A (cop x sites) B (sites x kp).  Block (g, sp): the up to 4 x
-// WG_TILES_PER_WAVE C tiles of group g (WG_TILES_PER_WAVE per wave, accumulated in
-// registers) over the site tiles sp, sp + nsp, ... (K chunks of 32 sites = 4 x-rows of
-// 8).  A operands (dY, [cop][TS]) are shared by a wave's tiles; B operands come from
-// the shifted row copies (one 16-byte read each).  Partial C per site slice goes to
-// `part` [sp][cop][kp] and is summed in a fixed order by k_sum_blocks.
-constexpr int WG_TILES_PER_WAVE = 8;
-constexpr int WG_TILES_PER_BLOCK = 4 * WG_TILES_PER_WAVE;
+// dW[o][c][k] = sum_b sum_x dY[b][o][x] X[b][c][x + off_k], a contraction over the sites, for the
+// layers of one box in one launch (on coarse levels a layer alone has a few blocks).  Block
+// (layer, g, sl) owns the input channels 8 g .. 8 g + 7 and the site tiles sl, sl + slices, ...
+// of 8 XC x 4 x 4 sites.  Its C matrix is (output channels) x (9 row offsets (dz, dy) x 8
+// channels) for each dx: 5 column tiles of 16 and 3 dx, in registers, once per wave; the four
+// waves take the 32-site K chunks in turn and their sums are added at the end.  The B operand
+// for dx = 0 (8 sites of a row) is one aligned LDS read, those for dx = -1 and +1 are funnel
+// shifts of it with a neighbouring word, so an input site is staged once (16-byte loads, 8-byte
+// LDS stores).  The A operand (8 sites of dY) goes from memory to registers: with the channels
+// split over blocks no other wave of the block needs it.  The bias gradient is summed (FP64)
+// from the same values.
+//
+// Bound by staging: the latency of its loads and a barrier pair per tile (60 matrix
+// instructions per wave).  Measured at 64^3, batch 2 (8 -> 8 channels alone): 18 us, of which
+// the 34 MB of X and dY take 7 at the rate of a copy; three x-shifted LDS copies staged value by
+// value, a launch per layer, took 82.  The five layers of that level together 80 us against
+// 501, four layers of 32^3 (16 channels) 32 against 134, of 16^3 (24) 22 against 125, two of 8^3
+// (32) 13 against 67.
+constexpr int kWgTY = 4, kWgTZ = 4, kWgRows = (kWgTY + 2) * (kWgTZ + 2);
+constexpr int kWgCols = 5;             // 16-column tiles of 9 x 8 columns
+constexpr int kWgElems = 27 * 8;       // weights of one output channel in a block
 
-__global__ __launch_bounds__(256) void k_conv_wgrad(ConvIn in, int ci, int cip,
-                                                     const float *__restrict__ dY, int co, int cop, int kp,
-                                                     int L, int tiles_x, int tiles_y, int tiles_per_sample,
-                                                     int n_tiles, int n_groups, int n_slices,
-                                                     float *__restrict__ part)
+// LDS places: row r of channel c at wg_at(c, r): sites x0 .. x0 + XW - 1, then x0 + XW; x0 - 1 just
+// before it.
+template <int XC>
+struct WgTile {
+    static constexpr int XW = 8 * XC, PITCH = XW + 8, CP = kWgRows * PITCH + 8, LEAD = 8, SIZE = LEAD + 8 * CP;
+    static __device__ __forceinline__ int at(int c, int row) { return LEAD + c * CP + row * PITCH; }
+};
+
+// Channels 8 g .. 8 g + 7 of a tile's rows.
+template <int MODE, bool VEC, int XC>
+__device__ __forceinline__ void wgrad_stage(const ConvIn &in, int ci, int b, int g, int x0, int y0, int z0, int L,
+                                            __bf16 *xs)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __bf16 *xr = reinterpret_cast<__bf16 *>(smem);        // [3][cip][kWgChan]
-    __bf16 *ys = xr + (size_t)3 * cip * kWgChan;         // [cop][kWgYPitch]
-    const int g = blockIdx.x % n_groups, sp = blockIdx.x / n_groups;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int grp = lane >> 4, col = lane & 15;
-    const int nnt = kp / 16, ntiles = (cop / 16) * nnt;
+    using T = WgTile<XC>;
+    const int wave = threadIdx.x >> 6;
+            // groups of four sites: of the first 32 rows a thread takes one place and 2 XC channels, of
+            // the last 4 one place and channel; then the rows' two neighbours
+            const long long stride = conv_stride<MODE>(L), base = ((long long)b * ci + 8 * g) * stride;
+            auto wrap = [&](int v) {
+                if constexpr (!VEC) return wrapL(v, L);
+                v = v < 0 ? v + L : v;   // -L <= v < 3 L
+                v = v >= L ? v - L : v;
+                return v >= L ? v - L : v;
+            };
+            auto place = [&](int row, int x) {
+                return base + conv_offset<MODE>(wrap(x0 + x), wrap(y0 + row % (kWgTY + 2) - 1),
+                                                wrap(z0 + row / (kWgTY + 2) - 1), L);
+            };
+            auto group = [&](long long e, int row, int q) {
+                if constexpr (VEC) return conv_load4<MODE>(in, e, L);
+                floatv4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = conv_load1<MODE>(in, e - place(row, 4 * q) + place(row, 4 * q + i), L);
+                return v;
+            };
+            auto store = [&](int c, int row, int q, const floatv4 &v) {
+                bf16x4 w;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = (__bf16)v[i];
+                *reinterpret_cast<bf16x4 *>(xs + T::at(c, row) + 4 * q) = w;
+            };
+            int tid = threadIdx.x;   // opaque: places are computed per tile, not kept in registers
+            asm volatile("" : "+v"(tid));
+            {
+                constexpr int NC = 2 * XC, U = MODE == CONV_IN_POOL ? 1 : MODE == CONV_IN_ADD ? (NC < 4 ? NC : 4) : NC;
+                const int p = tid % (64 * XC), row = p / (2 * XC), q = p % (2 * XC), c0 = wave / XC * NC;
+                const long long e = place(row, 4 * q) + c0 * stride;
+#pragma unroll
+                for (int i0 = 0; i0 < NC; i0 += U) {
+                    floatv4 v[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        v[u] = floatv4{0.f, 0.f, 0.f, 0.f};
+                        if (8 * g + c0 + i0 + u < ci) v[u] = group(e + (i0 + u) * stride, row, q);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) store(c0 + i0 + u, row, q, v[u]);
+                }
+            }
+            if (tid < 64 * XC) {
+                const int p = tid % (8 * XC), row = 32 + p / (2 * XC), q = p % (2 * XC), c = tid / (8 * XC);
+                floatv4 v = {0.f, 0.f, 0.f, 0.f};
+                if (8 * g + c < ci) v = group(place(row, 4 * q) + c * stride, row, q);
+                store(c, row, q, v);
+            }
+            if (tid < 6 * kWgRows) {
+                const int p = tid % (2 * kWgRows), row = p >> 1, x = (p & 1) ? T::XW : -1, c0 = tid / (2 * kWgRows);
+                const long long e = place(row, x);
+                float v[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const int c = c0 + 3 * i;
+                    v[i] = 0.0f;
+                    if (c < 8 && 8 * g + c < ci) v[i] = conv_load1<MODE>(in, e + c * stride, L);
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (c0 + 3 * i < 8) xs[T::at(c0 + 3 * i, row) + x] = (__bf16)v[i];
+            }
+}
+
+// VEC: L is a multiple of 4 and rows are read in 16-byte loads.
+template <bool VEC, int XC, int MT>
+__global__ __launch_bounds__(256, MT == 1 ? 3 : 2) void k_conv_wgrad(WgradJobs W, int L, int tiles_x,
+                                                                                     int tiles_y, int tiles_per_sample,
+                                                                                     int n_tiles)
+{
+    using T = WgTile<XC>;
+    constexpr int XW = T::XW, PITCH = T::PITCH;
+    constexpr size_t kX = sizeof(__bf16) * T::SIZE, kR = sizeof(floatx4) * 2 * kWgCols * 64;
+    __shared__ __align__(16) unsigned char smem[kX > kR ? kX : kR];   // the tile; then the waves' sums
+    __shared__ double bs[16][MT * 16];
+    __bf16 *xs = reinterpret_cast<__bf16 *>(smem);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, col = lane & 15;
+    // the last layer that starts at or before this block
+    const int job = __builtin_popcountll(__ballot(lane < W.n && W.j[min(lane, W.n - 1)].block0 <= (int)blockIdx.x)) - 1;
+    const WgradJob J = W.j[job];
+    const int slices = J.slices, co = J.co;
+    const int g = ((int)blockIdx.x - J.block0) / slices, sl = ((int)blockIdx.x - J.block0) % slices;
+    const float *dY = J.dY;
     const long long V = (long long)L * L * L;
-    // this lane's B column of each of the wave's tiles: LDS offset of the row copy at the
-    // tile's centre row (-1 for the zero padding rows of K) and the tile's M tile
-    int boff[WG_TILES_PER_WAVE], mt[WG_TILES_PER_WAVE];
+    int boff[kWgCols];
 #pragma unroll
-    for (int j = 0; j < WG_TILES_PER_WAVE; ++j) {
-        const int tix = g * WG_TILES_PER_BLOCK + wave * WG_TILES_PER_WAVE + j;
-        const int nt = tix % nnt, kk = nt * 16 + col, k = kk / cip, c = kk - k * cip;
-        mt[j] = tix / nnt;
-        boff[j] = -1;
-        if (tix < ntiles && k <= 26) {
-            const int dx = (k % 3) - 1, dy = ((k / 3) % 3) - 1, dz = (k / 9) - 1;
-            boff[j] = ((dx + 1) * cip + c) * kWgChan + ((1 + dz) * HY + (1 + dy)) * TX;
-        }
+    for (int t = 0; t < kWgCols; ++t) {
+        const int j = t * 16 + col, r = min(j >> 3, 8);   // columns beyond 72 are dropped
+        boff[t] = T::at(j & 7, (r / 3) * (kWgTY + 2) + r % 3);
     }
-    floatx4 acc[WG_TILES_PER_WAVE];
+    floatx4 acc[MT][kWgCols][3];
+    double bsum[MT];
 #pragma unroll
-    for (int j = 0; j < WG_TILES_PER_WAVE; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int tile = sp; tile < n_tiles; tile += n_slices) {
+    for (int m = 0; m < MT; ++m) {
+        bsum[m] = 0.0;
+#pragma unroll
+        for (int t = 0; t < kWgCols; ++t)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) acc[m][t][d] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int tile = sl; tile < n_tiles; tile += slices) {
         const int b = tile / tiles_per_sample;
         int t = tile % tiles_per_sample;
-        const int x0 = (t % tiles_x) * TX;
+        const int x0 = (t % tiles_x) * XW;
         t /= tiles_x;
-        const int y0 = (t % tiles_y) * TY;
-        const int z0 = (t / tiles_y) * TZ;
-        __syncthreads();
-        stage_rows3(in, b, ci, cip, L, x0, y0, z0, xr);
-        for (int e0 = threadIdx.x; e0 < TS * cop; e0 += 256 * 8) {
-            float v[8];
+        const int y0 = (t % tiles_y) * kWgTY, z0 = (t / tiles_y) * kWgTZ;
+        // this wave's A operands: chunk wave + 4 j holds the 8-site groups 4 (wave + 4 j) + grp;
+        // the next chunk's loads are in flight while one is multiplied
+        float a[2][MT][8];
+        auto load_a = [&](int j, float (&v)[MT][8]) {
+            const int q = 4 * (wave + 4 * j) + grp, row = q / XC;
+            const int gx = x0 + 8 * (q % XC), gy = y0 + (row & 3), gz = z0 + (row >> 2);
+            const bool in_box = gy < L && gz < L;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = e0 + u * 256;
-                const int n = e % TS, o = e / TS;
-                const int tx = n % TX, ty = (n / TX) % TY, tz = n / (TX * TY);
-                const int gx = x0 + tx, gy = y0 + ty, gz = z0 + tz;
-                v[u] = 0.0f;
-                if (e < TS * cop && o < co && gx < L && gy < L && gz < L)   // sites outside the box add nothing
-                    v[u] = dY[((long long)b * co + o) * V + gx + (long long)L * (gy + (long long)L * gz)];
-            }
+            for (int m = 0; m < MT; ++m) {
+                const int o = m * 16 + col;
+                const float *p = dY + ((long long)b * co + o) * V + ((long long)gz * L + gy) * L + gx;
+                if constexpr (VEC) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = e0 + u * 256;
-                if (e < TS * cop) ys[(e / TS) * kWgYPitch + e % TS] = (__bf16)v[u];
+                    for (int h = 0; h < 2; ++h) {
+                        floatv4 w = {0.f, 0.f, 0.f, 0.f};
+                        if (in_box && o < co && gx + 4 * h < L) w = *reinterpret_cast<const floatv4 *>(p + 4 * h);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[m][4 * h + i] = w[i];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[m][i] = in_box && o < co && gx + i < L ? p[i] : 0.0f;
+                }
             }
+        };
+        load_a(0, a[0]);
+        __syncthreads();   // the previous tile has been read
+        switch (J.in.mode) {
+        case CONV_IN_ADD: wgrad_stage<CONV_IN_ADD, VEC, XC>(J.in, J.ci, b, g, x0, y0, z0, L, xs); break;
+        case CONV_IN_UP: wgrad_stage<CONV_IN_UP, VEC, XC>(J.in, J.ci, b, g, x0, y0, z0, L, xs); break;
+        case CONV_IN_POOL: wgrad_stage<CONV_IN_POOL, VEC, XC>(J.in, J.ci, b, g, x0, y0, z0, L, xs); break;
+        default: wgrad_stage<CONV_IN_PLAIN, VEC, XC>(J.in, J.ci, b, g, x0, y0, z0, L, xs);
         }
         __syncthreads();
-#pragma unroll 1
-        for (int kc = 0; kc < TS; kc += 32) {
-            // 8 consecutive sites of this lane group: one x-row of the tile
-            const int s0 = kc + 8 * grp;
-            const int ty = (s0 / TX) % TY, tz = s0 / (TX * TY);
-            const int roff = (tz * HY + ty) * TX;
-            const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(ys + col * kWgYPitch + s0);
-            bf16x8 a1 = a0;
-            if (cop > 16) a1 = *reinterpret_cast<const bf16x8 *>(ys + (16 + col) * kWgYPitch + s0);
 #pragma unroll
-            for (int j = 0; j < WG_TILES_PER_WAVE; ++j) {
-                const int tix = g * WG_TILES_PER_BLOCK + wave * WG_TILES_PER_WAVE + j;
-                if (tix < ntiles) {
-                    bf16x8 bv;
-                    if (boff[j] < 0) {
+        for (int j = 0; j < XC; ++j) {
+            if (j + 1 < XC) load_a(j + 1, a[(j + 1) & 1]);
+            bf16x8 ab[MT];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) bv[q] = (__bf16)0.0f;
-                    } else {
-                        bv = *reinterpret_cast<const bf16x8 *>(xr + boff[j] + roff);
-                    }
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mt[j] ? a1 : a0, bv, acc[j], 0, 0, 0);
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    ab[m][i] = (__bf16)a[j & 1][m][i];
+                    bsum[m] += (double)a[j & 1][m][i];
+                }
+            const int q = 4 * (wave + 4 * j) + grp, row = q / XC;
+            const int roff = ((row >> 2) * (kWgTY + 2) + (row & 3)) * PITCH + 8 * (q % XC);
+#pragma unroll
+            for (int t = 0; t < kWgCols; ++t) {
+                const __bf16 *p = xs + boff[t] + roff;
+                const uint4 w = *reinterpret_cast<const uint4 *>(p);
+                const unsigned lo = *reinterpret_cast<const unsigned *>(p - 2);
+                const unsigned hi = *reinterpret_cast<const unsigned *>(p + 8);
+                const unsigned s1 = __builtin_amdgcn_alignbit(w.y, w.x, 16), s2 = __builtin_amdgcn_alignbit(w.z, w.y, 16),
+                               s3 = __builtin_amdgcn_alignbit(w.w, w.z, 16);
+                const uint4 bl = {__builtin_amdgcn_alignbit(w.x, lo, 16), s1, s2, s3};
+                const uint4 br = {s1, s2, s3, __builtin_amdgcn_alignbit(hi, w.w, 16)};
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    acc[m][t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[m], __builtin_bit_cast(bf16x8, bl),
+                                                                           acc[m][t][0], 0, 0, 0);
+                    acc[m][t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[m], __builtin_bit_cast(bf16x8, w),
+                                                                           acc[m][t][1], 0, 0, 0);
+                    acc[m][t][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[m], __builtin_bit_cast(bf16x8, br),
+                                                                           acc[m][t][2], 0, 0, 0);
                 }
             }
         }
     }
-    float *P = part + (long long)sp * cop * kp;
+    // the waves' sums, (0 + 2) + (1 + 3), and the result of wave 0 to the slice's partials
+    floatx4 *red = reinterpret_cast<floatx4 *>(smem);
+    float *P = J.part + ((long long)g * slices + sl) * co * kWgElems;
 #pragma unroll
-    for (int j = 0; j < WG_TILES_PER_WAVE; ++j) {
-        const int tix = g * WG_TILES_PER_BLOCK + wave * WG_TILES_PER_WAVE + j;
-        if (tix < ntiles) {
-            const int m = tix / nnt, nt = tix % nnt;
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) P[(long long)(m * 16 + 4 * grp + i) * kp + nt * 16 + col] = acc[j][i];
+        for (int d = 0; d < 3; ++d) {
+#pragma unroll
+            for (int half = 2; half > 0; half >>= 1) {
+                __syncthreads();
+                if (wave >= half && wave < 2 * half)
+#pragma unroll
+                    for (int t = 0; t < kWgCols; ++t) red[((wave - half) * kWgCols + t) * 64 + lane] = acc[m][t][d];
+                __syncthreads();
+                if (wave < half)
+#pragma unroll
+                    for (int t = 0; t < kWgCols; ++t) acc[m][t][d] += red[(wave * kWgCols + t) * 64 + lane];
+            }
+            if (wave == 0)
+#pragma unroll
+                for (int t = 0; t < kWgCols; ++t) {
+                    const int j = t * 16 + col;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int o = m * 16 + 4 * grp + i;
+                        if (o < co && j < 72) P[o * kWgElems + ((j >> 3) * 3 + d) * 8 + (j & 7)] = acc[m][t][d][i];
+                    }
+                }
         }
+    if (g > 0) return;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) bs[wave * 4 + grp][m * 16 + col] = bsum[m];
+    __syncthreads();
+    if ((int)threadIdx.x < co) {
+        double t = 0.0;
+        for (int j = 0; j < 16; ++j) t += bs[j][threadIdx.x];
+        J.bpart[(long long)sl * co + threadIdx.x] = t;
     }
 }
 
-// out[e] = sum_b part[b][e], e < n, in a fixed order: thread (j, e) sums the partials
-// b = j, j + 32, ... of element e; the 32 sums are then added in order j = 0..31.  A
-// block covers 8 elements (32-byte rows of consecutive elements per partial).
-__global__ __launch_bounds__(256) void k_sum_blocks(const float *__restrict__ part, int nblk, long long n,
-                                                    float *__restrict__ out)
+// Sums of all layers' partials over their slices, in a fixed order, into the parameter vector's
+// layout.  A block takes 32 consecutive elements of one layer, 32 threads for each four (slices
+// j, j + 32, ... and then the 32 sums in order); a layer's last block its bias.  Bound by the
+// latency of two batches of eight loads: 14 us for the 15 layers of a four-level network (a launch
+// per layer for the sums, the reordering, and two for the bias took 370).
+__global__ __launch_bounds__(256) void k_wgrad_sum(WgradSums W, const float *__restrict__ part,
+                                                   const double *__restrict__ bpart, float *__restrict__ grad)
 {
-    __shared__ float red[32][8];
-    const int el = threadIdx.x & 7, j = threadIdx.x >> 3;
-    const long long e = (long long)blockIdx.x * 8 + el;
-    float s = 0.0f;
-    if (e < n)
-        for (int b = j; b < nblk; b += 32) s += part[(long long)b * n + e];
-    red[j][el] = s;
-    __syncthreads();
-    if (j == 0 && e < n) {
-        float t = red[0][el];
+    __shared__ __align__(16) float red[4 * 256];
+    double *redd = reinterpret_cast<double *>(red);
+    const int lane = threadIdx.x & 63;   // the last layer that starts at or before this block
+    const int l = __builtin_popcountll(__ballot(lane < W.n && W.l[min(lane, W.n - 1)].block0 <= (int)blockIdx.x)) - 1;
+    const WgradSum S = W.l[l];
+    const int blk = (int)blockIdx.x - S.block0, per = S.co * kWgElems, n = (S.ci + 7) / 8 * per;
+    if (blk * 32 < n) {
+        floatx4 *red4 = reinterpret_cast<floatx4 *>(red);
+        const int j = threadIdx.x >> 3, e = blk * 32 + 4 * (threadIdx.x & 7);   // 4 divides per
+        const int g = e / per, r = e % per;
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+        if (e < n) {
+            const floatx4 *p = reinterpret_cast<const floatx4 *>(part + S.part + (long long)g * S.slices * per + r);
+            const long long step = per / 4;
+            int k = j;
+            for (; k + 7 * 32 < S.slices; k += 8 * 32) {
+                floatx4 v[8];
 #pragma unroll
-        for (int q = 1; q < 32; ++q) t += red[q][el];
-        out[e] = t;
+                for (int u = 0; u < 8; ++u) v[u] = p[(k + u * 32) * step];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += v[u];
+            }
+            for (; k < S.slices; k += 32) s += p[k * step];
+        }
+        red4[threadIdx.x] = s;
+        __syncthreads();
+        if (j == 0 && e < n) {
+            floatx4 t = red4[threadIdx.x];
+#pragma unroll
+            for (int q = 1; q < 32; ++q) t += red4[q * 8 + threadIdx.x];
+            const int o = r / kWgElems, k = r % kWgElems;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = 8 * g + (k & 7) + i;
+                if (c < S.ci) grad[S.w_off + ((long long)o * S.ci + c) * 27 + (k >> 3)] = t[i];
+            }
+        }
+        return;
+    }
+    const int o = threadIdx.x & 31, j = threadIdx.x >> 5;
+    double s = 0.0;
+    if (o < S.co)
+        for (int k = j; k < S.slices; k += 8) s += bpart[S.bpart + (long long)k * S.co + o];
+    redd[threadIdx.x] = s;
+    __syncthreads();
+    if (j == 0 && o < S.co) {
+        double t = redd[threadIdx.x];
+        for (int q = 1; q < 8; ++q) t += redd[q * 32 + threadIdx.x];
+        grad[S.b_off + o] = (float)t;
     }
 }
 
 // ---------------------------------------------------------------- element-wise parts
-__global__ void k_silu_bwd(const float *__restrict__ dA, const float *__restrict__ Y, float *__restrict__ dY,
-                           long long n)
+// gradient of the pooling: a fine site is given dout[coarse] / 8.  A thread takes two sites of a
+// row (L is even).
+__global__ void k_pool_bwd(const float *__restrict__ dout, ConvGive to, int L, long long n_in)
 {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) dY[e] = dA[e] * silu_grad(Y[e]);
-}
-
-// gradient of the pooling: din[fine] (+)= dout[coarse] / 8
-__global__ void k_pool_bwd(const float *__restrict__ dout, float *__restrict__ din, int L, long long n_in, int add)
-{
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long e = 2 * ((long long)blockIdx.x * blockDim.x + threadIdx.x);
     if (e >= n_in) return;
-    const int h = L / 2;
-    const long long vo = (long long)h * h * h, vi = (long long)L * L * L;
-    const long long bc = e / vi, r = e % vi;
-    const int x = (int)(r % L), y = (int)((r / L) % L), z = (int)(r / ((long long)L * L));
-    const float g = 0.125f * dout[bc * vo + (x / 2) + (long long)h * ((y / 2) + (long long)h * (z / 2))];
-    din[e] = add ? din[e] + g : g;
+    const int h = L / 2, x = (int)(e % L);
+    const long long row = e / L, yz = row % ((long long)L * L), bc = row / ((long long)L * L);
+    const int y = (int)(yz % L), z = (int)(yz / L);
+    const float g = 0.125f * dout[bc * h * h * h + x / 2 + (long long)h * (y / 2 + (long long)h * (z / 2))];
+    floatv2 v = {g, g};
+    if (to.add) v = *reinterpret_cast<const floatv2 *>(to.dst + e) + g;
+    if (to.Y) {
+        const floatv2 p = *reinterpret_cast<const floatv2 *>(to.Y + e);
+        v = floatv2{v.x * silu_grad(p.x), v.y * silu_grad(p.y)};
+    }
+    *reinterpret_cast<floatv2 *>(to.dst + e) = v;
 }
 
-// gradient of the upsampling: dcoarse (+)= sum of the 8 fine gradients
-__global__ void k_up_bwd(const float *__restrict__ dout, float *__restrict__ din, int L, long long n_in, int add)
+// gradient of the upsampling: a coarse site is given the sum of its 8 fine gradients
+__global__ void k_up_bwd(const float *__restrict__ dout, ConvGive to, int L, long long n_in)
 {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n_in) return;
@@ -591,49 +853,7 @@ __global__ void k_up_bwd(const float *__restrict__ dout, float *__restrict__ din
     for (int dz = 0; dz < 2; ++dz)
         for (int dy = 0; dy < 2; ++dy)
             for (int dx = 0; dx < 2; ++dx) s += p[(2 * x + dx) + (long long)L * ((2 * y + dy) + (long long)L * (2 * z + dz))];
-    din[e] = add ? din[e] + s : s;
-}
-
-// dst = src, or dst += src
-__global__ void k_accum(float *__restrict__ dst, const float *__restrict__ src, long long n, int add)
-{
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) dst[e] = add ? dst[e] + src[e] : src[e];
-}
-
-// Per-channel sum over batch and sites, out[c] = sum_{b,x} g[b][c][x], in two fixed-order
-// stages: block (c, j) sums slice j of the B V values of channel c into part[c][j];
-// k_channel_final adds the slices in order.
-constexpr int kChanSlices = 64;
-
-__global__ __launch_bounds__(256) void k_channel_partial(const float *__restrict__ g, int B, int C, long long V,
-                                                         double *__restrict__ part)
-{
-    const int c = blockIdx.x / kChanSlices, j = blockIdx.x % kChanSlices;
-    const long long n = (long long)B * V, per = (n + kChanSlices - 1) / kChanSlices;
-    const long long lo = j * per, hi = min(n, lo + per);
-    double s = 0.0;
-    for (long long e = lo + threadIdx.x; e < hi; e += 256) {
-        const long long b = e / V, x = e - b * V;
-        s += g[(b * C + c) * V + x];
-    }
-    __shared__ double red[256];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ void k_channel_final(const double *__restrict__ part, int C, float *__restrict__ out)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    double s = 0.0;
-    for (int j = 0; j < kChanSlices; ++j) s += part[c * kChanSlices + j];
-    out[c] = (float)s;
+    give_gradient(to, e, s);
 }
 
 // squared error: per-block partial sums of (p - t)^2 and dp = 2 (p - t) / count
@@ -696,17 +916,6 @@ __global__ void k_stage_weights(const float *__restrict__ W, int co, int ci, int
         if (c < ci && k < 27 && o < co) v = W[((long long)o * ci + c) * 27 + (26 - k)];
         Wt[f] = (__bf16)v;
     }
-}
-
-// master-layout gradient dW[o][c][k] from the matrix-core layout dWm[o][k cip + c]
-__global__ void k_unstage_grad(const float *__restrict__ dWm, int co, int ci, int cip, int kp,
-                               float *__restrict__ dW)
-{
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long n = (long long)co * ci * 27;
-    if (e >= n) return;
-    const int k = (int)(e % 27), c = (int)((e / 27) % ci), o = (int)(e / (27LL * ci));
-    dW[e] = dWm[(long long)o * kp + k * cip + c];
 }
 
 // Warm start from the network's prediction p (FP32, 2 polymer channels):
@@ -891,12 +1100,16 @@ static void conv_fwd_launch(hipStream_t s, ConvIn in, int B, int ci, int cip, co
     const int tx = (L + BX - 1) / BX, ty = (L + BY - 1) / BY, tz = (L + BZ - 1) / BZ;
     const int tps = tx * ty * tz;
     const size_t lds = conv_fwd_lds_t<BX, BY, BZ>(cip, cop);
-    if (cop == 16)
-        hipLaunchKernelGGL((k_conv_fwd<BX, BY, BZ, 1>), dim3(B * tps), dim3(256), lds, s, in, ci, cip, Wm, kp, co, cop,
-                           bias, out, L, tx, ty, tps);
-    else
-        hipLaunchKernelGGL((k_conv_fwd<BX, BY, BZ, 2>), dim3(B * tps), dim3(256), lds, s, in, ci, cip, Wm, kp, co, cop,
-                           bias, out, L, tx, ty, tps);
+    auto go = [&](auto NM, auto GIVE) {
+        hipLaunchKernelGGL((k_conv_fwd<BX, BY, BZ, NM(), GIVE()>), dim3(B * tps), dim3(256), lds, s, in, ci, cip, Wm, kp,
+                           co, cop, bias, out, L, tx, ty, tps);
+    };
+    auto tiles = [&](auto GIVE) {
+        if (cop == 16) go(std::integral_constant<int, 1>(), GIVE);
+        else go(std::integral_constant<int, 2>(), GIVE);
+    };
+    if (out.give[0].dst) tiles(std::true_type());
+    else tiles(std::false_type());
 }
 
 // Tile per layer: the largest of 16x8x4, 8x8x4, 8x4x4 that the box fills, whose LDS
@@ -927,58 +1140,77 @@ void net_conv_fwd(hipStream_t s, ConvIn in, int B, int ci, int cip, const __bf16
         conv_fwd_launch<8, 4, 2>(s, in, B, ci, cip, Wm, kp, co, cop, bias, out, L);
 }
 
-// Site slices of the weight gradient: enough blocks (groups x slices, about 1024) to
-// fill the chip, each covering at least one site tile.  The partials buffer holds
-// slices x cop x kp floats.
-int net_wgrad_slices(int B, int L, int cop, int kp)
+// Width of the weight gradient's site tiles in units of 8: the widest of 32, 16 and 8 sites that
+// pads the box by at most an eighth (a wide tile stages fewer neighbours of its rows and gives
+// each wave more K chunks per barrier); 8 where rows are not read four sites at a time.
+static int wgrad_xc(int L)
 {
-    const int tx = (L + TX - 1) / TX, ty = (L + TY - 1) / TY, tz = (L + TZ - 1) / TZ;
-    const int n_tiles = B * tx * ty * tz;
-    const int groups = ((cop / 16) * (kp / 16) + WG_TILES_PER_BLOCK - 1) / WG_TILES_PER_BLOCK;
-    const int want = std::max(1, 1024 / groups);
-    return std::min(n_tiles, want);
+    if (L % 4) return 1;
+    for (int xc = 4; xc > 1; xc /= 2)
+        if (((L + 8 * xc - 1) / (8 * xc) * 8 * xc - L) * 8 <= L) return xc;
+    return 1;
 }
 
-void net_conv_wgrad(hipStream_t s, ConvIn in, int B, int ci, int cip, const float *dY, int co, int cop, int kp,
-                    int L, float *part, float *dWm)
+static int wgrad_tiles(int B, int L)
 {
-    const int tx = (L + TX - 1) / TX, ty = (L + TY - 1) / TY, tz = (L + TZ - 1) / TZ;
-    const int tps = tx * ty * tz, n_tiles = B * tps;
-    const int slices = net_wgrad_slices(B, L, cop, kp);
-    const int ntiles = (cop / 16) * (kp / 16), groups = (ntiles + WG_TILES_PER_BLOCK - 1) / WG_TILES_PER_BLOCK;
-    const size_t lds = ((size_t)3 * cip * kWgChan + (size_t)cop * kWgYPitch) * sizeof(__bf16);
-    hipLaunchKernelGGL(k_conv_wgrad, dim3(groups * slices), dim3(256), lds, s, in, ci, cip, dY, co, cop, kp, L, tx,
-                       ty, tps, n_tiles, groups, slices, part);
-    const long long n = (long long)cop * kp;
-    hipLaunchKernelGGL(k_sum_blocks, dim3(nb(n, 8)), dim3(256), 0, s, part, slices, n, dWm);
+    const int xw = 8 * wgrad_xc(L);
+    return B * ((L + xw - 1) / xw) * ((L + kWgTY - 1) / kWgTY) * ((L + kWgTZ - 1) / kWgTZ);
 }
 
-void net_silu_bwd(hipStream_t s, const float *dA, const float *Y, float *dY, long long n)
+// Slices of a layer's weight gradient: kWgBlocks blocks (channel octets x slices), each with at
+// least one tile.  A level's layers share a launch, so one block per CU and layer fills the
+// chip; more blocks write more partials (64^3, batch 2, five layers and the sums of all: 512
+// blocks 90 + 22 us, 256 80 + 14).
+constexpr int kWgBlocks = 256;
+int net_wgrad_slices(int B, int L, int ci)
 {
-    hipLaunchKernelGGL(k_silu_bwd, dim3(nb(n, 256)), dim3(256), 0, s, dA, Y, dY, n);
+    return std::min(wgrad_tiles(B, L), std::max(1, kWgBlocks / ((ci + 7) / 8)));
+}
+long long net_wgrad_part(int slices, int ci, int co) { return (long long)((ci + 7) / 8) * slices * co * kWgElems; }
+
+void net_conv_wgrad(hipStream_t s, WgradJobs &W, int B, int L)
+{
+    int blocks = 0, co = 0;
+    for (int k = 0; k < W.n; ++k) {
+        W.j[k].block0 = blocks;
+        blocks += (W.j[k].ci + 7) / 8 * W.j[k].slices;
+        co = std::max(co, W.j[k].co);
+    }
+    // above 16 outputs the accumulators leave no registers for the widest tile's staging
+    const int xc = co > 16 ? std::min(wgrad_xc(L), 2) : wgrad_xc(L), xw = 8 * xc;
+    const int tx = (L + xw - 1) / xw, ty = (L + kWgTY - 1) / kWgTY, tz = (L + kWgTZ - 1) / kWgTZ;
+    auto go = [&](auto VEC, auto XC, auto MT) {
+        hipLaunchKernelGGL((k_conv_wgrad<VEC(), XC(), MT()>), dim3(blocks), dim3(256), 0, s, W, L, tx, ty, tx * ty * tz,
+                           B * tx * ty * tz);
+    };
+    auto width = [&](auto MT) {
+        if (L % 4) go(std::false_type(), std::integral_constant<int, 1>(), MT);
+        else if (xc == 2) go(std::true_type(), std::integral_constant<int, 2>(), MT);
+        else go(std::true_type(), std::integral_constant<int, 1>(), MT);
+    };
+    if (xc == 4) go(std::true_type(), std::integral_constant<int, 4>(), std::integral_constant<int, 1>());
+    else if (co <= 16) width(std::integral_constant<int, 1>());
+    else width(std::integral_constant<int, 2>());
 }
 
-void net_pool_bwd(hipStream_t s, const float *dout, float *din, int L, long long n_in, int add)
+void net_wgrad_sum(hipStream_t s, WgradSums &W, const float *part, const double *bpart, float *grad)
 {
-    hipLaunchKernelGGL(k_pool_bwd, dim3(nb(n_in, 256)), dim3(256), 0, s, dout, din, L, n_in, add);
+    int blocks = 0;
+    for (int l = 0; l < W.n; ++l) {
+        W.l[l].block0 = blocks;
+        blocks += (int)nb((long long)((W.l[l].ci + 7) / 8) * W.l[l].co * kWgElems, 32) + 1;
+    }
+    hipLaunchKernelGGL(k_wgrad_sum, dim3(blocks), dim3(256), 0, s, W, part, bpart, grad);
 }
 
-void net_up_bwd(hipStream_t s, const float *dout, float *din, int L, long long n_in, int add)
+void net_pool_bwd(hipStream_t s, const float *dout, const ConvGive &to, int L, long long n_in)
 {
-    hipLaunchKernelGGL(k_up_bwd, dim3(nb(n_in, 256)), dim3(256), 0, s, dout, din, L, n_in, add);
+    hipLaunchKernelGGL(k_pool_bwd, dim3(nb(n_in / 2, 256)), dim3(256), 0, s, dout, to, L, n_in);
 }
 
-void net_accum(hipStream_t s, float *dst, const float *src, long long n, int add)
+void net_up_bwd(hipStream_t s, const float *dout, const ConvGive &to, int L, long long n_in)
 {
-    hipLaunchKernelGGL(k_accum, dim3(nb(n, 256)), dim3(256), 0, s, dst, src, n, add);
-}
-
-int net_channel_parts(int C) { return C * kChanSlices; }
-
-void net_channel_sum(hipStream_t s, const float *g, int B, int C, long long V, double *part, float *out)
-{
-    hipLaunchKernelGGL(k_channel_partial, dim3(C * kChanSlices), dim3(256), 0, s, g, B, C, V, part);
-    hipLaunchKernelGGL(k_channel_final, dim3(1), dim3(64), 0, s, part, C, out);
+    hipLaunchKernelGGL(k_up_bwd, dim3(nb(n_in, 256)), dim3(256), 0, s, dout, to, L, n_in);
 }
 
 int net_mse(hipStream_t s, const float *p, const float *t, float *dp, long long n, float inv_count, double *part)
@@ -1000,12 +1232,6 @@ void net_stage_weights(hipStream_t s, const float *W, int co, int ci, int cip, i
     const long long n = (long long)cop_rows * kp + (long long)cop_rows_t * kp_t;
     hipLaunchKernelGGL(k_stage_weights, dim3(nb(n, 256)), dim3(256), 0, s, W, co, ci, cip, kp, cop_rows, Wm, cip_t,
                        kp_t, cop_rows_t, Wt);
-}
-
-void net_unstage_grad(hipStream_t s, const float *dWm, int co, int ci, int cip, int kp, float *dW)
-{
-    const long long n = (long long)co * ci * 27;
-    hipLaunchKernelGGL(k_unstage_grad, dim3(nb(n, 256)), dim3(256), 0, s, dWm, co, ci, cip, kp, dW);
 }
 
 void net_warm_input(hipStream_t s, const double *phi, const double *h0, const double *h1, int nsp, long long V,
