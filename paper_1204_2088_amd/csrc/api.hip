@@ -1580,8 +1580,9 @@ int hsf_lb_advance(hsf_ctx *c, int n_steps, const double *force, int where)
     for (int k = 0; k < n_steps; ++k) {
         {
             Timed t(c, HSF_K_LB);
-            launch_lb(c->stream, c->plan, c->rep_d, c->nA, c->nB, c->lb32, f, c->rho, c->u, (c->noise & HSF_NOISE_LB) != 0,
-                      c->noise_step, c->lb_all, t.a, t.b);
+            const bool last = k == n_steps - 1;   // density and velocity are those of the last step
+            launch_lb(c->stream, c->plan, c->rep_d, c->nA, c->nB, c->lb32, f, last ? c->rho : nullptr,
+                      last ? c->u : nullptr, (c->noise & HSF_NOISE_LB) != 0, c->noise_step, c->lb_all, t.a, t.b);
         }
         std::swap(c->nA, c->nB);
         if (c->noise) ++c->noise_step;

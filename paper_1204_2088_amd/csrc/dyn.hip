@@ -243,11 +243,11 @@ __host__ __device__ constexpr double mrt_e(int k, int cx, int cy, int cz)
 }
 
 
-// The basis at the 19 velocities and 1 / b_k, as compile-time tables (the unrolled
-// projections below index them with constants).
+// The basis at the 19 velocities, 1 / b_k and its square root, as compile-time tables (the
+// unrolled projections below index them with constants).
 struct MrtTable {
     double e[19][19];   // [k][q]
-    double binv[19];
+    double binv[19], rbinv[19];
 };
 
 constexpr MrtTable make_mrt_table()
@@ -260,18 +260,46 @@ constexpr MrtTable make_mrt_table()
             b += lb_w(q) * t.e[k][q] * t.e[k][q];
         }
         t.binv[k] = 1.0 / b;
+        double r = 1.0;
+        for (int it = 0; it < 60; ++it) r = 0.5 * (r + t.binv[k] / r);
+        t.rbinv[k] = r;
     }
     return t;
 }
 
 __device__ constexpr MrtTable kMrt = make_mrt_table();
 
-// Post-collision populations of one site for the MRT scheme: n* = n_eq + w_i sum_k
-// e_k(c_i) m*_k / b_k with m*_k = gamma_k (n - n_eq)_k + (Delta^f)_k, where the forcing
-// Delta^f_i = (w_i / c_s^2) [f.c_i + Sigma : (c_i c_i - c_s^2 1) / (2 c_s^2)] and
-// Sigma = (1 + gamma_s)/2 (u f + f u - 2/3 (u.f) 1) + (1 + gamma_b)/3 (u.f) 1 (eq. 14).
+// Velocities 2 p + 1 and 2 p + 2 are opposite: modes even in c see the sum of a pair, odd ones the
+// difference, so a transform takes half the terms, and those with e_k = 0 are left out (the
+// compiler has to keep a product with zero): about 100 terms where 19 x 19 are written out.
+constexpr bool mrt_odd(int k) { return (k >= 1 && k <= 3) || (k >= 10 && k <= 15); }
+
+// sum_k e_k(c) v_k over the even (odd) modes K0 .. 18 at velocity q.
+template <int K0, bool ODD>
+__device__ __forceinline__ double mrt_back(const double *v, int q)
+{
+    double a = 0.0;
+    bool first = true;
+#pragma unroll
+    for (int k = K0; k < 19; ++k) {
+        const double e = kMrt.e[k][q];
+        if (mrt_odd(k) != ODD || e == 0.0) continue;
+        a = first ? e * v[k] : a + e * v[k];
+        first = false;
+    }
+    return a;
+}
+
+// Collision of one site by the MRT scheme: n* = n_eq + w_i sum_k e_k(c_i) m*_k / b_k with m*_k =
+// gamma_k (n - n_eq)_k + (Delta^f)_k, where the forcing Delta^f_i = (w_i / c_s^2) [f.c_i + Sigma :
+// (c_i c_i - c_s^2 1) / (2 c_s^2)] and Sigma = (1 + gamma_s)/2 (u f + f u - 2/3 (u.f) 1) + (1 +
+// gamma_b)/3 (u.f) 1 (eq. 14).  The forcing is a polynomial of second degree in c_i, so its
+// moments are f (modes 1-3), tr Sigma (4), Sxx - Syy (5), Sxx + Syy - 2 Szz (6), the
+// off-diagonal elements (7-9) and zero for the others.  noise (or null): numbers added to the
+// modes k >= 4 of n* (lb_noise_modes).  emit(q, n*_q) takes the results.
+template <typename Emit>
 __device__ __forceinline__ void mrt_collide(const double *n, double rho, double ux, double uy, double uz, double fx,
-                                            double fy, double fz, const Rep &R, double *ns)
+                                            double fy, double fz, const Rep &R, const double *noise, Emit emit)
 {
     const double gs = R.gamma_s, gb = R.gamma_b, gg = R.gamma_ghost;
     const double uu = ux * ux + uy * uy + uz * uz, uf = ux * fx + uy * fy + uz * fz;
@@ -281,67 +309,81 @@ __device__ __forceinline__ void mrt_collide(const double *n, double rho, double 
     const double syy = as * (2.0 * uy * fy - 2.0 / 3.0 * uf) + ab * uf;
     const double szz = as * (2.0 * uz * fz - 2.0 / 3.0 * uf) + ab * uf;
     const double sxy = as * (ux * fy + uy * fx), sxz = as * (ux * fz + uz * fx), syz = as * (uy * fz + uz * fy);
-    const double trs = sxx + syy + szz;
-    double dn[19], df[19], neq[19];
+    const double mf[10] = {0.0, fx, fy, fz, sxx + syy + szz, sxx - syy, sxx + syy - 2.0 * szz, sxy, sxz, syz};
+    // n_eq = rho w (ev +- od), and the pairs' sums and differences of n - n_eq
+    const double ev0 = 1.0 - 1.5 * uu;
+    auto equilibrium = [&](int q, double &ev, double &od) {
+        const double cu = kCx[q] * ux + kCy[q] * uy + kCz[q] * uz;
+        ev = ev0 + 4.5 * cu * cu;
+        od = 3.0 * cu;
+    };
+    double dn[19];
+    dn[0] = n[0] - rho * lb_w(0) * ev0;
 #pragma unroll
-    for (int q = 0; q < 19; ++q) {
-        const double cx = kCx[q], cy = kCy[q], cz = kCz[q];
-        const double cu = cx * ux + cy * uy + cz * uz;
-        neq[q] = rho * lb_w(q) * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu);
-        dn[q] = n[q] - neq[q];
-        // Sigma : (c c - 1/3) = c.Sigma.c - tr(Sigma)/3
-        const double scc = cx * cx * sxx + cy * cy * syy + cz * cz * szz +
-                           2.0 * (cx * cy * sxy + cx * cz * sxz + cy * cz * syz) - trs / 3.0;
-        df[q] = 3.0 * lb_w(q) * (cx * fx + cy * fy + cz * fz + 1.5 * scc);
+    for (int p = 1; p < 10; ++p) {
+        const int q = 2 * p - 1;
+        double ev, od;
+        equilibrium(q, ev, od);
+        const double rw = rho * lb_w(q), da = n[q] - rw * (ev + od), db = n[q + 1] - rw * (ev - od);
+        dn[q] = da + db;
+        dn[q + 1] = da - db;
     }
     double ms[19];
 #pragma unroll
     for (int k = 0; k < 19; ++k) {
-        double m = 0.0, mf = 0.0;
+        double m = 0.0;
+        bool first = true;
+        if (!mrt_odd(k)) {
+            m = kMrt.e[k][0] * dn[0];
+            first = kMrt.e[k][0] == 0.0;
+        }
 #pragma unroll
-        for (int q = 0; q < 19; ++q) {
-            const double e = kMrt.e[k][q];
-            m += e * dn[q];
-            mf += e * df[q];
+        for (int p = 1; p < 10; ++p) {
+            const double e = kMrt.e[k][2 * p - 1], v = dn[mrt_odd(k) ? 2 * p : 2 * p - 1];
+            if (e == 0.0) continue;
+            m = first ? e * v : m + e * v;
+            first = false;
         }
         const double g = k <= 3 ? 1.0 : (k == 4 ? gb : (k <= 9 ? gs : gg));
-        ms[k] = (g * m + mf) * kMrt.binv[k];
+        if (k > 0 && k < 10) m = g * m + mf[k];
+        else if (k > 0) m *= g;
+        ms[k] = m * kMrt.binv[k];
+        if (noise && k >= 4) ms[k] += noise[k];
     }
+    asm volatile("" : "+v"(ux), "+v"(uy), "+v"(uz));   // computed again: 19 values fewer kept
+    emit(0, lb_w(0) * (rho * ev0 + mrt_back<0, false>(ms, 0)));
 #pragma unroll
-    for (int q = 0; q < 19; ++q) {
-        double a = 0.0;
-#pragma unroll
-        for (int k = 0; k < 19; ++k) a += kMrt.e[k][q] * ms[k];
-        ns[q] = neq[q] + lb_w(q) * a;
+    for (int p = 1; p < 10; ++p) {
+        const int q = 2 * p - 1;
+        double ev, od;
+        equilibrium(q, ev, od);
+        const double a = rho * ev + mrt_back<0, false>(ms, q), b = rho * od + mrt_back<0, true>(ms, q);
+        emit(q, lb_w(q) * (a + b));
+        emit(q + 1, lb_w(q) * (a - b));
     }
 }
 
-// Mode noise of eq. 13 added to the post-collision populations ns of site i of replica r:
-// mode k >= 4 receives phi_k r_k, phi_k = sqrt(rho kT b_k (1 - gamma_k^2) / c_s^2), carried
-// to the populations as w_q e_k(c_q) phi_k r_k / b_k.  kT = dt^2 / Omega in LB units;
-// gamma_k of the collision (BGK: 1 - 1/tau for every non-conserved mode).  r_k are the
-// normal numbers of purposes 0-3 (mode k takes number k - 4).
-__device__ __forceinline__ void lb_mode_noise(const Rep &R, int r, long long i, unsigned long long step,
-                                              double rho, double *ns)
+// Mode noise of eq. 13 for site i of replica r: mode k >= 4 receives phi_k r_k, phi_k = sqrt(rho kT
+// b_k (1 - gamma_k^2) / c_s^2), carried to the populations as w_q e_k(c_q) a_k, a_k = phi_k r_k /
+// b_k.  kT = dt^2 / Omega in LB units; gamma_k of the collision (BGK: 1 - 1/tau for every
+// non-conserved mode).  r_k are the normal numbers of purposes 0-3 (mode k takes number k - 4).
+__device__ __forceinline__ void lb_noise_modes(const Rep &R, int r, long long i, unsigned long long step, double rho,
+                                               double *a)
 {
-    double z[16];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) normals4(R.seed, (uint64_t)r, (uint64_t)i, step, (uint64_t)p, z + 4 * p);
     const double rk = 3.0 * fmax(rho, 0.0) * (R.dt * R.dt / R.omega);
     const bool mrt = R.lb_mode == HSF_LB_MRT;
     const double gbgk = 1.0 - 1.0 / R.tau;
-    double a[19];
+    const double gb = mrt ? R.gamma_b : gbgk, gs = mrt ? R.gamma_s : gbgk, gg = mrt ? R.gamma_ghost : gbgk;
+    const double sb = sqrt(rk * (1.0 - gb * gb)), ss = sqrt(rk * (1.0 - gs * gs)), sg = sqrt(rk * (1.0 - gg * gg));
 #pragma unroll
-    for (int k = 4; k < 19; ++k) {
-        const double g = mrt ? (k == 4 ? R.gamma_b : (k <= 9 ? R.gamma_s : R.gamma_ghost)) : gbgk;
-        a[k] = sqrt(rk * (1.0 - g * g) * kMrt.binv[k]) * z[k - 4];
-    }
+    for (int p = 0; p < 4; ++p) {
+        double z[4];
+        normals4(R.seed, (uint64_t)r, (uint64_t)i, step, (uint64_t)p, z);
 #pragma unroll
-    for (int q = 0; q < 19; ++q) {
-        double acc = 0.0;
-#pragma unroll
-        for (int k = 4; k < 19; ++k) acc += kMrt.e[k][q] * a[k];
-        ns[q] += lb_w(q) * acc;
+        for (int j = 0; j < 4; ++j) {
+            const int k = 4 + 4 * p + j;
+            if (k < 19) a[k] = (k == 4 ? sb : (k <= 9 ? ss : sg)) * (kMrt.rbinv[k] * z[j]);
+        }
     }
 }
 
@@ -353,8 +395,17 @@ __device__ __forceinline__ void lb_mode_noise(const Rep &R, int r, long long i, 
 // the mode noise of eq. 13 before streaming.  MODE: HSF_LB_BGK or HSF_LB_MRT when every
 // replica uses that collision (each variant needs only its own registers), -1 for a batch
 // that mixes them (chosen per replica).
+//
+// Without noise bound by memory: 152 B (FP32 populations) or 304 B per site and 24 B of force;
+// 128^3 FP32 with density and velocity (another 32 B, written by a call's last step only) 86 us,
+// 5.0 TB/s, without 75 us.  MRT the same: with all 19 x 19 products written out it took 143
+// against BGK's 97 us for four steps of a 64^3 FP64 box and its copies, now 94 against 93.  With
+// noise bound by the 16 normal numbers of a site (Philox's integer products, log, sqrt, sincos):
+// 64^3 FP64 MRT 34 us against 46 with the full products, 15 square roots and 7
+// multiplications per 128-bit product.  Up to 128 registers, four wavefronts per SIMD, where
+// the variant has that few.
 template <bool NOISE, int MODE, typename pop_t>
-__global__ __launch_bounds__(kBlock) void k_lb(const int *__restrict__ blk_rep, const int *__restrict__ blk_first,
+__global__ __launch_bounds__(kBlock, NOISE && MODE != HSF_LB_MRT ? 3 : 4) void k_lb(const int *__restrict__ blk_rep, const int *__restrict__ blk_first,
                                                const Rep *__restrict__ rep, const pop_t *__restrict__ nsrc,
                                                pop_t *__restrict__ ndst, const double *__restrict__ f,
                                                double *__restrict__ rho_out, double *__restrict__ u_out,
@@ -387,14 +438,19 @@ __global__ __launch_bounds__(kBlock) void k_lb(const int *__restrict__ blk_rep, 
     const double ux = (jx + 0.5 * fx) / rho, uy = (jy + 0.5 * fy) / rho, uz = (jz + 0.5 * fz) / rho;
     // a non-finite population or force shows in the moments; the host rolls the step back
     if (bad && !(isfinite(rho) && isfinite(ux) && isfinite(uy) && isfinite(uz))) bad[0] = 1;
-    double ns[19];
-    const bool mrt = MODE == HSF_LB_MRT || (MODE < 0 && R.lb_mode == HSF_LB_MRT);
-    if (mrt) {
-        mrt_collide(n, rho, ux, uy, uz, fx, fy, fz, R, ns);
+    double am[19];
+    if (NOISE) lb_noise_modes(R, sr.r, i, step, rho, am);
+    auto emit = [&](int q, double v) {
+        const int xd = wrap1(x + kCx[q], R.Lx), yd = wrap1(y + kCy[q], R.Ly), zd = wrap1(z + kCz[q], R.Lz);
+        pop_store(ndst, base + q * V + sidx(R, xd, yd, zd), q, v);
+    };
+    if (MODE == HSF_LB_MRT || (MODE < 0 && R.lb_mode == HSF_LB_MRT)) {
+        mrt_collide(n, rho, ux, uy, uz, fx, fy, fz, R, NOISE ? am : nullptr, emit);
     } else {
         const double om = 1.0 / R.tau, fp = 1.0 - 0.5 / R.tau;
         const double uu = ux * ux + uy * uy + uz * uz;
         const double uf = ux * fx + uy * fy + uz * fz;
+        double even = 0.0, odd = 0.0;   // the noise of a pair of opposite velocities
 #pragma unroll
         for (int q = 0; q < 19; ++q) {
             const double cu = kCx[q] * ux + kCy[q] * uy + kCz[q] * uz;
@@ -402,21 +458,17 @@ __global__ __launch_bounds__(kBlock) void k_lb(const int *__restrict__ blk_rep, 
             const double wq = lb_w(q);
             const double neq = rho * wq * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu);
             const double F = fp * wq * (3.0 * (cf - uf) + 9.0 * cu * cf);
-            ns[q] = n[q] - om * (n[q] - neq) + F;
-            if (!NOISE) {   // stored at once: fewer live registers
-                const int xd = wrap1(x + kCx[q], R.Lx), yd = wrap1(y + kCy[q], R.Ly), zd = wrap1(z + kCz[q], R.Lz);
-                pop_store(ndst, base + q * V + sidx(R, xd, yd, zd), q, ns[q]);
+            double v = n[q] - om * (n[q] - neq) + F;
+            if (NOISE) {
+                const bool lower = q > 0 && q % 2 == 0;   // the second of a pair
+                if (!lower) even = mrt_back<4, false>(am, q);
+                if (!lower && q > 0) odd = mrt_back<4, true>(am, q);
+                v += wq * (q == 0 ? even : (lower ? even - odd : even + odd));
             }
+            emit(q, v);   // stored at once: fewer live registers
         }
     }
-    if (NOISE) lb_mode_noise(R, sr.r, i, step, rho, ns);
-    if (NOISE || mrt) {
-#pragma unroll
-        for (int q = 0; q < 19; ++q) {
-            const int xd = wrap1(x + kCx[q], R.Lx), yd = wrap1(y + kCy[q], R.Ly), zd = wrap1(z + kCz[q], R.Lz);
-            pop_store(ndst, base + q * V + sidx(R, xd, yd, zd), q, ns[q]);
-        }
-    }
+    if (!rho_out) return;   // a later step of the call writes them
     rho_out[R.site_off + i] = rho;
     u_out[vo + i] = ux;
     u_out[vo + V + i] = uy;

@@ -17,6 +17,18 @@ struct U64x4 {
     uint64_t v[4];
 };
 
+// 128-bit product from four 32 x 32 + 64 bit multiply-adds (a multiply for the low half and one for
+// the high half take seven multiplications, which are most of a draw).
+__device__ __forceinline__ void mul_hilo(uint64_t a, uint64_t b, uint64_t &hi, uint64_t &lo)
+{
+    const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+    const uint64_t p = (uint64_t)a0 * b0;
+    const uint64_t q = (uint64_t)a1 * b0 + (p >> 32);
+    const uint64_t r = (uint64_t)a0 * b1 + (uint32_t)q;
+    lo = (r << 32) | (uint32_t)p;
+    hi = (uint64_t)a1 * b1 + (q >> 32) + (r >> 32);
+}
+
 __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
                                                uint64_t k1)
 {
@@ -24,8 +36,9 @@ __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_
     constexpr uint64_t kW0 = 0x9E3779B97F4A7C15ULL, kW1 = 0xBB67AE8584CAA73BULL;
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint64_t h0 = __umul64hi(kM0, c0), l0 = kM0 * c0;
-        const uint64_t h1 = __umul64hi(kM1, c2), l1 = kM1 * c2;
+        uint64_t h0, l0, h1, l1;
+        mul_hilo(kM0, c0, h0, l0);
+        mul_hilo(kM1, c2, h1, l1);
         const uint64_t n0 = h1 ^ c1 ^ k0, n2 = h0 ^ c3 ^ k1;
         c0 = n0;
         c1 = l1;
