@@ -34,9 +34,22 @@ __device__ __forceinline__ int wrapL(int v, int L)
 }
 
 __device__ __forceinline__ float silu(float y) { return y / (1.0f + __expf(-y)); }
+// silu and its derivative for |y| < 80: the quotient by a reciprocal and one correction of the remainder (the
+// scaling for overflow and underflow that a division adds is not needed there)
+__device__ __forceinline__ float silu80(float y)
+{
+    const float d = 1.0f + __expf(-y), r = __builtin_amdgcn_rcpf(d), q = y * r;
+    return __builtin_fmaf(__builtin_fmaf(-d, q, y), r, q);
+}
 __device__ __forceinline__ float silu_grad(float y)
 {
     const float s = 1.0f / (1.0f + __expf(-y));
+    return s * (1.0f + y * (1.0f - s));
+}
+__device__ __forceinline__ float silu_grad80(float y)
+{
+    const float d = 1.0f + __expf(-y), r = __builtin_amdgcn_rcpf(d);
+    const float s = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
     return s * (1.0f + y * (1.0f - s));
 }
 
@@ -60,8 +73,32 @@ __device__ __forceinline__ void give_gradient(const ConvGive &t, long long e, fl
 // banks), so the K loop reads only LDS; the next slab's loads are in flight while the
 // current one is multiplied.  Small slabs keep a 16x8x4 block of a 16-channel layer
 // under 40 KB of LDS, four blocks per CU.
+// Bound by instructions around the products: a wave of a 64^3, batch 2, 16 -> 16 layer issues 1450
+// vector instructions for 112 matrix ones, in the staging, the epilogue and their addresses
+// (2170 with divisions by runtime counts, full divisions in SiLU and an address per store), and
+// its LDS reads take a third of the 20.3 us (31.5 before).
 constexpr int kSlab = 4;
 constexpr int kSlabRow = kSlab * 32 + 8;
+
+// Units of a plane of the staged tile (8 channels of every halo site), a multiple of 16: a 16-byte
+// LDS read takes lanes of two 16-lane groups together (0-3 and 12-15 of one, 4-11 of the
+// next), and with planes a multiple of 256 bytes apart those two groups, which read two planes
+// at the same sites, share no bank (16x8x4 tile, 1080 units: 2.3M conflict cycles a launch,
+// with 1088 0.5M).
+template <int BX, int BY, int BZ>
+constexpr int conv_plane()
+{
+    return ((BX + 2) * (BY + 2) * (BZ + 2) + 15) / 16 * 16;
+}
+
+// e / d for the small counts of a tile (0 <= e, e d < 2^16), e / D with a constant: one multiply
+// and a shift.
+__device__ __forceinline__ int div_small(int e, int inv) { return (int)(__umul24((unsigned)e, (unsigned)inv) >> 16); }
+template <int D>
+__device__ __forceinline__ int div_by(int e)
+{
+    return div_small(e, 65536 / D + 1);
+}
 
 // periodic index for -L <= v < 2L (boxes at least one tile wide), general otherwise
 __device__ __forceinline__ int wrap_tile(int v, int L, bool small)
@@ -156,7 +193,7 @@ __device__ __forceinline__ floatv4 conv_load4(const ConvIn &in, long long e, int
     }
 }
 
-// A BX x BY x BZ tile with its one-site halo, unit-major xs[cip / 8][h][8] (forward): a
+// A BX x BY x BZ tile with its one-site halo, unit-major xs[cip / 8][h][8] (forward; planes conv_plane apart): a
 // work item is one halo site and eight consecutive channels, written to LDS as one
 // 16-byte unit; two items (16 loads) per thread are in flight at once.
 template <int BX, int BY, int BZ>
@@ -166,6 +203,7 @@ __device__ __forceinline__ void stage_halo_sm(const ConvIn &in, int b, int ci, i
     constexpr int GX = BX + 2, GY = BY + 2, GS = GX * GY * (BZ + 2);
     constexpr int BMAX = BX > BY ? (BX > BZ ? BX : BZ) : (BY > BZ ? BY : BZ);
     const bool small = L < BMAX;
+    constexpr int GP = conv_plane<BX, BY, BZ>();
     const int oct = cip / 8, total = GS * oct;
     for (int e0 = threadIdx.x; e0 < total; e0 += 256 * 2) {
         float v[2][8];
@@ -194,7 +232,7 @@ __device__ __forceinline__ void stage_halo_sm(const ConvIn &in, int b, int ci, i
                 bf16x8 pk;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) pk[j] = (__bf16)v[u][j];
-                *reinterpret_cast<bf16x8 *>(xs + ((e % oct) * GS + e / oct) * 8) = pk;
+                *reinterpret_cast<bf16x8 *>(xs + ((e % oct) * GP + e / oct) * 8) = pk;
             }
         }
     }
@@ -211,7 +249,9 @@ __device__ __forceinline__ void stage_halo_rows(const ConvIn &in, int b, int ci,
     constexpr int GX = BX + 2, GY = BY + 2, GZ = BZ + 2, GS = GX * GY * GZ;
     constexpr int NG = (BX + 8) / 4;   // float4 groups covering x in [x0 - 4, x0 + BX + 4)
     constexpr int U = MODE == CONV_IN_POOL ? 1 : 2;
-    const int oct = cip / 8, total = GY * GZ * NG * oct;
+    constexpr int GP = conv_plane<BX, BY, BZ>();
+    static_assert(GY * GZ * NG * 4 * 4 < 65536 && GS * 18 < 65536, "div_small");
+    const int oct = cip / 8, oinv = 65536 / oct + 1, total = GY * GZ * NG * oct;
     const long long stride = conv_stride<MODE>(L), base = (long long)b * ci * stride;
     for (int e0 = threadIdx.x; e0 < total; e0 += 256 * U) {
         floatv4 v[U][8];
@@ -219,9 +259,9 @@ __device__ __forceinline__ void stage_halo_rows(const ConvIn &in, int b, int ci,
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * 256;
             const bool ok = e < total;
-            const int c8 = e % oct, r = e / oct;
-            const int g = r % NG, row = r / NG;
-            const int hy = row % GY, hz = row / GY;
+            const int r = div_small(e, oinv), c8 = e - r * oct;
+            const int row = div_by<NG>(r), g = r - row * NG;
+            const int hz = div_by<GY>(row), hy = row - hz * GY;
             int xb = x0 - 4 + 4 * g;   // a multiple of 4; wraps as a whole group
             xb = xb < 0 ? xb + L : (xb >= L ? xb - L : xb);
             const int gy = wrap_tile(y0 + hy - 1, L, false), gz = wrap_tile(z0 + hz - 1, L, false);
@@ -240,8 +280,8 @@ __device__ __forceinline__ void stage_halo_rows(const ConvIn &in, int b, int ci,
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * 256;
             if (e < total) {
-                const int c8 = e % oct, r = e / oct;
-                const int g = r % NG, row = r / NG;
+                const int r = div_small(e, oinv), c8 = e - r * oct;
+                const int row = div_by<NG>(r), g = r - row * NG;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int hx = 4 * g + q - 3;   // halo x position of this site
@@ -249,7 +289,7 @@ __device__ __forceinline__ void stage_halo_rows(const ConvIn &in, int b, int ci,
                         bf16x8 pk;
 #pragma unroll
                         for (int j = 0; j < 8; ++j) pk[j] = (__bf16)v[u][j][q];
-                        *reinterpret_cast<bf16x8 *>(xs + (c8 * GS + row * GX + hx) * 8) = pk;
+                        *reinterpret_cast<bf16x8 *>(xs + (c8 * GP + row * GX + hx) * 8) = pk;
                     }
                 }
             }
@@ -269,7 +309,9 @@ __device__ __forceinline__ void stage_halo_packed(const __bf16 *__restrict__ xp,
     constexpr int BMAX = BX > BY ? (BX > BZ ? BX : BZ) : (BY > BZ ? BY : BZ);
     constexpr int U = 8;
     const bool small = L < BMAX;
-    const int oct = cip / 8, total = GS * oct;
+    constexpr int GP = conv_plane<BX, BY, BZ>();
+    const int oct = cip / 8, oinv = 65536 / oct + 1, total = GS * oct;
+    static_assert(GS * 4 * 4 < 65536 && GS * GX < 65536, "div_small");
     const __bf16 *base = xp + (long long)b * L * L * L * cip;
     for (int e0 = threadIdx.x; e0 < total; e0 += 256 * U) {
         bf16x8 v[U];
@@ -277,18 +319,19 @@ __device__ __forceinline__ void stage_halo_packed(const __bf16 *__restrict__ xp,
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * 256;
             if (e < total) {
-                const int c8 = e % oct, h = e / oct;
-                const int hx = h % GX, hy = (h / GX) % GY, hz = h / (GX * GY);
+                const int h = div_small(e, oinv), c8 = e - h * oct;
+                const int row = div_by<GX>(h), hx = h - row * GX, hz = div_by<GY>(row), hy = row - hz * GY;
                 const int gx = wrap_tile(x0 + hx - 1, L, small), gy = wrap_tile(y0 + hy - 1, L, small),
                           gz = wrap_tile(z0 + hz - 1, L, small);
-                const long long site = gx + (long long)L * (gy + (long long)L * gz);
-                v[u] = *reinterpret_cast<const bf16x8 *>(base + site * cip + 8 * c8);
+                const unsigned long long site = (unsigned long long)((unsigned)gy + (unsigned)L * gz) * (unsigned)L + (unsigned)gx;
+                v[u] = *reinterpret_cast<const bf16x8 *>(base + site * (unsigned)cip + 8 * c8);
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * 256;
-            if (e < total) *reinterpret_cast<bf16x8 *>(xs + ((e % oct) * GS + e / oct) * 8) = v[u];
+            const int h = div_small(e, oinv), c8 = e - h * oct;
+            if (e < total) *reinterpret_cast<bf16x8 *>(xs + (c8 * GP + h) * 8) = v[u];
         }
     }
 }
@@ -298,14 +341,14 @@ constexpr int kMaxKGroups = 27 * 32 / 8 + 4;   // K rows / 8 for cip <= 32, roun
 template <int BX, int BY, int BZ>
 constexpr size_t conv_fwd_lds_t(int cip, int cop)
 {
-    return (size_t)((BX + 2) * (BY + 2) * (BZ + 2) * cip + cop * kSlabRow) * sizeof(__bf16) +
+    return (size_t)(conv_plane<BX, BY, BZ>() * cip + cop * kSlabRow) * sizeof(__bf16) +
            kMaxKGroups * sizeof(int);
 }
 
 // Block: a BX x BY x BZ tile of one sample; its 16-site MFMA column tiles are dealt to
 // the four waves (NTW each), each with NM = cop / 16 (1 or 2) 16-channel output tiles.
 // GIVE: the data gradient, which adds to ConvOut::give instead of writing Y, A or Ap (the sum and
-// the derivative of the activation in the epilogue cost 3 us at 64^3, batch 2, 8 -> 8 channels,
+// the derivative of the activation in the epilogue cost 2 us at 64^3, batch 2, 8 -> 8 channels,
 // the passes over memory they replace 20).
 // Four blocks of the 16-channel 16x8x4 tile per CU (LDS) need at most 128 registers.
 template <int BX, int BY, int BZ, int NM, bool GIVE>
@@ -313,13 +356,13 @@ __global__ __launch_bounds__(256, BX == 16 && NM == 1 ? 4 : 1) void k_conv_fwd(C
                                                    int co, int cop, const float *__restrict__ bias, ConvOut out, int L,
                                                    int tiles_x, int tiles_y, int tiles_per_sample)
 {
-    constexpr int BS = BX * BY * BZ, GX = BX + 2, GY = BY + 2, GS = GX * GY * (BZ + 2);
+    constexpr int BS = BX * BY * BZ, GX = BX + 2, GY = BY + 2, GP = conv_plane<BX, BY, BZ>();
     constexpr int NTW = BS / 64;   // column tiles per wave
     constexpr int NPRE = (NM * 16 * kSlab * 4 + 255) / 256;   // weight vectors per thread and slab
     static_assert(BS % 64 == 0 && BX % 8 == 0, "tile shape");
     extern __shared__ __align__(16) unsigned char smem[];
-    __bf16 *xs = reinterpret_cast<__bf16 *>(smem);   // [cip / 8][GS][8]
-    __bf16 *ws = xs + GS * cip;                       // [cop][kSlabRow]
+    __bf16 *xs = reinterpret_cast<__bf16 *>(smem);   // [cip / 8][GP][8]
+    __bf16 *ws = xs + GP * cip;                       // [cop][kSlabRow]
     int *koff = reinterpret_cast<int *>(ws + cop * kSlabRow);   // [kp / 8]
     const int bid = plan_block();   // neighbouring tiles on one XCD
     const int b = bid / tiles_per_sample;
@@ -368,7 +411,7 @@ __global__ __launch_bounds__(256, BX == 16 && NM == 1 ? 4 : 1) void k_conv_fwd(C
         int k = (8 * g) / cip;
         const int c0 = 8 * g - k * cip;
         if (k > 26) k = 13;
-        koff[g] = ((((k / 9) - 1) * GX * GY + (((k / 3) % 3) - 1) * GX + ((k % 3) - 1)) + (c0 / 8) * GS) * 8;
+        koff[g] = ((((k / 9) - 1) * GX * GY + (((k / 3) % 3) - 1) * GX + ((k % 3) - 1)) + (c0 / 8) * GP) * 8;
     }
     if (in.mode == CONV_IN_PACKED)
         stage_halo_packed<BX, BY, BZ>(in.xp, b, cip, L, x0, y0, z0, xs);
@@ -422,6 +465,7 @@ __global__ __launch_bounds__(256, BX == 16 && NM == 1 ? 4 : 1) void k_conv_fwd(C
     }
     if constexpr (GIVE) {   // a batch of sites' loads in flight before the first is needed
         constexpr int QB = NTW < 4 / NM ? NTW : 4 / NM;
+        const long long first = ((long long)b * co + 4 * grp) * V;
 #pragma unroll
         for (int d = 0; d < 2; ++d) {
             const ConvGive to = out.give[d];
@@ -429,13 +473,13 @@ __global__ __launch_bounds__(256, BX == 16 && NM == 1 ? 4 : 1) void k_conv_fwd(C
 #pragma unroll
             for (int q0 = 0; q0 < NTW; q0 += QB) {
                 long long at[QB];
-                float old[QB][NM][4], pre[QB][NM][4];
+                float old[QB][NM][4], pre[QB][NM][4], top = 0.0f;
 #pragma unroll
                 for (int q = 0; q < QB; ++q) {
                     const int n = (wave * NTW + q0 + q) * 16 + col;
                     const int gx = x0 + n % BX, gy = y0 + (n / BX) % BY, gz = z0 + n / (BX * BY);
                     at[q] = gx < L && gy < L && gz < L
-                                ? (long long)b * co * V + gx + (long long)L * (gy + (long long)L * gz)
+                                ? (long long)((unsigned long long)((unsigned)gy + (unsigned)L * gz) * (unsigned)L + (unsigned)gx)
                                 : -1;
                 }
 #pragma unroll
@@ -444,64 +488,92 @@ __global__ __launch_bounds__(256, BX == 16 && NM == 1 ? 4 : 1) void k_conv_fwd(C
                     for (int m = 0; m < NM; ++m)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const int o = m * 16 + 4 * grp + i;
                             old[q][m][i] = pre[q][m][i] = 0.0f;
-                            if (at[q] >= 0 && o < co) {
-                                if (to.add) old[q][m][i] = to.dst[at[q] + o * V];
-                                if (to.Y) pre[q][m][i] = to.Y[at[q] + o * V];
+                            if (at[q] >= 0 && m * 16 + 4 * grp + i < co) {
+                                if (to.add) old[q][m][i] = to.dst[first + (m * 16 + i) * V + at[q]];
+                                if (to.Y) pre[q][m][i] = to.Y[first + (m * 16 + i) * V + at[q]];
                             }
+                            top = fmaxf(top, fabsf(pre[q][m][i]));
                         }
+                auto write = [&](auto grad) {
 #pragma unroll
-                for (int q = 0; q < QB; ++q)
+                    for (int q = 0; q < QB; ++q)
 #pragma unroll
-                    for (int m = 0; m < NM; ++m)
+                        for (int m = 0; m < NM; ++m)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int o = m * 16 + 4 * grp + i;
-                            float v = acc[q0 + q][m][i];
-                            if (to.add) v = old[q][m][i] + v;
-                            if (to.Y) v *= silu_grad(pre[q][m][i]);
-                            if (at[q] >= 0 && o < co) to.dst[at[q] + o * V] = v;
-                        }
+                            for (int i = 0; i < 4; ++i) {
+                                float v = acc[q0 + q][m][i];
+                                if (to.add) v = old[q][m][i] + v;
+                                if (to.Y) v *= grad(pre[q][m][i]);
+                                if (at[q] >= 0 && m * 16 + 4 * grp + i < co)
+                                    to.dst[first + (m * 16 + i) * V + at[q]] = v;
+                            }
+                };
+                if (__ballot(!(top < 80.0f)) == 0) write([](float y) { return silu_grad80(y); });
+                else write([](float y) { return silu_grad(y); });
             }
         }
         return;
     }
     // epilogue: lane holds rows 4 grp + i of each M tile, column = its site
-    float *Yb = out.Y ? out.Y + (long long)b * co * V : nullptr;
-    float *Ab = out.A ? out.A + (long long)b * co * V : nullptr;
-    const int cpk = (co + 7) & ~7;   // channel stride of the packed activation
-    __bf16 *Pb = out.Ap ? out.Ap + (long long)b * V * cpk : nullptr;
+    float bo[NM][4], top = 0.0f;
 #pragma unroll
-    for (int q = 0; q < NTW; ++q) {
-        const int n = (wave * NTW + q) * 16 + col;
-        const int tx = n % BX, ty = (n / BX) % BY, tz = n / (BX * BY);
-        const int gx = x0 + tx, gy = y0 + ty, gz = z0 + tz;
-        if (gx >= L || gy >= L || gz >= L) continue;
-        const long long site = gx + (long long)L * (gy + (long long)L * gz);
+    for (int m = 0; m < NM; ++m)
 #pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            const int o0 = m * 16 + 4 * grp;
-            if (Pb && o0 < cpk) {   // four consecutive channels of the site: one 8-byte store
-                bf16x4 pk;
+        for (int i = 0; i < 4; ++i) {
+            const int o = m * 16 + 4 * grp + i;
+            bo[m][i] = bias && o < co ? bias[o] : 0.0f;
+        }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int o = o0 + i;
-                    pk[i] = (__bf16)(o < co ? silu(acc[q][m][i] + (bias ? bias[o] : 0.0f)) : 0.0f);
-                }
-                *reinterpret_cast<bf16x4 *>(Pb + site * cpk + o0) = pk;
-            }
+    for (int q = 0; q < NTW; ++q)
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int o = o0 + i;
-                if (o >= co) continue;
-                float y = acc[q][m][i] + (bias ? bias[o] : 0.0f);
-                if (Ab) Ab[(long long)o * V + site] = silu(y);
-                if (out.shift) y = (y - out.shift[o]) * out.scale[o];
-                if (Yb) Yb[(long long)o * V + site] = y;
+                acc[q][m][i] += bo[m][i];
+                top = fmaxf(top, fabsf(acc[q][m][i]));
+            }
+    const int cpk = (co + 7) & ~7;   // channel stride of the packed activation
+    __bf16 *Pb = out.Ap ? out.Ap + (long long)b * V * cpk + 4 * grp : nullptr;
+    const long long first = ((long long)b * co + 4 * grp) * V;
+    float *Yb = out.Y ? out.Y + first : nullptr, *Ab = out.A ? out.A + first : nullptr;
+    auto write = [&](auto act) {
+#pragma unroll
+        for (int q = 0; q < NTW; ++q) {
+            const int n = (wave * NTW + q) * 16 + col;
+            const int gx = x0 + n % BX, gy = y0 + (n / BX) % BY, gz = z0 + n / (BX * BY);
+            if (gx >= L || gy >= L || gz >= L) continue;
+            const unsigned long long site = (unsigned long long)((unsigned)gy + (unsigned)L * gz) * (unsigned)L + (unsigned)gx;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const int o0 = m * 16 + 4 * grp;
+                floatx4 a = acc[q][m];
+                if (Pb || Ab) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) a[i] = act(a[i]);
+                }
+                if (Pb && o0 < cpk) {   // four consecutive channels of the site: one 8-byte store
+                    bf16x4 pk;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) pk[i] = (__bf16)(o0 + i < co ? a[i] : 0.0f);
+                    *reinterpret_cast<bf16x4 *>(Pb + site * (unsigned)cpk + m * 16) = pk;
+                }
+                if (Yb || Ab) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (o0 + i >= co) continue;
+                        if (Ab) Ab[(m * 16 + i) * V + site] = a[i];
+                        float y = acc[q][m][i];
+                        if (out.shift) y = (y - out.shift[o0 + i]) * out.scale[o0 + i];
+                        if (Yb) Yb[(m * 16 + i) * V + site] = y;
+                    }
+                }
             }
         }
-    }
+    };
+    // infinities and large values, which silu80 does not take, are rare: one test per wave
+    if (__ballot(!(top < 80.0f)) == 0) write([](float y) { return silu80(y); });
+    else write([](float y) { return silu(y); });
 }
 
 // ---------------------------------------------------------------- weight gradient
