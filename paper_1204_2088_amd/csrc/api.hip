@@ -324,6 +324,20 @@ int run_seq(hsf_ctx *c, int kind, F &&body)
     return HSF_OK;
 }
 
+// Whether the kernels can use a caller's buffer themselves: memory of the current device, aligned
+// for the widest loads and stores.  Other device buffers go through a copy.
+bool in_place(const void *p, int where)
+{
+    if (where != HSF_DEVICE || !p || reinterpret_cast<uintptr_t>(p) % 16) return false;
+    hipPointerAttribute_t a;
+    int dev = -1;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && a.device == dev;
+}
+
 template <typename real>
 PropBufs<real> bufs(hsf_ctx *c)
 {
@@ -918,23 +932,38 @@ int run_resident(hsf_ctx *c, int kind, double *out, double tol, int max_iter, in
 }
 
 // One evaluation of the density functional at the current fields, with phibar from the
-// current densities, into eval_out (and, with `out`, copied to the caller); ln Q, phibar and
-// <exp(-w_S)> stay in the replica states.  An evaluation whose propagators left the
-// floating-point range is repeated with the per-step scales it adapted (at most three more
-// times).  The solvent's density and the copy are issued with the sweeps, before the
-// states are read, so a call waits for the stream once.
+// current densities, into eval_out or the caller's `out`; ln Q, phibar and <exp(-w_S)> stay in
+// the replica states.  An evaluation whose propagators left the floating-point range is
+// repeated with the per-step scales it adapted (at most three more times).  The solvent's
+// density and the copy are issued with the sweeps, before the states are read, so a call waits
+// for the stream once.
+//
+// A caller's device buffer is written by the density launch itself.  The captured sequence
+// writes eval_out, so the launches are then issued one by one, which suits boxes whose
+// kernels outlast their launches: kDirectSites sites and more (the copy and the gap before it
+// against the sequence: 128^3 FP32 279 -> 256 us, two 64^3 139 -> 133, 48^3 84 -> 82; 32^3, with
+// more and shorter kernels, takes 91 us launched one by one against 76).
+constexpr long long kDirectSites = 1 << 16;
+
 int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, int where = HSF_DEVICE)
 {
+    const bool res = use_resident(c), direct = (res || c->T >= kDirectSites) && in_place(out, where);
+    double *dst = direct ? out : c->eval_out;
+    auto sequence = [&] {
+        // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
+        target_setup(c, 0.0, 0, c->ch.nsp == 3);
+        run_eval_any(c, 0, 0, dst, nullptr, 1);
+        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch, sweep_plan(c),
+                          c->partG, 0.0, 0, c->st_hd);
+    };
     for (int attempt = 0; attempt < (check_range ? 4 : 1); ++attempt) {
-        int rc0 = use_resident(c) ? run_resident(c, RES_EVAL, c->eval_out, 0.0, 0, 1) : run_seq(c, hsf_ctx::GK_EVAL, [&] {
-            // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
-            target_setup(c, 0.0, 0, c->ch.nsp == 3);
-            run_eval_any(c, 0, 0, c->eval_out, nullptr, 1);
-            launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch,
-                              sweep_plan(c), c->partG, 0.0, 0, c->st_hd);
-        });
+        int rc0 = HSF_OK;
+        if (res) rc0 = run_resident(c, RES_EVAL, dst, 0.0, 0, 1);
+        else if (direct) sequence();
+        else rc0 = run_seq(c, hsf_ctx::GK_EVAL, sequence);
         if (rc0) return rc0;
-        if (out && (rc0 = copy_out(c, out, c->eval_out, (size_t)c->ch.nsp * c->T, where))) return rc0;
+        HIPCHK(c, hipGetLastError());
+        if (out && !direct && (rc0 = copy_out(c, out, c->eval_out, (size_t)c->ch.nsp * c->T, where))) return rc0;
         if (!check_range) break;
         if ((rc0 = read_status(c))) return rc0;
         bool bad = false;
@@ -1519,16 +1548,14 @@ int hsf_invert(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats 
 int hsf_mu_force(hsf_ctx *c, double *mu, double *force, int where)
 {
     if (!c) return HSF_EINVAL;
-    // device buffers are written by the kernels themselves
-    const bool direct = where == HSF_DEVICE;
-    double *m = direct && mu ? mu : c->mu, *f = direct && force ? force : c->force;
+    const bool mu_in = in_place(mu, where), force_in = in_place(force, where);
+    double *m = mu_in ? mu : c->mu, *f = force_in ? force : c->force;
     launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->phi, c->w, m);
     launch_force(c->stream, c->plan, c->rep_d, c->ch, c->phi, m, f);
     HIPCHK(c, hipGetLastError());
-    if (direct) return HSF_OK;
     int rc = HSF_OK;
-    if (mu) rc = copy_out(c, mu, c->mu, (size_t)c->ch.nsp * c->T, where);
-    if (rc == HSF_OK && force) rc = copy_out(c, force, c->force, (size_t)3 * c->T, where);
+    if (mu && !mu_in) rc = copy_out(c, mu, c->mu, (size_t)c->ch.nsp * c->T, where);
+    if (rc == HSF_OK && force && !force_in) rc = copy_out(c, force, c->force, (size_t)3 * c->T, where);
     return rc;
 }
 
@@ -1570,8 +1597,8 @@ int hsf_lb_advance(hsf_ctx *c, int n_steps, const double *force, int where)
 {
     if (!c || n_steps < 0) return HSF_EINVAL;
     const double *f = nullptr;
-    if (force && where == HSF_DEVICE) {
-        f = force;   // read in place, on the context's stream
+    if (in_place(force, where)) {
+        f = force;
     } else if (force) {
         int rc = copy_in(c, c->uin, force, (size_t)3 * c->T, where);
         if (rc) return rc;
@@ -1603,16 +1630,14 @@ int hsf_get_flow(hsf_ctx *c, double *rho, double *u, int where)
 int hsf_cd_advance(hsf_ctx *c, const double *mu, const double *u, int where)
 {
     if (!c || !mu) return HSF_EINVAL;
-    // device buffers are read in place, on the context's stream
     const double *mm = mu, *uu = u;
-    if (where != HSF_DEVICE) {
-        int rc = copy_in(c, c->mu, mu, (size_t)c->ch.nsp * c->T, where);
-        if (rc) return rc;
+    if (!in_place(mu, where)) {
+        if (int rc = copy_in(c, c->mu, mu, (size_t)c->ch.nsp * c->T, where)) return rc;
         mm = c->mu;
-        if (u) {
-            if ((rc = copy_in(c, c->uin, u, (size_t)3 * c->T, where))) return rc;
-            uu = c->uin;
-        }
+    }
+    if (u && !in_place(u, where)) {
+        if (int rc = copy_in(c, c->uin, u, (size_t)3 * c->T, where)) return rc;
+        uu = c->uin;
     }
     launch_cd(c->stream, c->cdplan, c->col_p, c->plan, c->rep_d, c->ch, c->phi, mm, uu, c->phi_tmp,
               (c->noise & HSF_NOISE_CD) ? c->noise_flux : nullptr, c->noise_step);

@@ -1,0 +1,75 @@
+"""Device buffers that the kernels read and write themselves, and those that go through a copy
+because they are not aligned to 16 bytes: the same numbers as through host arrays, bit for bit,
+and nothing written beside the output."""
+import numpy as np
+import pytest
+
+from paper_1204_2088_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hsf():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1204_2088_amd import hsf as H
+    H.load()
+    return H
+
+
+def slot(n, off, fill=None):
+    """A device view of n doubles, off doubles from a 256-byte boundary, and its whole buffer."""
+    import torch
+    buf = torch.full((n + 4,), 7.0, dtype=torch.float64, device="cuda")
+    v = buf[off:off + n]
+    if fill is not None:
+        v.copy_(torch.from_numpy(np.ascontiguousarray(fill).ravel()))
+    return v, buf
+
+
+def check(v, buf, off, ref):
+    got = v.cpu().numpy()
+    assert np.array_equal(got, np.asarray(ref).ravel())
+    rest = buf.cpu().numpy()
+    assert np.all(rest[:off] == 7.0) and np.all(rest[off + got.size:] == 7.0)
+
+
+@pytest.mark.parametrize("off", [0, 1, 2])
+# resident; a captured sequence; just below and above the size of direct launches
+@pytest.mark.parametrize("L", [(16, 15, 12), (24, 20, 18), (40, 40, 40), (42, 40, 40)])
+def test_device_buffers(hsf, L, off):
+    import torch
+    wl = W.Workload("place", L, W.chain(3, 4), True, W.chi_matrix(ab=15 / 7, bs=10 / 7), tau=1.0, noise=0.02, seed=3,
+                    phi_p=0.3, precision="fp32")
+    T = int(np.prod(L))
+    rng = np.random.Generator(np.random.PCG64(2))
+    w = 0.3 * rng.standard_normal((3,) + wl.shape)
+    phi = W.initial_composition(wl)
+    res = []
+    for dev in (False, True):
+        ctx = hsf.Context(wl, stream=torch.cuda.current_stream())
+        ctx.set_densities(phi)
+        ctx.set_fields(w)
+        if not dev:
+            out, q = ctx.evaluate()
+            mu, f = ctx.mu_force()
+            u = 1e-3 * rng.standard_normal(3 * T)
+            ctx.cd_advance(mu, u)
+            ctx.lb_advance(2, f)
+            res = [np.array(v) for v in (out, q, mu, f, u, ctx.get_densities(), ctx.get_flow()[1])]
+        else:
+            (o, ob), (m, mb), (g, gb) = slot(3 * T, off), slot(3 * T, off), slot(3 * T, off)
+            _, q = ctx.evaluate(out=o)
+            check(o, ob, off, res[0])
+            assert np.array_equal(q, res[1])
+            ctx.mu_force(m, g)
+            check(m, mb, off, res[2])
+            check(g, gb, off, res[3])
+            u, _ = slot(3 * T, off, res[4])
+            ctx.cd_advance(m, u)
+            ctx.lb_advance(2, g)
+            assert np.array_equal(np.asarray(ctx.get_densities()).ravel(), res[5].ravel())
+            assert np.array_equal(np.asarray(ctx.get_flow()[1]).ravel(), res[6].ravel())
+        ctx.close()
