@@ -572,10 +572,11 @@ void run_eval_stream(hsf_ctx *c, int use_alpha, int final_mode, double *out, con
 }
 
 // Row tilings (K = -tile.k >= 2 steps per launch): the field factors in a launch of their own
-// (both halves of the first sweep launch read them), the sweeps (rows_schedule), and step 1
+// (both halves of the first sweep launch read them; have_exp: the target statistics have
+// written them), the sweeps (rows_schedule), and step 1
 // in the one-step density launch.
 template <typename real>
-void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums)
+void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums, bool have_exp)
 {
     PropBufs<real> b = bufs<real>(c);
     const TileCfg tile = rows_tile(c, sizeof(real) == sizeof(double));
@@ -583,7 +584,7 @@ void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const
     const int N = c->ch.N, K = -tile.k;
     const bool alt = sizeof(real) == sizeof(double) && c->precision == HSF_FP32;   // refinement phase
     real *Gf[2] = {(real *)(alt ? c->Gf64[0] : c->Gf0), (real *)(alt ? c->Gf64[1] : c->Gf1)};
-    {
+    if (!have_exp) {
         Timed t(c, HSF_K_PREP);
         launch_field_exp<real>(c->stream, c->plan, c->rep_d, c->st_d, c->ch, c->w, c->d, use_alpha, b.E, t.a, t.b);
     }
@@ -608,10 +609,11 @@ void run_eval_rows(hsf_ctx *c, int use_alpha, int final_mode, double *out, const
 }
 
 template <typename real>
-void run_eval(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums)
+void run_eval(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums, bool have_exp)
 {
     if (tile_is_stream(c->tile)) return run_eval_stream<real>(c, use_alpha, final_mode, out, d, sums);
-    if (tile_is_rows(c->tile) && c->ch.N >= 2) return run_eval_rows<real>(c, use_alpha, final_mode, out, d, sums);
+    if (tile_is_rows(c->tile) && c->ch.N >= 2)
+        return run_eval_rows<real>(c, use_alpha, final_mode, out, d, sums, have_exp);
     if (c->tile.k < 0 && c->ch.N >= 2) return run_eval_paired<real>(c, use_alpha, final_mode, out, d, sums);
     PropBufs<real> b = bufs<real>(c);
     const int N = c->ch.N, K = std::max(1, c->dtile.k);
@@ -644,20 +646,29 @@ void run_eval(hsf_ctx *c, int use_alpha, int final_mode, double *out, const doub
 }
 
 // sums: also produce the per-step propagator sums that update the FP32 scales
-void run_eval_any(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums)
+void run_eval_any(hsf_ctx *c, int use_alpha, int final_mode, double *out, const double *d, int sums,
+                  bool have_exp = false)
 {
     if (c->precision == HSF_FP32 && !c->eval64)
-        run_eval<float>(c, use_alpha, final_mode, out, d, sums);
+        run_eval<float>(c, use_alpha, final_mode, out, d, sums, have_exp);
     else
-        run_eval<double>(c, use_alpha, final_mode, out, d, sums);
+        run_eval<double>(c, use_alpha, final_mode, out, d, sums, have_exp);
 }
 
-// solvent: also <exp(-w_S)> (evaluations of solutions)
-void target_setup(hsf_ctx *c, double tol, int max_iter, bool solvent = false)
+// solvent: also <exp(-w_S)> (evaluations of solutions).  with_exp: also the field factors, where
+// the sweeps take them from a launch of their own; returns whether they were written.
+bool target_setup(hsf_ctx *c, double tol, int max_iter, bool solvent = false, bool with_exp = false)
 {
-    launch_target_stats(c->stream, c->cplan, c->rep_d, c->st_d, c->ch, c->phi, c->w, solvent, c->part);
+    const bool exps = with_exp && tile_is_rows(c->tile) && c->ch.N >= 2;
+    if (c->precision == HSF_FP32 && !c->eval64)
+        launch_target_stats<float>(c->stream, c->cplan, c->rep_d, c->ch, c->phi, c->w, solvent, c->part,
+                                   exps ? bufs<float>(c).E : nullptr);
+    else
+        launch_target_stats<double>(c->stream, c->cplan, c->rep_d, c->ch, c->phi, c->w, solvent, c->part,
+                                    exps ? bufs<double>(c).E : nullptr);
     launch_reduce_ctl(c->stream, c->n_rep, c->cplan, c->st_d, c->rep_d, c->part,
                       solvent ? PH_TARGET_SOLVENT : PH_TARGET, c->ch, c->cplan, c->partG, tol, max_iter, c->st_hd);
+    return exps;
 }
 
 // Starting fields of an inversion (the warm start), before the gauge is fixed.
@@ -951,8 +962,8 @@ int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, in
     double *dst = direct ? out : c->eval_out;
     auto sequence = [&] {
         // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
-        target_setup(c, 0.0, 0, c->ch.nsp == 3);
-        run_eval_any(c, 0, 0, dst, nullptr, 1);
+        const bool exps = target_setup(c, 0.0, 0, c->ch.nsp == 3, true);
+        run_eval_any(c, 0, 0, dst, nullptr, 1, exps);
         launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch, sweep_plan(c),
                           c->partG, 0.0, 0, c->st_hd);
     };

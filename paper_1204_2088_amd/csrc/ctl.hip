@@ -99,7 +99,7 @@ __device__ void reduce_and_control(RepState &S, int r, const int *__restrict__ b
     }
     // Each row is split into contiguous parts of the replica's blocks, one wavefront per
     // part (as many parts as the wavefronts allow, the same for every row of the phase);
-    // within a part the lanes stride over the blocks and a fixed shuffle tree adds them,
+    // within a part the lanes stride over the blocks and a fixed order adds them,
     // then the parts are added in order: the order of additions is fixed, so results are
     // reproducible.
     constexpr int kWaves = kCtlBlock / 64;
@@ -125,8 +125,7 @@ __device__ void reduce_and_control(RepState &S, int r, const int *__restrict__ b
 #pragma unroll 8
                 for (int b = lo + lane; b < hi; b += 64) v += base[b];
             }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+            v = wave_sum(v);
             if (lane == 0) psum[wid] = v;
         }
         __syncthreads();
@@ -158,18 +157,20 @@ void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, co
 // |phi^t_A|^2, |phi^t_B|^2, sum of w_A and of w_B, and (SOLVENT) of exp(-w_S).  One read of
 // the arrays; a block takes p.span sites, so that its reduction of seven sums and the
 // control kernel's pass over the blocks are paid once per span (128^3: 30.5 us for 8192
-// blocks of 256 sites and 11 us in the control kernel).
-template <bool SOLVENT>
+// blocks of 256 sites and 11 us in the control kernel).  E (or null): also the polymers' field
+// factors exp(-w), as launch_field_exp writes them, from the same read of w.
+template <bool SOLVENT, typename real>
 __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__ blk_rep,
                                                          const int *__restrict__ blk_first,
                                                          const Rep *__restrict__ rep, int nsp, int span,
                                                          const double *__restrict__ phit,
-                                                         const double *__restrict__ w, double *__restrict__ part)
+                                                         const double *__restrict__ w, double *__restrict__ part,
+                                                         real *__restrict__ E)
 {
     const SiteRef sr = span_ref(blk_rep, blk_first, span);
     const Rep &R = rep[sr.r];
     const long long V = R.V;
-    const long long fo = off_field(R, nsp);
+    const long long fo = off_field(R, nsp), po = off_poly(R);
     constexpr int NV = SOLVENT ? 7 : 6;
     double v[NV];
 #pragma unroll
@@ -183,8 +184,13 @@ __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__
         if (nsp == 3) v[1] += phit[fo + 2 * V + i];
         v[2] += a * a;
         v[3] += bb * bb;
-        v[4] += w[fo + i];
-        v[5] += w[fo + V + i];
+        const double wa = w[fo + i], wb = w[fo + V + i];
+        v[4] += wa;
+        v[5] += wb;
+        if (E) {
+            E[po + i] = (real)exp(-wa);
+            E[po + V + i] = (real)exp(-wb);
+        }
         if (SOLVENT) v[NV - 1] += exp(-w[fo + 2 * V + i]);
     }
     block_sums(v);
@@ -192,12 +198,18 @@ __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__
         for (int q = 0; q < NV; ++q) part[(long long)plan_block() * kNQ + q] = v[q];
 }
 
-void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, RepState *, Chain ch,
-                         const double *phit, const double *w, bool solvent, double *part)
+template <typename real>
+void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phit, const double *w,
+                         bool solvent, double *part, real *E)
 {
-    hipLaunchKernelGGL(solvent ? k_target_stats<true> : k_target_stats<false>, dim3(p.nblocks), dim3(kBlock), 0, s,
-                       p.blk_rep, p.blk_first, rep, ch.nsp, p.span, phit, w, part);
+    auto kern = solvent ? k_target_stats<true, real> : k_target_stats<false, real>;
+    hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, ch.nsp, p.span, phit, w,
+                       part, E);
 }
+template void launch_target_stats<float>(hipStream_t, const Plan &, const Rep *, Chain, const double *, const double *,
+                                         bool, double *, float *);
+template void launch_target_stats<double>(hipStream_t, const Plan &, const Rep *, Chain, const double *, const double *,
+                                          bool, double *, double *);
 
 // Local ideal-gas starting guess w_I = -ln phi_I (the constant -ln <phi_I> is removed
 // by the gauge shift that follows).

@@ -124,14 +124,39 @@ __device__ __forceinline__ SiteRef span_ref(const int *blk_rep, const int *blk_f
     return s;
 }
 
-// Deterministic block sum (fixed shuffle tree inside each 64-lane wavefront, then
+// Sum over a full wavefront, in every lane: row shifts by 1, 2, 4, 8, then row broadcasts (a fixed
+// order).  Lane moves between vector registers, where a shuffle goes through LDS twice per
+// step: six dependent LDS round trips were much of a short reduction kernel (with the field
+// factors fused into the target statistics, evaluations of two 64^3 boxes 133 -> 121 us, 128^3
+// 256 -> 249, all FP32).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return v + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3; lane 63 holds the sum
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Deterministic block sum (wave_sum in each 64-lane wavefront, then
 // the four wavefront sums in order).  Every thread must call it; the result is
 // valid in thread 0.
 __device__ __forceinline__ double block_sum(double v)
 {
     __shared__ double ws[kBlock / 64];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    v = wave_sum(v);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) ws[wid] = v;
     __syncthreads();
@@ -144,17 +169,15 @@ __device__ __forceinline__ double block_sum(double v)
     return t;
 }
 
-// Block sums of NV values at once, each bit for bit block_sum's (the same shuffle tree
-// and the same order over the wavefronts), with one barrier pair for all of them.  Every
+// Block sums of NV values at once, each bit for bit block_sum's (the same order
+// inside and over the wavefronts), with one barrier pair for all of them.  Every
 // thread must call it; the results are valid in thread 0.
 template <int NV>
 __device__ __forceinline__ void block_sums(double (&v)[NV])
 {
     __shared__ double ws[NV][kBlock / 64];
 #pragma unroll
-    for (int q = 0; q < NV; ++q)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_down(v[q], o, 64);
+    for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0)
 #pragma unroll

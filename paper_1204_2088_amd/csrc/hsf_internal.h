@@ -131,8 +131,9 @@ void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, co
                        int max_iter, RepState *mirror);
 
 // solvent: also the sum of exp(-w_S) (for PH_TARGET_SOLVENT)
-void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,
-                         const double *phit, const double *w, bool solvent, double *part);
+template <typename real>
+void launch_target_stats(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phit, const double *w,
+                         bool solvent, double *part, real *E);
 void launch_local_guess(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phit,
                         double *w, double *part);
 void launch_init_fields(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, Chain ch,

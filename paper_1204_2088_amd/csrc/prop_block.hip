@@ -774,8 +774,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
             const double *row = partG + (long long)(N - 1) * nblocks;
 #pragma unroll 8
             for (int q = b0 + (int)threadIdx.x; q < b1; q += 64) v += row[q];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+            v = wave_sum(v);
             if (threadIdx.x == 0) {
                 double q, lq;
                 bool bad;
@@ -823,8 +822,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(r
             const double *row = partG + (long long)(N - 1) * nblocks;
 #pragma unroll 8
             for (int q = b0 + (int)threadIdx.x; q < b1; q += 64) v += row[q];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+            v = wave_sum(v);
             if (threadIdx.x == 0) {
                 double q, lq;
                 bool bad;

@@ -262,11 +262,6 @@ __device__ __forceinline__ void rows_half(const RowsTile<real, P, K, CY, CZ> &t,
     const int s_last = s1 + h.n - 1;
     if (!sums && s_last != N) return;
     __shared__ double ws[NY][K + 3];
-    auto wave_sum = [](double x) {
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) x += __shfl_down(x, d, 64);
-        return x;
-    };
 #pragma unroll
     for (int k = 0; k <= K; ++k) {
         const double x = wave_sum(gsum[k]);

@@ -40,27 +40,6 @@ struct ResShared {
     double vals[kResSums];
 };
 
-// Sum over the wavefront, valid in lane 63 (row shifts by 1, 2, 4, 8, then row broadcasts: a
-// fixed order, without LDS).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
-    return v + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double wave_sum63(double v)
-{
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
-    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
-    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // x neighbours in rows of 16 lanes taken as rings (row_ror:1 and row_ror:15), summed.
 __device__ __forceinline__ float row_sums(float v)
 {
@@ -86,8 +65,8 @@ __device__ __forceinline__ void res_reduce(ResShared &sh, double (&v)[NV])
     const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
-        v[q] = wave_sum63(v[q]);
-        if (lane == 63) sh.ws[wid][q] = v[q];
+        v[q] = wave_sum(v[q]);
+        if (lane == 0) sh.ws[wid][q] = v[q];
     }
     __syncthreads();
     if (threadIdx.x < NV) {
@@ -201,9 +180,9 @@ __device__ __forceinline__ void res_evaluate(ResShared &sh, real *lds, ResCol &c
     const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
     const double alpha = use_alpha ? sh.S.alpha : 0.0;
     real E[kResZ][2];
-    auto wave_sum = [&](double v, int row) {
-        v = wave_sum63(v);
-        if (lane == 63) sh.ws[wid][row] = v;
+    auto row_sum = [&](double v, int row) {
+        v = wave_sum(v);
+        if (lane == 0) sh.ws[wid][row] = v;
     };
     // field factors, and G_1 (a column's planes past its last and dead lanes: factor 0, no sums)
     {
@@ -227,10 +206,10 @@ __device__ __forceinline__ void res_evaluate(ResShared &sh, real *lds, ResCol &c
             if (j < c.n && c.live) c.at(G, j) = g;
             gs += (double)g;
         }
-        if (sums || N == 1) wave_sum(gs, 0);
+        if (sums || N == 1) row_sum(gs, 0);
         if (sums) {
-            wave_sum(es[0], N);
-            wave_sum(es[1], N + 1);
+            row_sum(es[0], N);
+            row_sum(es[1], N + 1);
         }
     }
     __syncthreads();
@@ -255,7 +234,7 @@ __device__ __forceinline__ void res_evaluate(ResShared &sh, real *lds, ResCol &c
             double gs = 0.0;
 #pragma unroll
             for (int j = 0; j < kResZ; ++j) gs += (double)S[j];
-            wave_sum(gs, s - 1);
+            row_sum(gs, s - 1);
         }
         __syncthreads();
         real *t = g0;

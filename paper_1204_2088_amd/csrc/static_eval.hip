@@ -177,10 +177,9 @@ void static_evaluate(hipStream_t s, unsigned char *base, const Layout &L, const 
                      const double *phi, double *phi_out, double *part, double *partG)
 {
     PropBufs<real> b{(real *)(base + L.E), (real *)(base + L.G), {(real *)(base + L.Gp0), (real *)(base + L.Gp1)}};
-    launch_target_stats(s, plan, rep, st, ch, phi, w, ch.nsp == 3, part);
+    launch_target_stats<real>(s, plan, rep, ch, phi, w, ch.nsp == 3, part, rows ? b.E : nullptr);
     launch_reduce_ctl(s, 1, plan, st, rep, part, ch.nsp == 3 ? PH_TARGET_SOLVENT : PH_TARGET, ch, plan, partG, 0.0, 0,
                       nullptr);
-    if (rows) launch_field_exp<real>(s, plan, rep, st, ch, w, nullptr, 0, b.E, nullptr, nullptr);
     for (int k = sizeof(real) == sizeof(float) ? 0 : 1; k < 2; ++k) {
         if (rows)
             static_rows_pass<real>(s, *rows, plan, tplan, rplan, rep, st, ch, b, (real *)(base + L.Gf0),
