@@ -43,6 +43,7 @@ HBM_PEAK_GBS = 8000.0
 # Valid only for that workload, precision, tiling and kernel as they stand; anything
 # else reports null.
 MEASURED_TRAFFIC = {("vesicle128_a3b9s", "fp32", (32, 8, 4, -1), "pair"): 70.31e6,
+                    ("vesicle128_a3b9s", "fp32", (128, 8, 4, -2), "pair"): 93.64e6,
                     ("vesicle128_a3b9s", "fp32", "lb"): 436.68e6}
 METRIC = "propagator site·bead updates/s + LB MLUPS; step time learned vs plain at 1e-6"
 
@@ -652,7 +653,7 @@ def main():
         "evals_per_step": evals / args.steps,
         "iterations_last_step": [s["iterations"] for s in stats][:8],
         "lb_mlups": lb_roofline["mlups"] if lb_roofline else None,
-        "tile": {"core": list(tile[:3]), "steps_per_launch": max(1, tile[3]), "paired": tile[3] == -1,
+        "tile": {"core": list(tile[:3]), "steps_per_launch": max(1, abs(tile[3])), "paired": tile[3] < 0,
                  "autotune_ms_per_eval": tune_ms},
         "kernels": kernels,
         "kernel_timing_region": {"steps": t_steps,
