@@ -159,6 +159,9 @@ void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, co
 // control kernel's pass over the blocks are paid once per span (128^3: 30.5 us for 8192
 // blocks of 256 sites and 11 us in the control kernel).  E (or null): also the polymers' field
 // factors exp(-w), as launch_field_exp writes them, from the same read of w.
+// Bound by its loads: those of four sites are issued together, unconditionally (128^3 solution,
+// FP32 with field factors: 19.6 us, 118 MB at 6.0 TB/s; 27.6 with a bounds test between the
+// sites, which left one site's loads in flight).
 template <bool SOLVENT, typename real>
 __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__ blk_rep,
                                                          const int *__restrict__ blk_first,
@@ -175,23 +178,36 @@ __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__
     double v[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) v[q] = 0.0;
-#pragma unroll 4
-    for (int u = 0; u < span; u += kBlock) {
-        const long long i = sr.i + u;
-        if (i >= V) break;
-        const double a = phit[fo + i], bb = phit[fo + V + i];
-        v[0] += a + bb;
-        if (nsp == 3) v[1] += phit[fo + 2 * V + i];
-        v[2] += a * a;
-        v[3] += bb * bb;
-        const double wa = w[fo + i], wb = w[fo + V + i];
-        v[4] += wa;
-        v[5] += wb;
-        if (E) {
-            E[po + i] = (real)exp(-wa);
-            E[po + V + i] = (real)exp(-wb);
+    constexpr int U = 4;   // sites whose loads are in flight together
+    for (int u0 = 0; u0 < span; u0 += U * kBlock) {
+        const int n = min(U, (span - u0) / kBlock);
+        double a[U], b[U], c[U], wa[U], wb[U], ws[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long i = min(sr.i + u0 + min(k, n - 1) * kBlock, V - 1);
+            a[k] = phit[fo + i];
+            b[k] = phit[fo + V + i];
+            c[k] = nsp == 3 ? phit[fo + 2 * V + i] : 0.0;
+            wa[k] = w[fo + i];
+            wb[k] = w[fo + V + i];
+            ws[k] = SOLVENT ? w[fo + 2 * V + i] : 0.0;
         }
-        if (SOLVENT) v[NV - 1] += exp(-w[fo + 2 * V + i]);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long i = sr.i + u0 + k * kBlock;
+            if (k >= n || i >= V) continue;
+            v[0] += a[k] + b[k];
+            v[1] += c[k];
+            v[2] += a[k] * a[k];
+            v[3] += b[k] * b[k];
+            v[4] += wa[k];
+            v[5] += wb[k];
+            if (E) {
+                E[po + i] = (real)exp(-wa[k]);
+                E[po + V + i] = (real)exp(-wb[k]);
+            }
+            if (SOLVENT) v[NV - 1] += exp(-ws[k]);
+        }
     }
     block_sums(v);
     if (threadIdx.x == 0)
