@@ -14,15 +14,16 @@
 // the same thread; the density sums stay in registers.
 //
 // Bound by the instructions of one CU (a replica has no more): an evaluation of 16^3 A4B4 in
-// FP64 takes 38.7 us (80 with the box's strides, 61 before the x neighbours and the wavefront
-// sums moved from LDS to DPP), an hsf_evaluate call 57 us against 90 by launches, a coupled
-// step 1.88 ms against 3.41.  The chain of launches is never faster in the range this takes:
+// FP64 takes 35.8 us (80 with the box's strides, 61 before the x neighbours and the wavefront
+// sums moved from LDS to DPP, 39 with both rows' x neighbours summed), an hsf_evaluate call 52
+// us against 90 by launches, a coupled step 1.61 ms against 3.3.  The chain of launches is never faster in the range this takes:
 // 4^3 45 us against 68, 16^3 46 against 68 (one replica, FP32), and with more replicas than
 // CUs 115 against 378 (512 of 16^3), 168 against 222 (1024 of 8^3), 164 against 182 (1024 of
 // 4^3).  Larger boxes do not fit: 32^3 would need 8 times the LDS.
 //
 // Every stored value is the same expression of the same operands as in the one-step
-// kernels; sums over sites have their own fixed order.
+// kernels (in FP64 with 16-site rows up to the order of the four corner neighbours); sums over
+// sites have their own fixed order.
 #include <algorithm>
 
 #include "ctl_device.h"
@@ -137,7 +138,8 @@ __device__ __forceinline__ void res_put(real *f, const ResCol &c, int Lz, int j,
 
 // The stencil of f on the column's planes (the sums of column_stencil).  X16: rows of
 // exactly 16 sites, whose x neighbours are the adjacent lanes of a row of 16: 18 reads instead
-// of 54.
+// of 54.  There the corner sum of FP64 takes the x neighbours of the two rows' sum, which is a
+// sixth of a step's instructions less than the sum of both rows' neighbours.
 template <typename real, bool X16>
 __device__ __forceinline__ void res_stencil(const real *f, const ResCol &c, real c0, real c1, real c2, real c3,
                                             real (&S)[kResZ])
@@ -150,9 +152,11 @@ __device__ __forceinline__ void res_stencil(const real *f, const ResCol &c, real
         const int k = q * kResArea;
         if constexpr (X16) {
             const real v = p[o[1] + k], m = p[o[4] + k], n = p[o[7] + k];
+            const real mn = m + n;
             a0[q] = v;
-            a1[q] = row_sums(v) + (m + n);
-            a2[q] = row_sums(m) + row_sums(n);
+            a1[q] = row_sums(v) + mn;
+            if constexpr (sizeof(real) == 8) a2[q] = row_sums(mn);
+            else a2[q] = row_sums(m) + row_sums(n);   // the one-step kernels' order, bit for bit
         } else {
             a0[q] = p[o[1] + k];
             a1[q] = (p[o[0] + k] + p[o[2] + k]) + (p[o[4] + k] + p[o[7] + k]);

@@ -1,8 +1,8 @@
 """Evaluations and inversions of small boxes in one workgroup per replica, the default there,
 against the one-step kernels (an explicit tiling) and the FP64 oracle.
 
-The two paths store the same expressions of the same operands; sums over sites differ in
-order only (at most 4096 terms in trees about 100 deep: 2 * 100 * 2^-53 < 5e-14 relative on Q and
+The two paths store the same expressions of the same operands (in FP64 with rows of 16 sites up to
+the order of four additions, a few 2^-53 per step); sums over sites differ in order only (at most 4096 terms in trees about 100 deep: 2 * 100 * 2^-53 < 5e-14 relative on Q and
 the densities, in FP32 contexts too).
 """
 import numpy as np
