@@ -272,6 +272,7 @@ __device__ __forceinline__ void res_evaluate(ResShared &sh, real *lds, ResCol &c
         q_from_sum(sh.vals[N - 1], (double)R.V, sh.S.scale_e, N, sh.S.q, sh.S.ln_q, bad);
         if (bad) sh.S.nonfinite = 1;
     }
+    if (N == 1) __syncthreads();   // Q for every wavefront; longer chains have the barriers below
     real *gp = g1, *gn = g0;
     for (int s = N - 1; s >= 1; --s) {
         c.fresh();

@@ -149,3 +149,37 @@ def test_resident_state_round_trip(hsf):
         assert np.array_equal(ctx.get_fields(), ctx2.get_fields())
         ctx.close()
         ctx2.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("L", [(16, 16, 16), (16, 15, 13), (13, 14, 16), (3, 1, 1)])
+def test_resident_one_bead(hsf, orc, precision, L):
+    """Chains of one bead, whose evaluation has no contour step after Q, on boxes that fill all
+    wavefronts of the workgroup: the first evaluation of a fresh context and those after a change
+    of the fields (every one has another Q), then the line searches of an inversion (a B amount
+    that no bead makes keeps it from converging), against the oracle and the one-step kernels.
+    The fields after four iterations differ by rounding, in FP32 contexts that of the propagators
+    (2^-24 a site, in step lengths of order one)."""
+    wl = workload(L, W.chain(1, 0), precision)
+    sysw = orc.System(L=wl.L, types=wl.types, has_solvent=False, a=wl.a, chi=wl.chi, kappa=wl.kappa, dt=wl.dt, tau=wl.tau)
+    rng = np.random.default_rng(2)
+    tol = 1e-10 if precision == "fp64" else 1e-5
+    phi = np.stack([0.8 + 0.1 * rng.random(wl.shape), np.full(wl.shape, 0.1)])
+    inverted = []
+    for tile in (None, (32, 8, 2, 0)):
+        ctx = hsf.Context(wl)
+        if tile:
+            ctx.set_tile(tile)
+        ctx.set_densities(phi.ravel())
+        for k, shift in enumerate((0.0, 2.0, -1.5, 0.7, 3.0)):
+            w = fields(wl, 5 + k) + shift
+            ctx.set_fields(w.ravel())
+            got, q = ctx.evaluate()
+            ref, qref = orc.evaluate(sysw, w, phi.sum(0).mean(), 0.0)
+            assert rel(got, ref.ravel()) < tol and abs(q[0] / qref - 1) < tol, (tile, k)
+        ctx.set_fields(0.2 * fields(wl, 9).ravel())
+        st, rc = ctx.invert(tol=1e-12, max_iter=4, allow_noconv=True)
+        assert rc == hsf.HSF_ENOCONV and st[0]["iterations"] == 4
+        inverted.append(ctx.get_fields())
+        ctx.close()
+    assert rel(*inverted) < (1e-10 if precision == "fp64" else 1e-5)
