@@ -61,6 +61,7 @@ struct hsf_ctx {
     Plan rplan64;                    // and of their FP64 evaluations in an FP32 context (refinement)
     int sweep_most = 0;              // most sweep blocks of one replica
     bool resident = false;           // small boxes: evaluations and inversions in one workgroup per replica
+    bool recorded = false;           // a call was recorded into a graph of the caller's
     int max_tile_blocks = 0;         // over every configuration (sizes the partials)
     size_t lds_limit = 65536;
     int tuned = 0;
@@ -322,6 +323,16 @@ int run_seq(hsf_ctx *c, int kind, F &&body)
     }
     HIPCHK(c, hipGraphLaunch(g.exec, c->stream));
     return HSF_OK;
+}
+
+// Notes a call that the caller records into a graph: its replays use the buffers of that moment, so
+// from then on the densities keep their place between coupled steps (hsf_cd_advance copies the
+// update back, about 16 us for the 50 MB of a 128^3 solution, where it swaps the buffers otherwise).
+void note_recording(hsf_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!c->recorded && c->stream && hipStreamIsCapturing(c->stream, &st) == hipSuccess)
+        c->recorded = st == hipStreamCaptureStatusActive;
 }
 
 // Whether the kernels can use a caller's buffer themselves: memory of the current device, aligned
@@ -1507,12 +1518,14 @@ int hsf_get_fields(hsf_ctx *c, double *w, int where)
 int hsf_set_densities(hsf_ctx *c, const double *phi, int where)
 {
     if (!c) return HSF_EINVAL;
+    note_recording(c);
     return copy_in(c, c->phi, phi, (size_t)c->ch.nsp * c->T, where);
 }
 
 int hsf_get_densities(hsf_ctx *c, double *phi, int where)
 {
     if (!c) return HSF_EINVAL;
+    note_recording(c);
     return copy_out(c, phi, c->phi, (size_t)c->ch.nsp * c->T, where);
 }
 
@@ -1559,6 +1572,7 @@ int hsf_invert(hsf_ctx *c, double tol, int max_iter, int warm, hsf_invert_stats 
 int hsf_mu_force(hsf_ctx *c, double *mu, double *force, int where)
 {
     if (!c) return HSF_EINVAL;
+    note_recording(c);
     const bool mu_in = in_place(mu, where), force_in = in_place(force, where);
     double *m = mu_in ? mu : c->mu, *f = force_in ? force : c->force;
     launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->phi, c->w, m);
@@ -1641,6 +1655,7 @@ int hsf_get_flow(hsf_ctx *c, double *rho, double *u, int where)
 int hsf_cd_advance(hsf_ctx *c, const double *mu, const double *u, int where)
 {
     if (!c || !mu) return HSF_EINVAL;
+    note_recording(c);
     const double *mm = mu, *uu = u;
     if (!in_place(mu, where)) {
         if (int rc = copy_in(c, c->mu, mu, (size_t)c->ch.nsp * c->T, where)) return rc;
@@ -1654,7 +1669,11 @@ int hsf_cd_advance(hsf_ctx *c, const double *mu, const double *u, int where)
               (c->noise & HSF_NOISE_CD) ? c->noise_flux : nullptr, c->noise_step);
     if (c->noise) ++c->noise_step;
     HIPCHK(c, hipGetLastError());
-    std::swap(c->phi, c->phi_tmp);   // captured sequences exist once per density buffer
+    if (c->recorded)
+        HIPCHK(c, hipMemcpyAsync(c->phi, c->phi_tmp, sizeof(double) * c->ch.nsp * c->T, hipMemcpyDeviceToDevice,
+                                 c->stream));
+    else
+        std::swap(c->phi, c->phi_tmp);   // the library's own sequences are captured once per density buffer
     return HSF_OK;
 }
 

@@ -1,0 +1,70 @@
+"""Calls with device buffers recorded into a graph by the caller: replays advance the state as the
+calls themselves do, also between calls that are not recorded.  The same kernels run on the same
+numbers, so the results are the same bits."""
+import numpy as np
+import pytest
+
+from paper_1204_2088_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hsf():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1204_2088_amd import hsf as H
+    H.load()
+    return H
+
+
+@pytest.mark.parametrize("before", [0, 1])
+@pytest.mark.parametrize("record_update", [True, False])
+def test_dynamics_in_a_graph(hsf, record_update, before):
+    """Potential and force, two LB steps and the composition update, recorded as one graph, or
+    with the update called between the replays; after an even and an odd number of updates."""
+    import torch
+    wl = W.Workload("recorded", (20, 18, 16), W.chain(3, 5), True, W.chi_matrix(ab=20 / 8, bs=10 / 8), tau=1.0,
+                    noise=0.05, seed=4, phi_p=0.4)
+    stream = torch.cuda.Stream()
+    w = W.random_fields((3,) + wl.shape, seed=2, amplitude=0.5, smooth=1)
+    u = torch.from_numpy(1e-3 * np.random.default_rng(3).standard_normal(3 * wl.V)).cuda()
+    torch.cuda.synchronize()
+    out = []
+    for record in (False, True):
+        ctx = hsf.Context(wl, stream=stream)
+        ctx.set_densities(W.initial_composition(wl).ravel())
+        ctx.set_fields(0.1 * w.ravel())
+        with torch.cuda.stream(stream):
+            mu, f = (torch.zeros(n * wl.V, dtype=torch.float64, device="cuda") for n in (3, 3))
+        update = lambda: ctx.cd_advance(mu, u)
+
+        def forces():
+            ctx.mu_force(mu, f)
+            ctx.lb_advance(2, f)
+
+        forces()
+        for _ in range(before):
+            update()
+        stream.synchronize()
+        if record:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=stream):
+                forces()
+                if record_update:
+                    update()
+        for _ in range(3):
+            if record:
+                with torch.cuda.stream(stream):
+                    g.replay()
+            else:
+                forces()
+            if not (record and record_update):
+                update()
+        stream.synchronize()
+        out.append([ctx.get_densities(), mu.cpu().numpy(), f.cpu().numpy(), ctx.get_lb()])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    assert not np.array_equal(out[0][0], W.initial_composition(wl).ravel())
