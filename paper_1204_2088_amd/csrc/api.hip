@@ -1573,14 +1573,19 @@ int hsf_mu_force(hsf_ctx *c, double *mu, double *force, int where)
 {
     if (!c) return HSF_EINVAL;
     note_recording(c);
-    const bool mu_in = in_place(mu, where), force_in = in_place(force, where);
+    // outputs that share memory go through the copies: the force overwrites the potential there, and its
+    // kernel reads the potential of other sites
+    const size_t nm = (size_t)c->ch.nsp * c->T, nf = (size_t)3 * c->T;
+    const auto m0 = reinterpret_cast<uintptr_t>(mu), f0 = reinterpret_cast<uintptr_t>(force);
+    const bool apart = !mu || !force || m0 + nm * sizeof(double) <= f0 || f0 + nf * sizeof(double) <= m0;
+    const bool mu_in = apart && in_place(mu, where), force_in = apart && in_place(force, where);
     double *m = mu_in ? mu : c->mu, *f = force_in ? force : c->force;
     launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->phi, c->w, m);
     launch_force(c->stream, c->plan, c->rep_d, c->ch, c->phi, m, f);
     HIPCHK(c, hipGetLastError());
     int rc = HSF_OK;
-    if (mu && !mu_in) rc = copy_out(c, mu, c->mu, (size_t)c->ch.nsp * c->T, where);
-    if (rc == HSF_OK && force && !force_in) rc = copy_out(c, force, c->force, (size_t)3 * c->T, where);
+    if (mu && !mu_in) rc = copy_out(c, mu, c->mu, nm, where);
+    if (rc == HSF_OK && force && !force_in) rc = copy_out(c, force, c->force, nf, where);
     return rc;
 }
 

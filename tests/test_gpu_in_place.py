@@ -73,3 +73,24 @@ def test_device_buffers(hsf, L, off):
             assert np.array_equal(np.asarray(ctx.get_densities()).ravel(), res[5].ravel())
             assert np.array_equal(np.asarray(ctx.get_flow()[1]).ravel(), res[6].ravel())
         ctx.close()
+
+
+@pytest.mark.parametrize("shift", [0, 2, 1, 5000, 25600 - 2, 25600, -2, -1, -25600])
+def test_shared_outputs(hsf, shift):
+    """Potential and force into overlapping device memory (force `shift` doubles after the
+    potential): the force is the one of separate buffers and lies over the potential."""
+    import torch
+    wl = W.Workload("share", (32, 20, 20), W.chain(3, 4), False, W.chi_matrix(ab=15 / 7), tau=1.0, noise=0.2, seed=3)
+    ctx = hsf.Context(wl, stream=torch.cuda.current_stream())
+    ctx.set_densities(W.initial_composition(wl))
+    ctx.set_fields(0.3 * np.random.default_rng(2).standard_normal((2,) + wl.shape))
+    mu, f = ctx.mu_force()
+    n, m = mu.size, f.size
+    o = max(0, -shift)
+    buf = torch.zeros(o + n + m + abs(shift), dtype=torch.float64, device="cuda")
+    ctx.mu_force(buf[o:o + n], buf[o + shift:o + shift + m])
+    want = np.zeros(buf.numel())
+    want[o:o + n] = mu
+    want[o + shift:o + shift + m] = f
+    assert np.array_equal(buf.cpu().numpy(), want)
+    ctx.close()
