@@ -335,18 +335,23 @@ void note_recording(hsf_ctx *c)
         c->recorded = st == hipStreamCaptureStatusActive;
 }
 
-// Whether the kernels can use a caller's buffer themselves: memory of the current device, aligned
-// for the widest loads and stores.  Other device buffers go through a copy.
-bool in_place(const void *p, int where)
+// Whether the kernels can use a caller's buffer of n doubles themselves: memory of the current device,
+// aligned for the widest loads and stores, in one allocation that holds them all.  Other
+// device buffers go through a copy, which refuses those that end too early.
+bool in_place(const void *p, size_t n, int where)
 {
     if (where != HSF_DEVICE || !p || reinterpret_cast<uintptr_t>(p) % 16) return false;
     hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
     int dev = -1;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return a.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && a.device == dev;
+    return a.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && a.device == dev &&
+           n * sizeof(double) <= size - (size_t)((const char *)p - (const char *)base);
 }
 
 template <typename real>
@@ -969,7 +974,7 @@ constexpr long long kDirectSites = 1 << 16;
 
 int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, int where = HSF_DEVICE)
 {
-    const bool res = use_resident(c), direct = (res || c->T >= kDirectSites) && in_place(out, where);
+    const bool res = use_resident(c), direct = (res || c->T >= kDirectSites) && in_place(out, (size_t)c->ch.nsp * c->T, where);
     double *dst = direct ? out : c->eval_out;
     auto sequence = [&] {
         // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
@@ -1578,7 +1583,7 @@ int hsf_mu_force(hsf_ctx *c, double *mu, double *force, int where)
     const size_t nm = (size_t)c->ch.nsp * c->T, nf = (size_t)3 * c->T;
     const auto m0 = reinterpret_cast<uintptr_t>(mu), f0 = reinterpret_cast<uintptr_t>(force);
     const bool apart = !mu || !force || m0 + nm * sizeof(double) <= f0 || f0 + nf * sizeof(double) <= m0;
-    const bool mu_in = apart && in_place(mu, where), force_in = apart && in_place(force, where);
+    const bool mu_in = apart && in_place(mu, nm, where), force_in = apart && in_place(force, nf, where);
     double *m = mu_in ? mu : c->mu, *f = force_in ? force : c->force;
     launch_mu(c->stream, c->muplan, c->col_p, c->rep_d, c->ch, c->phi, c->w, m);
     launch_force(c->stream, c->plan, c->rep_d, c->ch, c->phi, m, f);
@@ -1627,7 +1632,7 @@ int hsf_lb_advance(hsf_ctx *c, int n_steps, const double *force, int where)
 {
     if (!c || n_steps < 0) return HSF_EINVAL;
     const double *f = nullptr;
-    if (in_place(force, where)) {
+    if (in_place(force, (size_t)3 * c->T, where)) {
         f = force;
     } else if (force) {
         int rc = copy_in(c, c->uin, force, (size_t)3 * c->T, where);
@@ -1662,11 +1667,11 @@ int hsf_cd_advance(hsf_ctx *c, const double *mu, const double *u, int where)
     if (!c || !mu) return HSF_EINVAL;
     note_recording(c);
     const double *mm = mu, *uu = u;
-    if (!in_place(mu, where)) {
+    if (!in_place(mu, (size_t)c->ch.nsp * c->T, where)) {
         if (int rc = copy_in(c, c->mu, mu, (size_t)c->ch.nsp * c->T, where)) return rc;
         mm = c->mu;
     }
-    if (u && !in_place(u, where)) {
+    if (u && !in_place(u, (size_t)3 * c->T, where)) {
         if (int rc = copy_in(c, c->uin, u, (size_t)3 * c->T, where)) return rc;
         uu = c->uin;
     }

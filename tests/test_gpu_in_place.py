@@ -94,3 +94,81 @@ def test_shared_outputs(hsf, shift):
     want[o + shift:o + shift + m] = f
     assert np.array_equal(buf.cpu().numpy(), want)
     ctx.close()
+
+
+class Raw:
+    """A device allocation of exactly `nbytes`, outside of torch's caching allocator, with the views
+    the C interface takes."""
+
+    def __init__(self, nbytes):
+        import ctypes
+        self.hip = ctypes.CDLL("libamdhip64.so.7")   # the runtime the library has loaded
+        self.hip.hipMalloc.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t]
+        self.hip.hipFree.argtypes = [ctypes.c_void_p]
+        self.hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+        p = ctypes.c_void_p()
+        assert self.hip.hipMalloc(ctypes.byref(p), nbytes) == 0
+        self.p = p.value
+
+    def put(self, a, at=0):
+        a = np.ascontiguousarray(a)
+        assert self.hip.hipMemcpy(self.p + at, a.ctypes.data, a.nbytes, 1) == 0
+
+    def get(self, n, at=0):
+        a = np.empty(n)
+        assert self.hip.hipMemcpy(a.ctypes.data, self.p + at, a.nbytes, 2) == 0
+        return a
+
+    def free(self):
+        self.hip.hipFree(self.p)
+
+
+@pytest.mark.parametrize("spare", [0, 16, -16])
+def test_ends_of_allocations(hsf, spare):
+    """Buffers that end with their allocation (also from an offset into it) are taken; buffers whose
+    allocation ends 16 bytes too early are refused by every call, as a copy refuses them.  The
+    sizes are whole 4 KiB pages, so those 16 bytes are mapped memory all the same."""
+    wl = W.Workload("ends", (8, 8, 8), W.chain(3, 4), False, W.chi_matrix(ab=15 / 7), tau=1.0, noise=0.2, seed=3)
+    n, m = 2 * 512, 3 * 512
+    rng = np.random.default_rng(4)
+    phi, w = W.initial_composition(wl).ravel(), 0.3 * rng.standard_normal(n)
+    u = 1e-3 * rng.standard_normal(m)
+    ctx = hsf.Context(wl)
+    ctx.set_densities(phi)
+    ctx.set_fields(w)
+    out, _ = ctx.evaluate()
+    mu, f = ctx.mu_force()
+    ctx.lb_advance(2, f)
+    flow = ctx.get_flow()[1]
+    ctx.cd_advance(mu, u)
+    new = ctx.get_densities()
+    ctx.close()
+    ctx = hsf.Context(wl)
+    ctx.set_densities(phi)
+    ctx.set_fields(w)
+    at = max(spare, 0)
+    a, b, v = Raw(8 * n + spare), Raw(8 * m + spare), Raw(8 * m + spare)
+    lib, h = ctx._lib, ctx._h
+    if spare < 0:
+        full = Raw(8 * m)
+        assert lib.hsf_evaluate(h, a.p, None, hsf.DEVICE) == hsf.HSF_EHIP
+        assert lib.hsf_mu_force(h, a.p, full.p, hsf.DEVICE) == hsf.HSF_EHIP
+        assert lib.hsf_mu_force(h, full.p, b.p, hsf.DEVICE) == hsf.HSF_EHIP
+        assert lib.hsf_lb_advance(h, 1, b.p, hsf.DEVICE) == hsf.HSF_EHIP
+        assert lib.hsf_cd_advance(h, a.p, None, hsf.DEVICE) == hsf.HSF_EHIP
+        assert lib.hsf_cd_advance(h, full.p, b.p, hsf.DEVICE) == hsf.HSF_EHIP
+        assert np.array_equal(ctx.get_densities(), phi)
+        full.free()
+    else:
+        assert lib.hsf_evaluate(h, a.p + at, None, hsf.DEVICE) == hsf.HSF_OK
+        assert np.array_equal(a.get(n, at), out)
+        assert lib.hsf_mu_force(h, a.p + at, b.p + at, hsf.DEVICE) == hsf.HSF_OK
+        assert np.array_equal(a.get(n, at), mu) and np.array_equal(b.get(m, at), f)
+        assert lib.hsf_lb_advance(h, 2, b.p + at, hsf.DEVICE) == hsf.HSF_OK
+        assert np.array_equal(ctx.get_flow()[1], flow)
+        v.put(u, at)
+        assert lib.hsf_cd_advance(h, a.p + at, v.p + at, hsf.DEVICE) == hsf.HSF_OK
+        assert np.array_equal(ctx.get_densities(), new)
+    ctx.close()
+    for r in (a, b, v):
+        r.free()
