@@ -408,8 +408,9 @@ int hsf_get_work(hsf_ctx *ctx, long long *evals, double *site_evals, int reset);
  * Contexts whose replicas are all at most 16 sites in each direction start with resident
  * sweeps instead, where the LDS holds them: one workgroup per replica runs a whole evaluation,
  * or the iterations of an inversion, in one launch (timed as HSF_K_PAIR; densities those of
- * k = 0 up to the summation order of Q, in FP64 boxes of 16 sites in x up to rounding).  hsf_set_tile and HSF_TILE switch them off,
- * hsf_autotune switches them on again, and a saved state keeps the choice.
+ * k = 0 up to the summation order of Q, in FP64 boxes of 16 sites in x up to rounding).
+ * hsf_set_tile and HSF_TILE switch them off, hsf_autotune takes them where they are the faster,
+ * and a saved state keeps the choice.
  * hsf_set_tile accepts only the configurations compiled into the library
  * (HSF_EINVAL otherwise); results do not depend on the choice beyond rounding.
  * hsf_autotune times one density-functional evaluation `reps` times with every

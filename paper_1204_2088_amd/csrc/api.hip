@@ -958,6 +958,16 @@ int run_resident(hsf_ctx *c, int kind, double *out, double tol, int max_iter, in
     return HSF_OK;
 }
 
+// The launches of an evaluation into dst.
+void evaluate_launches(hsf_ctx *c, double *dst)
+{
+    // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
+    const bool exps = target_setup(c, 0.0, 0, c->ch.nsp == 3, true);
+    run_eval_any(c, 0, 0, dst, nullptr, 1, exps);
+    launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch, sweep_plan(c),
+                      c->partG, 0.0, 0, c->st_hd);
+}
+
 // One evaluation of the density functional at the current fields, with phibar from the
 // current densities, into eval_out or the caller's `out`; ln Q, phibar and <exp(-w_S)> stay in
 // the replica states.  An evaluation whose propagators left the floating-point range is
@@ -976,13 +986,7 @@ int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, in
 {
     const bool res = use_resident(c), direct = (res || c->T >= kDirectSites) && in_place(out, (size_t)c->ch.nsp * c->T, where);
     double *dst = direct ? out : c->eval_out;
-    auto sequence = [&] {
-        // phibar_p, phibar_s (and <exp(-w_S)>) from the current state; all replicas active
-        const bool exps = target_setup(c, 0.0, 0, c->ch.nsp == 3, true);
-        run_eval_any(c, 0, 0, dst, nullptr, 1, exps);
-        launch_reduce_ctl(c->stream, c->n_rep, c->tplan, c->st_d, c->rep_d, c->part, PH_SCALES, c->ch, sweep_plan(c),
-                          c->partG, 0.0, 0, c->st_hd);
-    };
+    auto sequence = [&] { evaluate_launches(c, dst); };
     for (int attempt = 0; attempt < (check_range ? 4 : 1); ++attempt) {
         int rc0 = HSF_OK;
         if (res) rc0 = run_resident(c, RES_EVAL, dst, 0.0, 0, 1);
@@ -1938,29 +1942,27 @@ int hsf_autotune(hsf_ctx *c, int reps, double *best_ms)
         HSF_ROWS_CONFIGS(HSF_CAND)
 #undef HSF_CAND
     }
-    for (const TileCfg &t : cands) {
-        if (!tile_fits(c, t, lds_real_size(c))) continue;
-        if ((rc = set_tile(c, t)) != HSF_OK) break;
-        // `reps` evaluations (exp, sweeps, Q, normalisation; state untouched), captured in a
-        // graph and replayed as the inversion replays them
-        target_setup(c, 0.0, 0, c->ch.nsp == 3);
-        run_eval_any(c, 0, 0, c->eval_out, nullptr, 0);
+    // Time of `body`, a sequence of launches captured `reps` times in a graph and replayed, as
+    // inversions and evaluations replay theirs: the best of two replays.
+    auto timed = [&](auto &&body, float &ms) -> int {
         hipStream_t user = c->stream;
         if (!user && !c->cap_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
         hipStream_t cs = user ? user : c->cap_stream;
         HIPCHK(c, hipStreamSynchronize(user));
         HIPCHK(c, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
         c->stream = cs;
-        for (int k = 0; k < reps; ++k) run_eval_any(c, 0, 0, c->eval_out, nullptr, 0);
+        int brc = HSF_OK;
+        for (int k = 0; k < reps && brc == HSF_OK; ++k) brc = body();
         c->stream = user;
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
         hipError_t e = hipStreamEndCapture(cs, &graph);
-        if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+        if (e == hipSuccess && brc == HSF_OK) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
         if (graph) (void)hipGraphDestroy(graph);
+        if (brc) return brc;
         if (e == hipSuccess) e = hipGraphLaunch(exec, c->stream);   // warm
-        float ms = 1e30f;
-        for (int trial = 0; trial < 2 && e == hipSuccess; ++trial) {   // best of two replays
+        ms = 1e30f;
+        for (int trial = 0; trial < 2 && e == hipSuccess; ++trial) {
             if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
             if (e == hipSuccess) e = hipGraphLaunch(exec, c->stream);
             if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
@@ -1970,39 +1972,52 @@ int hsf_autotune(hsf_ctx *c, int reps, double *best_ms)
             ms = std::min(ms, t_ms / reps);
         }
         if (exec) (void)hipGraphExecDestroy(exec);
-        if (e != hipSuccess) {
-            rc = fail(c, HSF_EHIP, "autotune: %s", hipGetErrorString(e));
-            break;
-        }
+        return e == hipSuccess ? HSF_OK : fail(c, HSF_EHIP, "autotune: %s", hipGetErrorString(e));
+    };
+    for (const TileCfg &t : cands) {
+        if (!tile_fits(c, t, lds_real_size(c))) continue;
+        if ((rc = set_tile(c, t)) != HSF_OK) break;
+        // evaluations alone (exp, sweeps, Q, normalisation; state untouched)
+        target_setup(c, 0.0, 0, c->ch.nsp == 3);
+        run_eval_any(c, 0, 0, c->eval_out, nullptr, 0);
+        float ms;
+        rc = timed([&] {
+            run_eval_any(c, 0, 0, c->eval_out, nullptr, 0);
+            return (int)HSF_OK;
+        }, ms);
+        if (rc) break;
         if (ms < best_t) {
             best_t = ms;
             best = t;
         }
     }
+    if (rc == HSF_OK) rc = set_tile(c, best);
+    // Small boxes: one workgroup per replica against the launches of an hsf_evaluate with that
+    // tiling.  One workgroup is faster but for thousands of tiny boxes, which leave most of its
+    // threads idle (FP32 calls: 46 us against 68 for 16^3 A4B4, 718 against 485 for 1024 boxes of 16 x 1 x 1 with
+    // 64 beads).  Both update the per-step scales, which are put back.
+    c->resident = false;
+    if (rc == HSF_OK && resident_fits(c->reps.data(), c->n_rep, real_size(c), c->lds_limit)) {
+        const size_t bytes = sizeof(RepState) * c->n_rep;
+        float chain = 0.0f, res = 0.0f;
+        hipError_t e = hipMemcpy(c->st_save, c->st_d, bytes, hipMemcpyDeviceToDevice);
+        const std::vector<RepState> host(c->st_h, c->st_h + c->n_rep);
+        if (e == hipSuccess)
+            rc = timed([&] {
+                evaluate_launches(c, c->eval_out);
+                return (int)HSF_OK;
+            }, chain);
+        if (e == hipSuccess && rc == HSF_OK)
+            rc = timed([&] { return run_resident(c, RES_EVAL, c->eval_out, 0.0, 0, 1); }, res);
+        if (e == hipSuccess) e = hipMemcpy(c->st_d, c->st_save, bytes, hipMemcpyDeviceToDevice);
+        std::copy(host.begin(), host.end(), c->st_h);
+        if (e != hipSuccess && rc == HSF_OK) rc = fail(c, HSF_EHIP, "autotune: %s", hipGetErrorString(e));
+        c->resident = rc == HSF_OK && res <= chain;
+        if (c->resident) best_t = res;
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->timing = saved_timing;
-    if (rc == HSF_OK) rc = set_tile(c, best);
-    // boxes small enough for resident evaluations: one kernel against a chain of launches
-    // (16^3 A4B4 FP64: 39 us against 49 us and, in an inversion, no host turn per pass)
-    c->resident = rc == HSF_OK && resident_fits(c->reps.data(), c->n_rep, real_size(c), c->lds_limit);
-    if (c->resident) {
-        hipEvent_t a = nullptr, b = nullptr;
-        HIPCHK(c, hipEventCreate(&a));
-        HIPCHK(c, hipEventCreate(&b));
-        float ms = 1e30f;
-        for (int k = 0; k < 3 && rc == HSF_OK; ++k) {
-            (void)hipEventRecord(a, c->stream);
-            rc = run_resident(c, RES_EVAL, c->eval_out, 0.0, 0, 1);
-            (void)hipEventRecord(b, c->stream);
-            float t_ms = 1e30f;
-            if (hipEventSynchronize(b) == hipSuccess) (void)hipEventElapsedTime(&t_ms, a, b);
-            ms = std::min(ms, t_ms);
-        }
-        (void)hipEventDestroy(a);
-        (void)hipEventDestroy(b);
-        best_t = std::min(best_t, ms);
-    }
     c->tuned = 1;
     if (best_ms) *best_ms = best_t;
     return rc;

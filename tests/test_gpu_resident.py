@@ -183,3 +183,53 @@ def test_resident_one_bead(hsf, orc, precision, L):
         inverted.append(ctx.get_fields())
         ctx.close()
     assert rel(*inverted) < (1e-10 if precision == "fp64" else 1e-5)
+
+
+def runs_resident(ctx):
+    """Whether evaluations take one workgroup per replica: a single launch, with no density
+    launch after the sweeps."""
+    ctx.set_timing(True)
+    ctx.get_timing()
+    ctx.evaluate()
+    t = ctx.get_timing()
+    ctx.set_timing(False)
+    return t["bwd"][1] == 0 and t["pair"][1] > 0
+
+
+def test_autotune_takes_the_faster_path(hsf):
+    """One workgroup per replica at 16^3 (calls of 46 us against 68), launches for 1024 boxes of 16
+    sites and 64 beads (485 against 718).  Nothing of autotune's own is left in the timing."""
+    for boxes, types, resident in ([(16, 16, 16)], W.chain(4, 4), True), ([(16, 1, 1)] * 1024, W.chain(32, 32), False):
+        wls = [workload(L, types, "fp64", seed=r) for r, L in enumerate(boxes)]
+        ctx = hsf.Context(wls)
+        assert runs_resident(ctx)          # the default of small boxes
+        ctx.set_densities(np.concatenate([W.initial_composition(wl).ravel() for wl in wls]))
+        ctx.set_timing(True)
+        ctx.autotune(2)
+        assert all(n == 0 for _, n in ctx.get_timing().values())
+        assert runs_resident(ctx) == resident
+        ctx.close()
+
+
+def test_autotune_keeps_the_scales(hsf):
+    """The per-step scales of an FP32 context are those of its evaluations, not of the timing runs:
+    fields of 10 ln 2 give every step the exponent -10 (csum is 1), which a checkpoint holds as a run
+    of N equal integers; other fields change nothing until they are evaluated."""
+    wl = workload((12, 8, 8), W.chain(4, 4), "fp32")
+    ctx = hsf.Context(wl)
+    ctx.set_densities(W.initial_composition(wl).ravel())
+    ctx.set_fields(np.full(2 * wl.V, 10 * np.log(2.0)))
+    ctx.evaluate()
+
+    def scales():
+        n = ctx.get_state().size - 8 * (6 * 2 + 19) * wl.V   # header and replica states
+        return ctx.get_state()[:n // 4 * 4].view(np.int32)
+
+    run = lambda v, x: any(np.all(v[k:k + wl.N] == x) for k in range(v.size - wl.N))
+    assert run(scales(), -10)
+    ctx.set_fields(np.full(2 * wl.V, 3 * np.log(2.0)))
+    ctx.autotune(2)
+    assert run(scales(), -10)
+    ctx.evaluate()
+    assert run(scales(), -3) and not run(scales(), -10)
+    ctx.close()
