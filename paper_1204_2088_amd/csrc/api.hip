@@ -968,6 +968,25 @@ void evaluate_launches(hsf_ctx *c, double *dst)
                       c->partG, 0.0, 0, c->st_hd);
 }
 
+// Whether an evaluation's launches are better issued one by one than replayed from a graph with
+// a copy of the densities (4 to 14 us with the gap before it) at the end.  Kernels of fewer sites
+// than about kDirectSites finish before the next one is launched; the queue hides that for about
+// two dozen launches, whatever the box, and from some 10 us a kernel there is nothing to hide.
+// FP32, one by one against replayed: one 32^3 box 91 us / 76; two 32^3 boxes, paired
+// steps, with 8 beads 66 / 69, 16 beads 104 / 102, 64 beads 400 / 320; two 64^3, paired, 64 beads 602 /
+// 590; thirty-two 32^3, paired, 64 beads 1046 / 1067; row sweeps of K = 2 with 64 beads, three 32^3
+// 309 / 300, eight 32^3 407 / 412; two 64^3 with 16 beads, row sweeps 115 / 120.
+constexpr long long kDirectSites = 1 << 16;
+
+bool direct_launches(const hsf_ctx *c)
+{
+    if (c->T < kDirectSites) return false;
+    const int N = c->ch.N, K = std::max(1, c->tile.k), sweeps = (N + K - 1) / K;
+    const bool rows = tile_is_rows(c->tile) && N >= 2;
+    const int launches = rows ? rows_launches(N, -c->tile.k) + 4 : c->tile.k < 0 ? N + 4 : 2 * sweeps + 4;
+    return launches <= 24 || c->T >= (rows ? 1 << 17 : 3 << 18);
+}
+
 // One evaluation of the density functional at the current fields, with phibar from the
 // current densities, into eval_out or the caller's `out`; ln Q, phibar and <exp(-w_S)> stay in
 // the replica states.  An evaluation whose propagators left the floating-point range is
@@ -976,15 +995,11 @@ void evaluate_launches(hsf_ctx *c, double *dst)
 // for the stream once.
 //
 // A caller's device buffer is written by the density launch itself.  The captured sequence
-// writes eval_out, so the launches are then issued one by one, which suits boxes whose
-// kernels outlast their launches: kDirectSites sites and more (the copy and the gap before it
-// against the sequence: 128^3 FP32 279 -> 256 us, two 64^3 139 -> 133, 48^3 84 -> 82; 32^3, with
-// more and shorter kernels, takes 91 us launched one by one against 76).
-constexpr long long kDirectSites = 1 << 16;
-
+// writes eval_out, so the launches are then issued one by one (direct_launches).
 int evaluate_impl(hsf_ctx *c, bool check_range = true, double *out = nullptr, int where = HSF_DEVICE)
 {
-    const bool res = use_resident(c), direct = (res || c->T >= kDirectSites) && in_place(out, (size_t)c->ch.nsp * c->T, where);
+    const bool res = use_resident(c);
+    const bool direct = (res || direct_launches(c)) && in_place(out, (size_t)c->ch.nsp * c->T, where);
     double *dst = direct ? out : c->eval_out;
     auto sequence = [&] { evaluate_launches(c, dst); };
     for (int attempt = 0; attempt < (check_range ? 4 : 1); ++attempt) {

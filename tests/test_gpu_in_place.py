@@ -158,6 +158,7 @@ def test_ends_of_allocations(hsf, spare):
         assert lib.hsf_cd_advance(h, a.p, None, hsf.DEVICE) == hsf.HSF_EHIP
         assert lib.hsf_cd_advance(h, full.p, b.p, hsf.DEVICE) == hsf.HSF_EHIP
         assert np.array_equal(ctx.get_densities(), phi)
+        full.hip.hipGetLastError()   # the runtime keeps the copies' error until it is read
         full.free()
     else:
         assert lib.hsf_evaluate(h, a.p + at, None, hsf.DEVICE) == hsf.HSF_OK
@@ -172,3 +173,26 @@ def test_ends_of_allocations(hsf, spare):
     ctx.close()
     for r in (a, b, v):
         r.free()
+
+
+@pytest.mark.parametrize("tile,beads", [((64, 4, 4, -4), 8), ((64, 4, 4, -2), 40), ((32, 8, 2, -1), 2), ((32, 8, 2, -1), 12),
+                                        ((32, 8, 2, 0), 2), ((8, 8, 8, 4), 3), ((8, 8, 8, 4), 40)])
+def test_routes_of_an_evaluation(hsf, tile, beads):
+    """Launches one by one into the caller's buffer, and a replayed sequence with a copy: which one an
+    aligned buffer gets depends on the number of launches, a misaligned one always gets the
+    copy; both give the bits of a host array."""
+    import torch
+    wl = W.Workload("routes", (44, 40, 40), W.chain(1, beads - 1), True, W.chi_matrix(ab=15 / beads, bs=10 / beads), tau=1.0,
+                    noise=0.02, seed=3, phi_p=0.3, precision="fp32")
+    ctx = hsf.Context(wl, stream=torch.cuda.current_stream())
+    ctx.set_tile(tile)
+    ctx.set_densities(W.initial_composition(wl))
+    ctx.set_fields(0.3 * np.random.default_rng(2).standard_normal((3,) + wl.shape))
+    ctx.evaluate()
+    ref, q = ctx.evaluate()
+    ref = ref.copy()
+    for off in (0, 1, 0):
+        v, buf = slot(3 * wl.V, off)
+        assert np.array_equal(ctx.evaluate(out=v)[1], q)
+        check(v, buf, off, ref)
+    ctx.close()
