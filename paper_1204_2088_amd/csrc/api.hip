@@ -51,7 +51,7 @@ struct hsf_ctx {
     int *bad_h = nullptr;            // pinned flag set by the LB and CD kernels on a non-finite result
     int *bad_hd = nullptr;           // its device-side address
     Plan muplan, cdplan;             // column plans (chemical potential, convection-diffusion)
-    int col_p = 1;                   // their sites per lane
+    int col_p = 1;                   // their sites per lane (0: one, short rows share wavefronts)
     Plan plan;                       // site plan: kBlock consecutive sites per block
     Plan cplan;                      // the same with span sites per block, for the kernels that reduce
     TileCfg tile{8, 8, 8, 2};        // propagator tile configuration in use
@@ -1302,10 +1302,15 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     cblk_first.push_back((int)cblk_rep.size());
     c->cplan.nblocks = (int)cblk_rep.size();
     c->cplan.n_rep = n_rep;
-    // columns: two sites per lane where every row is a whole wavefront of them
+    // columns: two sites per lane where every row is a whole wavefront of them; rows of at most 30
+    // sites side by side in a wavefront where most of the sites lie in such rows
     c->col_p = 2;
-    for (const Rep &R : c->reps)
+    long long short_rows = 0;
+    for (const Rep &R : c->reps) {
         if (R.Lx != 128) c->col_p = 1;
+        if (col_rows(0, R.Lx) > 1) short_rows += R.V;
+    }
+    if (2 * short_rows > c->T) c->col_p = 0;
     std::vector<int> kblk_rep[2], kblk_first[2];
     for (int k = 0; k < 2; ++k) {
         for (int r = 0; r < n_rep; ++r) {

@@ -7,6 +7,8 @@
 #include <hip/hip_ext.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "philox.h"
 
@@ -44,8 +46,9 @@ __device__ __forceinline__ long long sidx(const Rep &R, int x, int y, int z)
 // A wavefront's part of the column plan: P consecutive x sites per lane of one row, CZ core
 // planes.  Rows of exactly 64 P sites are whole (the lanes form the periodic ring); others
 // are cut into pieces with a halo site at both ends, whose lanes compute and store nothing.
-// Every lane's address is inside the box.
-template <int P, int CZ>
+// SHORT: rows of at most 30 sites stand side by side in the wavefront, each with its two halo
+// sites (row and the y neighbours are then the lane's own).  Every lane's address is inside the box.
+template <int P, int CZ, bool SHORT>
 struct Col {
     int r, y, z0, nz, plane, Lz;
     long long V, row, up, dn;    // offsets of the row and of its y neighbours within a plane
@@ -61,10 +64,18 @@ struct Col {
         int lb = pb - blk_first[r];
         const int x0 = (lb % cut.ntx) * cut.width;
         lb /= cut.ntx;
-        const int nty = (R.Ly + kColY - 1) / kColY;
-        y = (lb % nty) * kColY + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int rows = SHORT ? col_rows(0, R.Lx) : 1, nty = (R.Ly + kColY * rows - 1) / (kColY * rows);
+        y = ((lb % nty) * kColY + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * rows;
         z0 = (lb / nty) * CZ;
         if (y >= R.Ly) return false;
+        int lane = (int)threadIdx.x & 63;
+        bool mine = true;
+        if (SHORT && rows > 1) {
+            const int k = lane / (R.Lx + 2);
+            lane -= k * (R.Lx + 2);
+            mine = k < rows && y + k < R.Ly;
+            y = min(y + k, R.Ly - 1);
+        }
         Lz = R.Lz;
         nz = min(CZ, Lz - z0);
         V = R.V;
@@ -72,8 +83,8 @@ struct Col {
         row = (long long)y * R.Lx;
         dn = (long long)wrap1(y - 1, R.Ly) * R.Lx;
         up = (long long)wrap1(y + 1, R.Ly) * R.Lx;
-        const int xu = x0 - cut.halo + ((int)threadIdx.x & 63) * P;
-        core = xu >= x0 && xu < x0 + cut.width && xu < R.Lx;
+        const int xu = x0 - cut.halo + lane * P;
+        core = mine && xu >= x0 && xu < x0 + cut.width && xu < R.Lx;
         int x = xu % R.Lx;
         if (x < 0) x += R.Lx;
         xb = (unsigned)x * (unsigned)sizeof(double);
@@ -113,15 +124,17 @@ __device__ __forceinline__ void x_pair(const Sites<double, P> &c, Sites<double, 
 // kMuZ = 4.5 loads per site, x neighbours from the adjacent lanes) and combines three
 // planes' class sums per site.  With one site per lane and its nine rows loaded anew (18
 // loads per site and species) the kernel was bound by its loads' latency: 85 us for 3 species
-// at 128^3 (151 MB); now 36 us, 4.2 TB/s.
-template <int NSP, int P>
+// at 128^3 (151 MB); now 36 us, 4.2 TB/s.  A box of 4 x 256 x 256 leaves most lanes idle with a
+// wavefront per row: potential and force 45 us a call, 27 with one site per lane of the whole box, 15
+// with ten rows side by side.
+template <int NSP, int P, bool SHORT>
 __global__ __launch_bounds__(kBlock) void k_mu(const int *__restrict__ blk_rep, const int *__restrict__ blk_first,
                                                const Rep *__restrict__ rep, const double *__restrict__ phi,
                                                const double *__restrict__ w, double *__restrict__ mu)
 {
     typedef Sites<double, P> row_t;
     constexpr int CZ = kMuZ;
-    Col<P, CZ> t;
+    Col<P, CZ, SHORT> t;
     if (!t.init(blk_rep, blk_first, rep)) return;
     const Rep &R = rep[t.r];
     const long long fo = off_field(R, NSP);
@@ -483,8 +496,9 @@ __global__ __launch_bounds__(kBlock, NOISE && MODE != HSF_LB_MRT ? 3 : 4) void k
 // beforehand by k_cd_noise into jn.
 // Columns as in k_mu: z neighbours are the lane's other planes, x neighbours come from the
 // adjacent lanes, the rows y +- 1 are loaded (23 loads per site for 3 species, against 44 with
-// one site per lane, which took 74 us at 128^3 for 201 MB; now 46 us, 4.4 TB/s).
-template <bool NOISE, int NSP, int P>
+// one site per lane, which took 74 us at 128^3 for 201 MB; now 46 us, 4.4 TB/s).  4 x 256 x 256 in
+// calls as above: 61, 25 and 12.5 us.
+template <bool NOISE, int NSP, int P, bool SHORT>
 __global__ __launch_bounds__(kBlock) void k_cd(const int *__restrict__ blk_rep, const int *__restrict__ blk_first,
                                                const Rep *__restrict__ rep, const double *__restrict__ phi,
                                                const double *__restrict__ mu, const double *__restrict__ u,
@@ -493,7 +507,7 @@ __global__ __launch_bounds__(kBlock) void k_cd(const int *__restrict__ blk_rep, 
 {
     typedef Sites<double, P> row_t;
     constexpr int CZ = kCdZ;
-    Col<P, CZ> t;
+    Col<P, CZ, SHORT> t;
     if (!t.init(blk_rep, blk_first, rep)) return;
     const Rep &R = rep[t.r];
     const long long fo = off_field(R, NSP), vo = 3LL * R.site_off;
@@ -659,7 +673,9 @@ __global__ __launch_bounds__(kBlock) void k_lb_convert(const int *__restrict__ b
 void launch_mu(hipStream_t s, const Plan &p, int P, const Rep *rep, Chain ch, const double *phi, const double *w,
                double *mu)
 {
-    auto kern = P == 2 ? (ch.nsp == 3 ? k_mu<3, 2> : k_mu<2, 2>) : (ch.nsp == 3 ? k_mu<3, 1> : k_mu<2, 1>);
+    auto kern = P == 2   ? (ch.nsp == 3 ? k_mu<3, 2, false> : k_mu<2, 2, false>)
+                : P == 1 ? (ch.nsp == 3 ? k_mu<3, 1, false> : k_mu<2, 1, false>)
+                         : (ch.nsp == 3 ? k_mu<3, 1, true> : k_mu<2, 1, true>);
     hipLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, p.blk_rep, p.blk_first, rep, phi, w, mu);
 }
 
@@ -717,11 +733,13 @@ void launch_cd(hipStream_t s, const Plan &p, int P, const Plan &ps, const Rep *r
                                phi, noise_flux, step);
         e0 = nullptr;
     }
-    auto pick = [&](auto three2, auto two2, auto three1, auto two1) {
-        return P == 2 ? (ch.nsp == 3 ? three2 : two2) : (ch.nsp == 3 ? three1 : two1);
+    auto pick = [&](auto noise) {
+        constexpr bool N = noise();
+        return P == 2   ? (ch.nsp == 3 ? k_cd<N, 3, 2, false> : k_cd<N, 2, 2, false>)
+               : P == 1 ? (ch.nsp == 3 ? k_cd<N, 3, 1, false> : k_cd<N, 2, 1, false>)
+                        : (ch.nsp == 3 ? k_cd<N, 3, 1, true> : k_cd<N, 2, 1, true>);
     };
-    auto kern = noise_flux ? pick(k_cd<true, 3, 2>, k_cd<true, 2, 2>, k_cd<true, 3, 1>, k_cd<true, 2, 1>)
-                           : pick(k_cd<false, 3, 2>, k_cd<false, 2, 2>, k_cd<false, 3, 1>, k_cd<false, 2, 1>);
+    auto kern = noise_flux ? pick(std::true_type()) : pick(std::false_type());
     if (e0 || e1)
         hipExtLaunchKernelGGL(kern, dim3(p.nblocks), dim3(kBlock), 0, s, e0, e1, 0, p.blk_rep, p.blk_first, rep, phi,
                               mu, u, phi_out, noise_flux, diff_scale, bad);

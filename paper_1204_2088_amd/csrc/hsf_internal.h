@@ -148,14 +148,17 @@ void launch_solvent(hipStream_t s, const Plan &p, const Rep *rep, RepState *st, 
 // dynamics
 // Column plans of the chemical-potential and convection-diffusion kernels: a wavefront takes
 // a row piece (rows_cut with K = 1 and P sites per lane) of kMuZ or kCdZ planes, a block
-// kColY rows.  The convection-diffusion kernel holds more arrays per plane: at 4 planes its
-// registers leave one wavefront per SIMD.
+// kColY of them.  The convection-diffusion kernel holds more arrays per plane: at 4 planes its
+// registers leave one wavefront per SIMD.  P = 0: one site per lane, and rows short enough to
+// stand side by side in a wavefront, each with its two halo sites, do so.
 constexpr int kColY = 4, kMuZ = 4, kCdZ = 2;
+__host__ __device__ inline int col_rows(int P, int Lx) { return P == 0 && Lx <= 30 ? 64 / (Lx + 2) : 1; }
 inline long long col_blocks(int P, int CZ, int Lx, int Ly, int Lz)
 {
-    return (long long)rows_cut(Lx, P, 1).ntx * ((Ly + kColY - 1) / kColY) * ((Lz + CZ - 1) / CZ);
+    const int rows = kColY * col_rows(P, Lx);
+    return (long long)rows_cut(Lx, P == 2 ? 2 : 1, 1).ntx * ((Ly + rows - 1) / rows) * ((Lz + CZ - 1) / CZ);
 }
-// p: the column plan, P its sites per lane
+// p: the column plan, P its sites per lane (or 0)
 void launch_mu(hipStream_t s, const Plan &p, int P, const Rep *rep, Chain ch, const double *phi,
                const double *w, double *mu);
 void launch_force(hipStream_t s, const Plan &p, const Rep *rep, Chain ch, const double *phi,

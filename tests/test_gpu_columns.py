@@ -115,3 +115,38 @@ def test_update_then_evaluate(hsf):
         assert np.array_equal(a, b) and np.array_equal(qa, qb), k
     ctx.close()
     ctx2.close()
+
+
+# rows that share a wavefront: one site to thirty, numbers of rows that do not fill the last
+# group or the block, batches where most sites (not all rows) are short
+SHORT = [[(1, 17, 5)], [(1, 90, 3)], [(2, 9, 4)], [(3, 53, 2)], [(4, 23, 6)], [(10, 33, 3)], [(16, 20, 9)], [(29, 9, 5)],
+         [(30, 8, 4)], [(31, 7, 4)], [(4, 30, 5), (9, 7, 6)], [(6, 40, 4), (70, 3, 4)], [(128, 3, 2), (8, 40, 6)],
+         [(64, 5, 2), (20, 40, 3), (1, 1, 1)]]
+
+
+@pytest.mark.parametrize("noise", [False, True])
+@pytest.mark.parametrize("solvent", [False, True])
+@pytest.mark.parametrize("boxes", SHORT)
+def test_short_rows_match_oracle(hsf, orc, boxes, solvent, noise):
+    wls = [workload(L, solvent, r) for r, L in enumerate(boxes)]
+    data = [inputs(wl, 17 + r) for r, wl in enumerate(wls)]
+    cat = lambda k: np.concatenate([d[k].ravel() for d in data])
+    ctx = hsf.Context(wls)
+    ctx.set_densities(cat(0))
+    ctx.set_fields(cat(1))
+    mu, f = ctx.mu_force()
+    if noise:
+        ctx.set_noise(cd=True, lb=False, omega=400.0, seed=11, step=5)
+    ctx.cd_advance(mu, cat(2))
+    out = ctx.get_densities()
+    ctx.set_densities(cat(0))
+    if noise:
+        ctx.set_noise(cd=True, lb=False, omega=400.0, seed=11, step=5)
+    ctx.cd_advance(mu)
+    out0 = ctx.get_densities()
+    for r, wl in enumerate(wls):
+        a, b = ctx.field_offset(r), ctx.site_offset(r)
+        n, V = wl.nsp * wl.V, wl.V
+        kw = dict(noise=1, omega=400.0, seed=11, rep=r, step=5) if noise else {}
+        check(orc, wl, *data[r], mu[a:a + n], f[3 * b:3 * b + 3 * V], out[a:a + n], out0[a:a + n], **kw)
+    ctx.close()
