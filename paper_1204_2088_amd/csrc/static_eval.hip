@@ -26,6 +26,20 @@ constexpr TileCfg kStaticTile{32, 8, 2, 0};
 
 // Row bundles of the sweeps: at least as fast as any other up to 32^3 and from 48^3 to 64^3.
 TileCfg static_rows(long long V) { return V < 65536 ? TileCfg{64, 4, 4, -4} : TileCfg{64, 8, 4, -3}; }
+
+// Whether the row sweeps are the faster: they compute `lanes` sites per step, with the idle lanes of short
+// rows, the rows and planes past a thin box and the halos, where the one-step kernels
+// compute V.  Up to about 48 MB of them (less for chains too short for all K steps) the fewer
+// launches count more, and up to 32 per site (9 and 4.4 in boxes that fill the bundles) there is
+// no loss.  Rows against one step: 8 beads, FP32, 1 x 64 x 64 71 us / 166, 2 x 128 x 128 147 / 196, 1 x 256 x 256
+// 474 / 271; FP64 4 x 128 x 128 116 / 138, 2 x 128 x 128 165 / 127, 1 x 1 x 4000 165 / 114; 2 beads, FP64,
+// 64 x 64 x 1 35 / 45, 6 x 100 x 100 53 / 39.
+bool static_rows_pay(const TileCfg &t, const Rep &R, int N, size_t rs)
+{
+    const int K = -t.k;
+    const long long lanes = rows_blocks(t, R.Lx, R.Ly, R.Lz) * 64 * (t.cy + 2 * K) * (t.cz + 2 * K);
+    return lanes * (long long)rs <= (48LL << 20) * std::min(K, N - 1) / K || lanes <= 32 * R.V;
+}
 constexpr int kMaxDevices = 64;
 
 // Device address of `scratch` per device, taken once with that device current (in host
@@ -237,7 +251,7 @@ extern "C" int hsf_evaluate_static(const hsf_params *p, const double *w, const d
     const int nbs = (int)nbs_ll, nbt = (int)nbt_ll;
     // row sweeps when the array holds them (chains of at least two beads)
     const TileCfg rows = static_rows(R.V);
-    int nbr = ch.N >= 2 ? (int)std::min(rows_blocks(rows, R.Lx, R.Ly, R.Lz), 1LL << 30) : 0;
+    int nbr = ch.N >= 2 && static_rows_pay(rows, R, ch.N, rs) ? (int)std::min(rows_blocks(rows, R.Lx, R.Ly, R.Lz), 1LL << 30) : 0;
     Layout L = layout(R.V, ch.N, rs, nbs, nbt, nbr);
     if (nbr && L.total > (size_t)HSF_STATIC_SCRATCH_BYTES) {
         nbr = 0;

@@ -174,3 +174,23 @@ def test_static_evaluation_at_its_limits(hsf, L, n, precision):
     torch.cuda.synchronize()
     tol = 1e-10 if precision == "fp64" else 1e-5
     assert rel(out.cpu().numpy(), ref) < tol and abs(qd.item() / q[0] - 1) < tol
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("L,n", [((1, 256, 40), 8), ((1, 90, 90), 8), ((6, 100, 100), 2), ((64, 64, 1), 2), ((1, 1, 4000), 12),
+                                 ((3, 1, 700), 3)])
+def test_static_evaluation_of_thin_boxes(hsf, orc, precision, L, n):
+    """Boxes on both sides of the line between row sweeps and one-step sweeps (few sites per row, few
+    rows), with a solvent, against the oracle."""
+    import torch
+    wl = workload(L, W.chain(1, n - 1), precision, True)
+    phi, w = W.initial_composition(wl), fields(wl, 12)
+    sysw = orc.System(L=wl.L, types=wl.types, has_solvent=True, a=wl.a, chi=wl.chi, kappa=wl.kappa, dt=wl.dt, tau=wl.tau)
+    ref, qref = orc.evaluate(sysw, w, phi[:2].sum(0).mean(), phi[2].mean())
+    wd, pd = torch.from_numpy(w.ravel().copy()).cuda(), torch.from_numpy(phi.ravel().copy()).cuda()
+    out, qd = torch.zeros_like(wd), torch.zeros(1, dtype=torch.float64, device="cuda")
+    for _ in range(2):
+        assert hsf.evaluate_static(wl, wd, pd, out, qd) == hsf.HSF_OK
+        torch.cuda.synchronize()
+        tol = 1e-10 if precision == "fp64" else 1e-5
+        assert rel(out.cpu().numpy(), ref.ravel()) < tol and abs(qd.item() / qref - 1) < tol
