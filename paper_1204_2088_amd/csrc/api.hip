@@ -2110,7 +2110,7 @@ int hsf_get_work(hsf_ctx *c, long long *evals, double *site_evals, int reset)
 namespace {
 struct StateHeader {
     unsigned long long magic;        // identifies the layout
-    int version;
+    int version;                     // 1, or 2 with resident evaluations: libraries that do not know them refuse it
     int n_rep, nsp, N, precision;
     int types[64];                   // bead species (the per-step scales belong to the chain)
     long long T;
@@ -2140,7 +2140,7 @@ int hsf_get_state(hsf_ctx *c, void *buf, long long size)
     char *p = static_cast<char *>(buf);
     StateHeader h{};
     h.magic = kStateMagic;
-    h.version = 1;
+    h.version = c->resident ? 2 : 1;
     h.n_rep = c->n_rep;
     h.nsp = c->ch.nsp;
     h.N = c->ch.N;
@@ -2181,7 +2181,7 @@ int hsf_set_state(hsf_ctx *c, const void *buf, long long size)
     if (size < (long long)sizeof(StateHeader)) return fail(c, HSF_EINVAL, "state buffer too small");
     StateHeader h;
     memcpy(&h, buf, sizeof h);
-    if (h.magic != kStateMagic || h.version != 1) return fail(c, HSF_EINVAL, "not a state written by hsf_get_state");
+    if (h.magic != kStateMagic || (h.version != 1 && h.version != 2)) return fail(c, HSF_EINVAL, "not a state written by hsf_get_state");
     bool same = h.n_rep == c->n_rep && h.nsp == c->ch.nsp && h.N == c->ch.N && h.precision == c->precision &&
                 h.T == c->T;
     for (int k = 0; same && k < c->ch.N; ++k) same = h.types[k] == c->ch.types[k];

@@ -233,3 +233,32 @@ def test_autotune_keeps_the_scales(hsf):
     ctx.evaluate()
     assert run(scales(), -3) and not run(scales(), -10)
     ctx.close()
+
+
+def test_state_version(hsf):
+    """A checkpoint with resident evaluations carries version 2, which a library without them
+    refuses, one with launches version 1 as ever; version 1 with the resident bit (bit 1 of the
+    fields' word) is taken as well, other versions are refused."""
+    wl = workload((12, 12, 12), W.chain(4, 4), "fp32")
+    ctx = hsf.Context(wl)
+    ctx.set_densities(W.initial_composition(wl).ravel())
+    ctx.step(1, tol=1e-5)
+    buf = ctx.get_state()
+    version = lambda b: int(b[8:12].view(np.int32)[0])   # after the 64-bit magic
+    assert version(buf) == 2
+    ctx.set_tile((32, 8, 2, -1))
+    assert version(ctx.get_state()) == 1 and not runs_resident(ctx)
+    ctx.set_state(buf)
+    assert runs_resident(ctx)
+    for v, ok in ((1, True), (0, False), (3, False)):
+        ctx.set_tile((32, 8, 2, -1))
+        other = buf.copy()
+        other[8:12] = np.frombuffer(np.int32(v).tobytes(), np.uint8)
+        if ok:
+            ctx.set_state(other)
+            assert runs_resident(ctx)
+        else:
+            with pytest.raises(hsf.HsfError):
+                ctx.set_state(other)
+            assert not runs_resident(ctx)
+    ctx.close()
