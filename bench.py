@@ -351,6 +351,7 @@ def run_arm(hsf, torch, wls, steps, warmup, timing, log, precond=False, tile=Non
     timing_out = {}
     t_elapsed = None
     t_steps = 0
+    t_site_evals = None
     if timing:
         # kernel-timing region: the same run continued with every hot kernel launched
         # directly and bracketed by HIP events (hipExtLaunchKernelGGL) on its stream
@@ -364,12 +365,22 @@ def run_arm(hsf, torch, wls, steps, warmup, timing, log, precond=False, tile=Non
         t_elapsed = time.perf_counter() - ta
         timing_out = ctx.get_timing()
         ctx.set_timing(False)
-    return ctx, tile, tune_ms, stats, (evals, site_evals), elapsed, timing_out, t_steps, t_elapsed
+        _, t_site_evals = ctx.get_work(reset=True)
+    return ctx, tile, tune_ms, stats, (evals, site_evals), elapsed, timing_out, t_steps, t_elapsed, t_site_evals
 
 
-def rooflines(timing, wls, tile, workload):
+def resident(timing):
+    """Whether the timed evaluations ran in one workgroup per replica: every tiling has forward
+    or backward launches beside its paired ones."""
+    launches = lambda k: timing.get(k, (0.0, 0))[1]
+    return launches("pair") > 0 and launches("fwd") == 0 and launches("bwd") == 0
+
+
+def rooflines(timing, wls, tile, workload, site_evals=None):
     """Per-kernel event times, and the rooflines of the dominant propagator kernel and of
-    the LB kernel: achieved = algorithmic bytes per launch / average launch time."""
+    the LB kernel: achieved = algorithmic bytes per launch / average launch time.  site_evals:
+    evaluations times sites of the timed region, for resident evaluations, whose launches
+    hold any number of them."""
     wl = wls[0]
     V_total = sum(w.V for w in wls)
     N = wl.N
@@ -379,7 +390,18 @@ def rooflines(timing, wls, tile, workload):
             kernels[k] = {"launches": cnt, "avg_us": 1e3 * ms / cnt, "total_ms": ms}
     prop_roof = lb_roof = None
     prop = {k: v for k, v in kernels.items() if k in ("fwd", "bwd", "pair")}
-    if prop:
+    if resident(timing):
+        b_unit, t = bytes_per_update(wl), kernels["pair"]["total_ms"] * 1e-3
+        units = 2 * N * site_evals if site_evals else None
+        achieved = b_unit * units / t / 1e9 if units else None
+        launches = kernels["pair"]["launches"]
+        prop_roof = {"bound": "instructions of one CU per replica", "kernel": "k_resident", "achieved": achieved,
+                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS if units else None,
+                     "traffic": None, "traffic_unit": "bytes per launch (counters)", "traffic_frac": None,
+                     "algorithmic_bytes_per_launch": b_unit * units / launches if units else None,
+                     "bytes_per_update": b_unit, "updates_per_launch": units / launches if units else None,
+                     "avg_launch_us": kernels["pair"]["avg_us"]}
+    elif prop:
         dom = max(prop, key=lambda k: prop[k]["total_ms"])
         avg_s = prop[dom]["avg_us"] * 1e-6
         # paired sweeps take 2N - 1 of an evaluation's 2N steps, in N launches of one step
@@ -451,12 +473,12 @@ def drift_arm(hsf, torch, steps, log):
 def short_run(hsf, torch, name, steps, warmup, log, precond):
     """A shorter run of another configuration: throughput, step time and rooflines."""
     wls = make_workloads(name, "fp32")
-    ctx, tile, _, _, (ev, se), el, timing, _, _ = run_arm(hsf, torch, wls, steps, warmup, True, log, precond)
-    kernels, roof, lb = rooflines(timing, wls, tile, name)
+    ctx, tile, _, _, (ev, se), el, timing, _, _, t_se = run_arm(hsf, torch, wls, steps, warmup, True, log, precond)
+    kernels, roof, lb = rooflines(timing, wls, tile, name, t_se)
     ctx.close()
     return {"workload": name, "replicas": len(wls), "sites": sum(w.V for w in wls), "steps": steps,
             "value": 2 * wls[0].N * se / el, "unit": "site·bead updates/s", "ms_per_step": 1e3 * el / steps,
-            "evals_per_step": ev / steps, "tile": list(tile), "solver": "preconditioned FR" if precond else "FR",
+            "evals_per_step": ev / steps, "tile": "resident" if resident(timing) else list(tile), "solver": "preconditioned FR" if precond else "FR",
             "roofline": roof, "lb_roofline": lb}
 
 
@@ -571,7 +593,7 @@ def main():
         wls = [w.with_(lb="mrt", gammas=W.mrt_gammas(w.tau)) for w in wls]
     wl = wls[0]
     precond = wl.has_solvent if args.precond == "auto" else args.precond == "on"
-    ctx, tile, tune_ms, stats, (evals, site_evals), elapsed, timing, t_steps, t_elapsed = run_arm(
+    ctx, tile, tune_ms, stats, (evals, site_evals), elapsed, timing, t_steps, t_elapsed, t_se = run_arm(
         hsf, torch, wls, args.steps, args.warmup, not args.no_timing, log, precond,
         tuple(int(v) for v in args.tile.split(",")) if args.tile else None, args.noise)
 
@@ -579,7 +601,7 @@ def main():
     N = wl.N
     # every evaluation of every replica counts 2 N V_r site-bead updates
     value = 2 * N * site_evals / elapsed
-    kernels, roofline, lb_roofline = rooflines(timing, wls, tile, args.workload) if timing else ({}, None, None)
+    kernels, roofline, lb_roofline = rooflines(timing, wls, tile, args.workload, t_se) if timing else ({}, None, None)
 
     err = floor = boundary = None
     if not args.lean:
@@ -653,7 +675,8 @@ def main():
         "evals_per_step": evals / args.steps,
         "iterations_last_step": [s["iterations"] for s in stats][:8],
         "lb_mlups": lb_roofline["mlups"] if lb_roofline else None,
-        "tile": {"core": list(tile[:3]), "steps_per_launch": max(1, abs(tile[3])), "paired": tile[3] < 0,
+        "tile": {"resident": True, "autotune_ms_per_eval": tune_ms} if resident(timing) else
+                {"core": list(tile[:3]), "steps_per_launch": max(1, abs(tile[3])), "paired": tile[3] < 0,
                  "autotune_ms_per_eval": tune_ms},
         "kernels": kernels,
         "kernel_timing_region": {"steps": t_steps,

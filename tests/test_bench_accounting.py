@@ -54,3 +54,26 @@ def test_rooflines_from_launch_times(bench):
     # counters taken for one tiling do not describe another
     _, prop2, _ = bench.rooflines({"pair": (19.5, 1000)}, wls, (32, 8, 2, -1), "vesicle128_a3b9s")
     assert prop2["traffic"] is None and prop2["traffic_frac"] is None
+
+
+def test_resident_evaluations(bench):
+    """One workgroup per replica: a launch holds a whole inversion part, so the rate is that of the
+    counted evaluations over the kernels' time and not of the tiling that is not in use."""
+    wls = bench.make_workloads("melt16_a4b4", "fp64")
+    V = 16 ** 3
+    timing = {"pair": (4.5, 20), "fwd": (0.0, 0), "bwd": (0.0, 0), "lb": (0.1, 10)}
+    kernels, prop, lb = bench.rooflines(timing, wls, (32, 8, 2, -1), "melt16_a4b4", 120 * V)
+    assert prop["kernel"] == "k_resident"
+    units = 2 * 8 * 120 * V          # 120 evaluations of 2 N V updates
+    b = bench.bytes_per_update(wls[0])
+    assert prop["achieved"] == pytest.approx(b * units / 4.5e-3 / 1e9)
+    assert prop["frac"] == pytest.approx(prop["achieved"] / 8000.0)
+    assert prop["updates_per_launch"] == pytest.approx(units / 20)
+    assert prop["algorithmic_bytes_per_launch"] == pytest.approx(b * units / 20)
+    assert prop["traffic"] is None and prop["traffic_frac"] is None
+    # without the count nothing is claimed
+    _, prop, _ = bench.rooflines(timing, wls, (32, 8, 2, -1), "melt16_a4b4")
+    assert prop["kernel"] == "k_resident" and prop["achieved"] is None and prop["frac"] is None
+    # a tiling has backward launches
+    assert not bench.resident({"pair": (1.0, 8), "bwd": (0.1, 1)}) and not bench.resident({"fwd": (1.0, 8), "bwd": (1.0, 8)})
+    assert not bench.resident({})
