@@ -165,9 +165,7 @@ void static_rows_pass(hipStream_t s, const TileCfg &tile, const Plan &plan, cons
     real *Gf[2] = {Gf0, Gf1};
     if (scales_only) {
         for (int j = 1; j <= rows_blocks_of(N, K); ++j) {
-            RowsLaunch l = rows_schedule(N, K, j);
-            l.has_g = false;
-            l.f.late = l.f.from_pp = l.f.out = 0;   // every G_s in its slot
+            const RowsLaunch l = rows_forward(N, K, j);
             launch_rows<real>(tile, s, rplan, rep, st, ch, l, b, nullptr, nullptr, nullptr, nullptr, partG, 1, nullptr,
                               nullptr);
         }
