@@ -350,8 +350,9 @@ bool in_place(const void *p, size_t n, int where)
         (void)hipGetLastError();
         return false;
     }
-    return a.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && a.device == dev &&
-           n * sizeof(double) <= size - (size_t)((const char *)p - (const char *)base);
+    const size_t at = (size_t)((const char *)p - (const char *)base);
+    return a.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && a.device == dev && at <= size &&
+           n * sizeof(double) <= size - at;
 }
 
 template <typename real>
