@@ -13,6 +13,7 @@
 #include <cmath>
 #include <deque>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "hsf_internal.h"
@@ -1360,15 +1361,35 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     ALLOC(c->rep_d, sizeof(Rep) * n_rep);
     ALLOC(c->st_d, sizeof(RepState) * n_rep);
     ALLOC(c->st_save, sizeof(RepState) * n_rep);
-    ALLOC(c->plan.blk_rep, sizeof(int) * blk_rep.size());
-    ALLOC(c->plan.blk_first, sizeof(int) * blk_first.size());
-    for (int k = 0; k < 2; ++k) {
-        Plan &p = k ? c->cdplan : c->muplan;
-        ALLOC(p.blk_rep, sizeof(int) * kblk_rep[k].size());
-        ALLOC(p.blk_first, sizeof(int) * kblk_first[k].size());
+    // the block tables of all plans in one allocation, those that stay as they are in one copy (each
+    // allocation and each copy of its own costs a context of a small box about 10 us)
+    int *tables = nullptr;
+    std::vector<int> table;
+    std::vector<std::pair<int **, size_t>> places;   // pointer to set and its offset
+    auto aligned = [](size_t n) { return (n + 63) / 64 * 64; };
+    auto keep = [&](int *&at, const std::vector<int> &v) {
+        places.push_back({&at, table.size()});
+        table.insert(table.end(), v.begin(), v.end());
+        table.resize(aligned(table.size()));
+    };
+    keep(c->plan.blk_rep, blk_rep);
+    keep(c->plan.blk_first, blk_first);
+    keep(c->muplan.blk_rep, kblk_rep[0]);
+    keep(c->muplan.blk_first, kblk_first[0]);
+    keep(c->cdplan.blk_rep, kblk_rep[1]);
+    keep(c->cdplan.blk_first, kblk_first[1]);
+    keep(c->cplan.blk_rep, cblk_rep);
+    keep(c->cplan.blk_first, cblk_first);
+    size_t n_tables = table.size();
+    for (Plan *p : {&c->tplan, &c->rplan, &c->rplan64}) {   // written by set_tile
+        places.push_back({&p->blk_rep, n_tables});
+        n_tables += aligned(c->max_tile_blocks);
+        places.push_back({&p->blk_first, n_tables});
+        n_tables += aligned(n_rep + 1);
     }
-    ALLOC(c->cplan.blk_rep, sizeof(int) * cblk_rep.size());
-    ALLOC(c->cplan.blk_first, sizeof(int) * cblk_first.size());
+    ALLOC(tables, sizeof(int) * n_tables);
+    if (rc == HSF_OK)
+        for (auto &p : places) *p.first = tables + p.second;
     ALLOC(c->w, sizeof(double) * nsp * T);
     ALLOC(c->w_start, sizeof(double) * nsp * T);
     ALLOC(c->phi, sizeof(double) * nsp * T);
@@ -1389,12 +1410,6 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     ALLOC(c->part, sizeof(double) * kNQ * max_blocks);
     c->part_cap = kNQ * max_blocks;
     ALLOC(c->partG, sizeof(double) * (N + 2) * max_blocks);
-    ALLOC(c->tplan.blk_rep, sizeof(int) * c->max_tile_blocks);
-    ALLOC(c->tplan.blk_first, sizeof(int) * (n_rep + 1));
-    for (Plan *p : {&c->rplan, &c->rplan64}) {
-        ALLOC(p->blk_rep, sizeof(int) * c->max_tile_blocks);
-        ALLOC(p->blk_first, sizeof(int) * (n_rep + 1));
-    }
     ALLOC(c->E, rs * 2 * T);
     ALLOC(c->G, rs * N * T);
     ALLOC(c->Gp0, rs * T);
@@ -1430,21 +1445,7 @@ int hsf_create(const hsf_params *reps, int n_rep, hsf_ctx **out)
     memset(st0.data(), 0, sizeof(RepState) * n_rep);
     if (e == hipSuccess) e = hipMemcpy(c->rep_d, c->reps.data(), sizeof(Rep) * n_rep, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->st_d, st0.data(), sizeof(RepState) * n_rep, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(c->plan.blk_rep, blk_rep.data(), sizeof(int) * blk_rep.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(c->plan.blk_first, blk_first.data(), sizeof(int) * blk_first.size(), hipMemcpyHostToDevice);
-    for (int k = 0; k < 2; ++k) {
-        Plan &p = k ? c->cdplan : c->muplan;
-        if (e == hipSuccess)
-            e = hipMemcpy(p.blk_rep, kblk_rep[k].data(), sizeof(int) * kblk_rep[k].size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess)
-            e = hipMemcpy(p.blk_first, kblk_first[k].data(), sizeof(int) * kblk_first[k].size(), hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess)
-        e = hipMemcpy(c->cplan.blk_rep, cblk_rep.data(), sizeof(int) * cblk_rep.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(c->cplan.blk_first, cblk_first.data(), sizeof(int) * cblk_first.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(tables, table.data(), sizeof(int) * table.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->w, 0, sizeof(double) * nsp * T);
     if (e == hipSuccess) e = hipMemset(c->phi, 0, sizeof(double) * nsp * T);
     if (e == hipSuccess) e = hipMemset(c->d, 0, sizeof(double) * 2 * T);
