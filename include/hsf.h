@@ -41,9 +41,10 @@
  *
  * Pointers: every data argument is either a host pointer (where = HSF_HOST;
  * the call copies synchronously) or a device pointer on the context's GPU
- * (where = HSF_DEVICE; the copy is ordered on the context's stream).  The
- * caller owns the buffers it passes; the library never keeps them past the
- * call.  The library owns all of its internal device memory.
+ * (where = HSF_DEVICE; the copy, or the kernels where they use the buffer
+ * themselves, are ordered on the context's stream).  The caller owns the buffers
+ * it passes; the library keeps them no longer than the work that the call
+ * enqueues.  The library owns all of its internal device memory.
  *
  * Errors: every int-returning call returns HSF_OK (0) or a negative code;
  * hsf_last_error() gives a message.  A context is not thread safe; distinct
@@ -415,7 +416,8 @@ int hsf_get_work(hsf_ctx *ctx, long long *evals, double *site_evals, int reset);
  * (HSF_EINVAL otherwise); results do not depend on the choice beyond rounding.
  * hsf_autotune times one density-functional evaluation `reps` times with every
  * configuration with k <= 0 that suits the replicas' boxes (those with k > 0 were never
- * the fastest) and keeps the fastest (best_ms, may be NULL, receives its time).  It leaves densities, fields and LB state unchanged. */
+ * the fastest) and keeps the fastest (best_ms, may be NULL, receives its time).  It leaves
+ * densities, fields, per-step scales and LB state unchanged. */
 int hsf_set_tile(hsf_ctx *ctx, const int cfg[4]);
 int hsf_get_tile(const hsf_ctx *ctx, int cfg[4]);
 int hsf_autotune(hsf_ctx *ctx, int reps, double *best_ms);

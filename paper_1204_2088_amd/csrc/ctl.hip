@@ -160,8 +160,8 @@ void launch_reduce_ctl(hipStream_t s, int n_rep, const Plan &p, RepState *st, co
 // blocks of 256 sites and 11 us in the control kernel).  E (or null): also the polymers' field
 // factors exp(-w), as launch_field_exp writes them, from the same read of w.
 // Bound by its loads: those of four sites are issued together, unconditionally (128^3 solution,
-// FP32 with field factors: 19.6 us, 118 MB at 6.0 TB/s; 27.6 with a bounds test between the
-// sites, which left one site's loads in flight).
+// FP32 with field factors: 24.4 us in a kernel trace, 118 MB at 4.8 TB/s, the rate of a copy; 32.7 with a
+// bounds test between the sites, which left one site's loads in flight).
 template <bool SOLVENT, typename real>
 __global__ __launch_bounds__(kBlock) void k_target_stats(const int *__restrict__ blk_rep,
                                                          const int *__restrict__ blk_first,

@@ -17,10 +17,10 @@
 // in the one-step kernels, so the densities are bit for bit those of the one-step
 // sequence (up to the order of Q's sum over workgroups).
 //
-// Measured against the one-step paired kernels (per evaluation, all its launches, device
-// buffers): FP32 64^3 pair 142 against 202 us (4 launches of 16.4 us for 16 of 7.8 us), 96^3
-// 241 / 257, 128^3 297 / 380 (6 of 23.0 for 12 of 18.5), 192^3 1226 / 1434, 12 solutions of
-// 32^3 to 64^3 266 / 326; FP64 64^3 143 / 203, 128^3 496 / 636 (6 of 48.3 for 12 of 36.3).
+// Measured against the one-step paired kernels (hsf_evaluate calls with device buffers, the best
+// tiling of each kind): FP32 64^3 pair 116 against 179 us (4 launches of 16.2 us for 16 of 8.0 us), 96^3
+// 203 / 228, 128^3 221 / 308 (6 of 22.4 for 12 of 18.4), 192^3 1040 / 1300, 12 solutions of
+// 32^3 to 64^3 205 / 271; FP64 64^3 pair 160 / 231, 128^3 419 / 506 (6 of 48.0 for 12 of 31.5).
 // At 128^3 a launch of the 128x8x4 K = 2 bundle moves 94 MB by the counters (20.3 us inside an
 // inversion, 4.6 TB/s) with the vector units issuing 37 % of the time: it is bound by the latency
 // of its phases (load, step, step, store) and by bytes, about equally.

@@ -16,9 +16,9 @@
 // Bound by the instructions of one CU (a replica has no more): an evaluation of 16^3 A4B4 in
 // FP64 takes 35.8 us (80 with the box's strides, 61 before the x neighbours and the wavefront
 // sums moved from LDS to DPP, 39 with both rows' x neighbours summed), an hsf_evaluate call 52
-// us against 90 by launches, a coupled step 1.61 ms against 3.3.  Up to 512 replicas the chain of launches is never
-// faster: 4^3 45 us against 68, 16^3 46 against 68 (one replica, FP32), 115 against 378 (512 of
-// 16^3).  With more, boxes of at most 64 sites leave too many threads idle (1024 of 8^3 169 us
+// us against 90 by launches, a coupled step 1.61 ms against 3.3.  Up to 256 replicas, one per CU, the chain of launches is
+// never faster: 4^3 45 us against 68, 16^3 46 against 68 (one replica, FP32); 512 of 16^3 115
+// against 378.  With more, boxes of at most 64 sites leave too many threads idle (1024 of 8^3 169 us
 // against 214, 1024 of 4^3 with 8 beads 167 against 174, with 64 beads 782 against 729, 4096 of 4^3 606 against
 // 536), so hsf_autotune times both.  Larger boxes do not fit: 32^3 would need 8 times the LDS.
 //
