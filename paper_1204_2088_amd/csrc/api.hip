@@ -986,7 +986,7 @@ bool direct_launches(const hsf_ctx *c)
     const int N = c->ch.N, K = std::max(1, c->tile.k), sweeps = (N + K - 1) / K;
     const bool rows = tile_is_rows(c->tile) && N >= 2;
     const int launches = rows ? rows_launches(N, -c->tile.k) + 4 : c->tile.k < 0 ? N + 4 : 2 * sweeps + 4;
-    return launches <= 24 || c->T >= (rows ? 1 << 17 : 3 << 18);
+    return !c->use_graphs || launches <= 24 || c->T >= (rows ? 1 << 17 : 3 << 18);
 }
 
 // One evaluation of the density functional at the current fields, with phibar from the

@@ -68,3 +68,32 @@ def test_dynamics_in_a_graph(hsf, record_update, before):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
     assert not np.array_equal(out[0][0], W.initial_composition(wl).ravel())
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("L,n", [((20, 18, 16), 7), ((1, 256, 40), 8), ((9, 7, 5), 1)])
+def test_static_evaluation_in_a_graph(hsf, precision, L, n):
+    """The allocation-free evaluation recorded once (row sweeps, one-step sweeps, a chain of one bead)
+    and replayed on new fields, against direct calls on the same fields."""
+    import torch
+    types = W.chain(n // 2, n - n // 2)
+    wl = W.Workload("recorded", L, types, False, W.chi_matrix(ab=15 / n), tau=1.0, noise=0.2, seed=3, precision=precision)
+    phi = W.initial_composition(wl) if n > 1 else np.stack([np.zeros(wl.shape), np.ones(wl.shape)])
+    pd = torch.from_numpy(phi.ravel().copy()).cuda()
+    w, out, ref = (torch.zeros_like(pd) for _ in range(3))
+    q, qref = (torch.zeros(1, dtype=torch.float64, device="cuda") for _ in range(2))
+    fields = [torch.from_numpy(W.random_fields((2,) + wl.shape, seed=k, amplitude=0.5 + k, smooth=1).ravel().copy()).cuda()
+              for k in range(3)]
+    assert hsf.evaluate_static(wl, w, pd, out, q) == hsf.HSF_OK
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        assert hsf.evaluate_static(wl, w, pd, out, q, stream=stream) == hsf.HSF_OK
+    for f in fields + fields[:1]:
+        w.copy_(f)
+        g.replay()
+        torch.cuda.synchronize()
+        assert hsf.evaluate_static(wl, f, pd, ref, qref) == hsf.HSF_OK
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(q, qref)
